@@ -85,10 +85,13 @@ typedef struct plc_graph plc_graph;
 
 /*
  * The plain path's edge scatter (Sec. 3.3, UpdateNgh as a fetch-and-add) has
- * two forms.  Small rounds: one FP64 atomic add per edge.  Rounds of at
+ * three forms.  Small rounds: one FP64 atomic add per edge.  Rounds of at
  * least bin_min_edges edges: destination-binned -- the round's (neighbour,
  * entry) pairs are sorted by destination range, each range's contributions
- * are summed in LDS, and every touched r[w] gets one update.  Results agree
+ * are summed in LDS, and every touched r[w] gets one update.  Rounds that
+ * cover a good part of the graph's arcs: dense -- every vertex sums over its
+ * own arcs (with 0, where that is the cheaper form; with a fixed threshold,
+ * from half the arcs and the threshold on).  Results agree
  * to the order of the additions.  bin_min_edges: 0 = 524288, which
  * plc_autotune may change per graph (it also tries four times that and no
  * binning); > 0 = that threshold, kept by plc_autotune; < 0 = always the
@@ -167,8 +170,8 @@ typedef struct {
    * the end of its sweep; batched path, from its admission into a slot to the
    * end of its sweep (so it includes rounds shared with other queries) */
   int64_t device_ns;
-  /* plain path only: rounds whose edge scatter went through the destination
-   * bins (plc_options.bin_min_edges), and their edges */
+  /* plain path only: rounds of at least plc_options.bin_min_edges edges whose
+   * edge scatter was binned or dense, and their edges */
   int32_t bin_rounds;
   uint32_t flags;     /* the query's flags */
   int64_t bin_edges;
@@ -182,8 +185,8 @@ typedef struct {
    * query finished pushing */
   int32_t table_grows;
   int64_t table_cap;
-  /* plain path only: among bin_rounds, the rounds of at least half the
-   * graph's arcs, which the bins pull from their own vertices' arcs */
+  /* plain path only: among bin_rounds, the dense rounds of at least half the
+   * graph's arcs */
   int32_t pull_rounds;
   int32_t reserved;
 } plc_result_info;

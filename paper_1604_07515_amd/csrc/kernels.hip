@@ -15,14 +15,15 @@
 //             frontier exactly when one atomic's (old, old + c) pair straddles
 //             eps*d(w); that atomic appends w.  On rounds of at least the
 //             binning threshold it is pass A of the binned scatter instead
-//             (pairs sorted into destination bins), and on rounds over half
-//             the arcs it only stamps the frontier's coefficients.
+//             (pairs sorted into destination bins).
 //   k_bin_apply  pass B of a binned round (LDS sums per bin, one update per
-//             touched destination) or the pull form; it exits at once on the
-//             other rounds.  The host leaves it out where no round can bin,
-//             and in a query's first chunk behind the launches where recent
-//             queries had no round large enough (k_scatter then takes the
-//             atomic form whatever the round's size).
+//             touched destination); it exits at once on the other rounds.
+//             The host leaves it out where no round can bin, and in a
+//             query's first chunk behind the launches where recent queries
+//             had no round large enough (k_scatter then takes the atomic
+//             form whatever the round's size).
+// Rounds that cover a good part of the arcs are dense: one launch of k_dense
+// each, queued in a row once a query has got there.
 // A frontier of at most one scan block is handled by k_self alone: its last
 // workgroup to arrive runs such rounds back to back (self step, scan, edge
 // scatter, round close) until the frontier grows, empties or a round has
@@ -65,9 +66,11 @@ __global__ void k_graph_init(PlainArgs a) {
     a.vr[v] = rec;
     a.p[v] = 0.0;
     a.hk_r1[v] = 0.0;
-    if (a.pull) a.pull[v] = PullRec{0.0, 0u, 0};
+    if (a.cd[0]) {
+      a.cd[0][v] = 0.0;
+      a.cd[1][v] = 0.0;
+    }
   }
-  if (a.pull_epoch && blockIdx.x == 0 && threadIdx.x == 0) *a.pull_epoch = 1u;
 }
 
 __device__ __forceinline__ void reset_round_book(Ctl* c) {
@@ -83,6 +86,12 @@ __device__ __forceinline__ void reset_round_book(Ctl* c) {
   c->bin_edges = 0;
   c->t_start = (long long)wall_clock64();
   c->t_end = 0;
+  c->dense = DN_LIST;
+  c->enext = 0;
+  c->fill = 0;
+  c->pairs0 = 0;
+  c->dsteps = 0;
+  c->dself = 0;
 }
 
 // Seed initialisation (Fig. alg:pr-nibble: r = {(x,1)}, Frontier = {x}).
@@ -211,6 +220,19 @@ __global__ void k_query_init_set(PlainArgs a, int32_t nseeds, int32_t rule, doub
 
 // ---------------------------------------------------------------- round
 
+// The head of the control block, read at once: without the pin the compiler
+// loads each field behind the test of the one before, a chain of cache
+// misses at the start of every launch.
+struct CtlHead {
+  int32_t status, round, cnt0, cnt1, dense, selfed;
+};
+__device__ __forceinline__ CtlHead ctl_head(const Ctl* c) {
+  CtlHead h{c->status, c->round, c->cnt[0], c->cnt[1], c->dense, c->selfed};
+  asm volatile("" : "+s"(h.status), "+s"(h.round), "+s"(h.cnt0), "+s"(h.cnt1), "+s"(h.dense),
+               "+s"(h.selfed));
+  return h;
+}
+
 __device__ __forceinline__ bool push_active(const Ctl* c, int64_t ncap, int* t_out, int* nf_out) {
   if (c->status != ST_PUSH) return false;
   int t = c->round;
@@ -251,7 +273,10 @@ __device__ __forceinline__ double* hk_res(const PlainArgs& a, int k, int32_t v) 
 //   Nibble step j -> j+1 (Fig. alg:nibble): coefficient rho / (2 d), and
 //     rho / 2 kept per entry for the scatter, which adds it to the vertex's
 //     own next value; the same clearing as HK-PR.
-template <int MODE>
+//   LIGHT (a round handed back by the dense form): the self step was taken
+//     there; the entries take their coefficients from cd[t & 1], which is
+//     cleared again.
+template <int MODE, bool LIGHT>
 __device__ __forceinline__ void self_body(const PlainArgs& a, int slot) {
   constexpr bool HK = MODE == kModeHK;
   constexpr bool LEVELS = MODE != kModePR;
@@ -292,8 +317,9 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot) {
   // a frontier of one scan block is handled by workgroup 0 alone, with no
   // ticket and no look-back (its exclusive prefix is 0; no descriptor is
   // published and the scan site is left as it was)
-  const bool solo = nblk == 1;
+  const bool solo = nblk == 1 && !LIGHT;
   if (solo && blockIdx.x != 0) return;
+  double* const cd = LIGHT ? a.cd[t & 1] : nullptr;
   if (threadIdx.x == 0) { s_nsup = 0; s_nstay = 0; }
   __syncthreads();
 
@@ -320,8 +346,12 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot) {
       bool stay = false, sup = false;
       if (i < nf) {
         v = F[i];
-        double rho;
-        if (LEVELS) {
+        double rho = 0.0;
+        if (LIGHT) {
+          const VRec rec = a.vr[v];
+          d = rec.deg;
+          stay = !opt && rec.r >= eps * (double)d;  // (r is keep rho already)
+        } else if (LEVELS) {
           rho = *hk_res(a, t, v);
           d = a.vr[v].deg;
         } else {
@@ -329,8 +359,11 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot) {
           rho = rec.r;
           d = rec.deg;
         }
-        double pold = MODE == kModeNB ? 1.0 : a.p[v];
-        if (MODE == kModeNB) {
+        double pold = MODE == kModeNB || LIGHT ? 1.0 : a.p[v];
+        if (LIGHT) {
+          a.coef[i] = cd[v];
+          cd[v] = 0.0;
+        } else if (MODE == kModeNB) {
           a.coef[i] = rho / (2.0 * (double)d);
           a.sp[i] = rho / 2.0;
         } else if (HK) {
@@ -381,6 +414,12 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot) {
     if (MODE != kModeNB)
       block_flush(&c->support_cnt, a.support, a.n, s_sup, &s_nsup, &s_base, &c->fault);
     if (!opt) block_flush(cntn, Fn, a.n, s_stay, &s_nstay, &s_base, &c->fault);
+  }
+  // (every workgroup has read the state it decided on by the time the last
+  // one gets here)
+  if (LIGHT && last_block(&c->done[DONE_DENSE], &s_base, false) && threadIdx.x == 0) {
+    c->dense = DN_LIST;
+    c->cd_dirty = 0;
   }
 }
 
@@ -601,6 +640,385 @@ __device__ void loop_rounds(const PlainArgs& a, int slot, int t, int nf) {
   }
 }
 
+// ---------------------------------------------------------------- dense rounds
+//
+// A round whose frontier's edges are a good part of the graph's arcs needs
+// neither atomics nor pairs: every row w sums the coefficients of its
+// neighbours, read from the dense array cd[t & 1] (0 off the frontier).  The
+// row's sum is complete in one place, so the same lane takes w's next self
+// step at once (p, r, and w's coefficient for round t + 1 into
+// cd[(t + 1) & 1]): a round is one launch with no frontier list.
+// Bound: one random 8-byte load of cd per arc (the neighbour ids stream).
+// A workgroup takes a block of rows with at most kDenseArcs arcs, so that its
+// products fit 16 KB of LDS and seven workgroups share a CU; rows are then
+// summed by 256 / rows lanes each, and a block's rows times its longest row
+// is bounded so that no lane sums more than 64 products.  Longer rows are cut
+// into pieces that add up in dacc; the last piece finishes the row.
+
+struct DenseLds {
+  double prod[kDenseArcs];
+  double sum[kDenseRows];
+  int roff[kDenseRows + 1];
+  int32_t sup[kDenseRows], tv[kDenseRows], fn[kDenseRows];
+  double wsum[kBlock / 64];
+  long long wcnt[2 * kBlock / 64];
+  int nsup, ntv, nfn, base;
+};
+
+// A round of E edges is cheaper dense: a dense round costs one launch and
+// every arc once, the other forms a launch more (about kDenseBase arcs'
+// worth) and about kDenseRatio times as much per edge.
+__device__ __forceinline__ bool dense_pays(const PlainArgs& a, long long E) {
+  if (a.cd[0] == nullptr || a.bin_emin >= kBinOff) return false;
+  if (a.dense_free) return a.vol_total <= kDenseBase + kDenseRatio * E;
+  return E >= a.bin_emin && E >= a.dense_emin;
+}
+
+// Whether the dense round t takes the next self step too: not if the push may
+// not go on or the next frontier has to be ranked first (beta); PR-Nibble then
+// lists the next frontier.
+template <int MODE>
+__device__ __forceinline__ bool dense_fuses(const Ctl* c, int t) {
+  return MODE == kModeHK ? t + 1 < c->hk_N : t + 1 < c->max_rounds && c->beta >= 1.0;
+}
+
+// The frontier of round t as the dense round before it counted it (counts of
+// an earlier launch), by one whole wave; the counts are cleared.
+__device__ __forceinline__ int dense_count(const PlainArgs& a, int t) {
+  static_assert(kDenseGroups == 64, "one group per lane");
+  int x = a.dgrp[PLC_LANE].nf[t & 1];
+  a.dgrp[PLC_LANE].nf[t & 1] = 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+  return x;
+}
+
+struct DenseCtl {
+  int32_t max_rounds, opt_rule, cd_dirty, hk_N;
+  double eps, cs, cn, keep, beta, hk_t, hk_A;
+};
+
+// Round t in the dense form, k the workgroup's first block and b its record
+// (loaded ahead of the control block).
+template <int MODE>
+__device__ __forceinline__ void dense_round(const PlainArgs& a, int slot, DenseLds& L, int k,
+                                            DenseBlk b, int t, int nf, int selfed,
+                                            const DenseCtl& q) {
+  constexpr bool HK = MODE == kModeHK;
+  Ctl* c = a.ctl;
+  const bool hk_last = HK && t + 1 == q.hk_N;
+  const bool fuse = HK ? !hk_last : t + 1 < q.max_rounds && q.beta >= 1.0;
+  // the list self step listed what stays, and beta carries what it did not
+  // push: then only crossings join the list
+  const bool listed = !fuse && selfed == t;
+  const bool wipe = (q.cd_dirty >> ((t + 1) & 1)) & 1;
+  const bool opt = q.opt_rule != 0;
+  const double cs = q.cs, cn = q.cn, keep = q.keep;
+  const double eps = HK ? q.hk_A : q.eps;
+  const double den = HK && !hk_last ? a.hk_B[t + 1] : 1.0;
+  const double hk_t = q.hk_t;
+  const bool hk_next_last = HK && t + 2 == q.hk_N;
+  const double* const cd = a.cd[t & 1];
+  double* const cdn = a.cd[(t + 1) & 1];
+  int32_t* const Fn = (t & 1) ? a.fbuf0 : a.fbuf1;
+  const int tid = threadIdx.x;
+  if (tid == 0) { L.nsup = 0; L.ntv = 0; L.nfn = 0; }
+  long long my_nf = 0, my_e = 0;
+
+  // the row's end: its residual, and its next self step when it is active
+  auto finish = [&](bool on, int32_t w, int32_t d, double s, double rold, double pold) {
+    bool sup = false, touch = false, list = false;
+    on = on && d > 0;
+    if (on) {
+      bool act;
+      double r = s;
+      if (HK) {
+        const double thr = (eps * (double)d) / den;
+        act = !hk_last && 0.0 < thr && s >= thr;
+        if (hk_last && s != 0.0) {
+          a.p[w] = pold + s;
+          sup = pold == 0.0;
+        }
+      } else {
+        const double thr = eps * (double)d;
+        r = rold + s;
+        act = listed ? rold < thr && r >= thr : r > 0.0 && r >= thr;
+        touch = s != 0.0 && __double_as_longlong(rold) == 0;
+        if (!(act && fuse) && s != 0.0) a.vr[w].r = r;
+      }
+      double x = 0.0;
+      if (act) {
+        list = !fuse;
+        if (fuse) {
+          my_nf += 1;
+          my_e += d;
+          a.p[w] = HK ? pold + r : pold + cs * r;
+          sup = pold == 0.0;
+          if (HK) {
+            x = hk_next_last ? r / (double)d : (hk_t * r) / ((double)(t + 2) * (double)d);
+          } else {
+            a.vr[w].r = opt ? -0.0 : keep * r;
+            x = (cn * r) / (double)d;
+          }
+        }
+      }
+      if (fuse || wipe) cdn[w] = x;
+    }
+    wave_append(sup, w, L.sup, &L.nsup);
+    if (!HK) {
+      wave_append(touch, w, L.tv, &L.ntv);
+      wave_append(list, w, L.fn, &L.nfn);
+    }
+  };
+
+  for (;;) {
+    const bool piece = b.lid >= 0;
+    const int R = piece ? 1 : b.nrows;
+    constexpr int kPer = kDenseArcs / kBlock;
+    static_assert(kDenseRows == kBlock, "one row per thread");
+    int32_t u[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; j++) {
+      // (a block has arcs; past its last one that one is read again)
+      const int e = j * kBlock + tid;
+      u[j] = a.nbr[b.first + (e < b.len ? e : b.len - 1)];
+    }
+    // the thread's row (a piece: the row, once it is complete)
+    const int32_t w = b.row + (tid < R ? tid : R - 1);
+    const long long o = a.off[w];
+    const VRec rec = a.vr[w];
+    const double pold = a.p[w];
+    double x[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; j++) x[j] = cd[u[j]];
+    if (piece) {
+      double s = 0.0;
+#pragma unroll
+      for (int j = 0; j < kPer; j++) s += j * kBlock + tid < b.len ? x[j] : 0.0;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      if (PLC_LANE == 0) L.wsum[PLC_WID] = s;
+      __syncthreads();
+      if (tid < 64) {  // one wave: the appends are ballots
+        bool last = false;
+        if (tid == 0) {
+          s = 0.0;
+          for (int w = 0; w < kBlock / 64; w++) s += L.wsum[w];
+          // the addition has returned, so it is in place, before it is counted
+          const double before = unsafeAtomicAdd(&a.dacc[b.lid], s);
+          unsigned one = 1;
+          asm volatile("" : "+v"(one) : "v"(before));
+          last = atomicAdd(&a.dcnt[b.lid], one) == (unsigned)b.nrows - 1;
+        }
+        if (last) {
+          s = ld_agent(&a.dacc[b.lid]);
+          st_agent(&a.dacc[b.lid], 0.0);
+          st_agent(&a.dcnt[b.lid], 0u);
+        }
+        finish(last, w, rec.deg, s, rec.r, pold);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < kPer; j++) L.prod[j * kBlock + tid] = x[j];
+      if (tid < R) L.roff[tid] = (int)(o - b.first);
+      if (tid == 0) L.roff[R] = b.len;
+      __syncthreads();
+      // lanes per row: a power of two, at most a wave
+      int tpr = 1;
+      while (2 * tpr * R <= kBlock && tpr < 64) tpr *= 2;
+      const int l = tid & (tpr - 1);
+      for (int i = tid / tpr; i < R; i += kBlock / tpr) {
+        // (four sums: their LDS reads are in flight together)
+        double s = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+        const int e1 = L.roff[i + 1];
+        int e = L.roff[i] + l;
+        for (; e + 3 * tpr < e1; e += 4 * tpr) {
+          s += L.prod[e];
+          s1 += L.prod[e + tpr];
+          s2 += L.prod[e + 2 * tpr];
+          s3 += L.prod[e + 3 * tpr];
+        }
+        for (; e < e1; e += tpr) s += L.prod[e];
+        s = (s + s1) + (s2 + s3);
+        for (int o = tpr >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (l == 0) L.sum[i] = s;
+      }
+      __syncthreads();
+      finish(tid < R, w, rec.deg, tid < R ? L.sum[tid] : 0.0, rec.r, pold);
+    }
+    __syncthreads();
+    const int nsup = L.nsup, ntv = L.ntv, nfn = L.nfn;
+    if (nsup > 0) block_flush(&c->support_cnt, a.support, a.n, L.sup, &L.nsup, &L.base, &c->fault);
+    if (ntv > 0) block_flush(&c->touched_cnt, a.touched, a.n, L.tv, &L.ntv, &L.base, &c->fault);
+    if (nfn > 0)
+      block_flush(&c->cnt[(t + 1) & 1], Fn, a.n, L.fn, &L.nfn, &L.base, &c->fault);
+    k += gridDim.x;
+    if (k >= a.ndblk) break;
+    b = a.dblk[k];
+    __syncthreads();
+  }
+
+  // the next frontier's size and edges, and the round's close.  A word that
+  // all workgroups add to costs ~15 ns per addition, so groups of kDenseGroup
+  // workgroups count themselves first, the edges in the same word (R-MAT 2^16,
+  // 700 workgroups: 16 us per round with one word)
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    my_nf += __shfl_xor(my_nf, o);
+    my_e += __shfl_xor(my_e, o);
+  }
+  if (PLC_LANE == 0) {
+    L.wcnt[2 * PLC_WID] = my_nf;
+    L.wcnt[2 * PLC_WID + 1] = my_e;
+  }
+  __syncthreads();
+  if (tid >= 64) return;
+  bool last = false;
+  unsigned long long en = 0;
+  if (tid == 0) {
+    long long n1 = 0;
+    for (int w = 0; w < kBlock / 64; w++) {
+      n1 += L.wcnt[2 * w];
+      en += (unsigned long long)L.wcnt[2 * w + 1];
+    }
+    const int G = gridDim.x, g0 = blockIdx.x / kDenseGroup * kDenseGroup;
+    const int members = G - g0 < kDenseGroup ? G - g0 : kDenseGroup;
+    DenseGrp* grp = &a.dgrp[blockIdx.x / kDenseGroup];
+    if (n1 > 0) atomicAdd(&grp->nf[(t + 1) & 1], (int)n1);
+    unsigned long long prev = atomicAdd(&grp->word, en << 16 | 1ull);
+    if ((int)(prev & 0xffff) == members - 1) {
+      st_agent(&grp->word, 0ull);
+      en += prev >> 16;
+      prev = atomicAdd(&c->enext, en << 16 | 1ull);
+      last = (int)(prev & 0xffff) == (G + kDenseGroup - 1) / kDenseGroup - 1;
+      en += prev >> 16;
+    }
+  }
+  last = __shfl((int)last, 0) != 0;
+  if (!last) return;
+  const bool own_self = selfed != t;  // the self step came with the previous dense round
+  const int counted = dense_count(a, t);
+  if (tid != 0) return;
+  const long long E = c->etotal;
+  if (own_self) {
+    c->steps += 1;
+    c->dself += 1;
+  }
+  if (slot >= 0) {
+    if (own_self) a.work_log[2 * slot] = 1;
+    a.work_log[2 * slot + 1] = 1;
+  }
+  c->pushes += own_self ? counted : nf;
+  c->edges += E;
+  if (E >= a.bin_emin) {  // (the counters tell rounds of the binning threshold)
+    c->bin_rounds += 1;
+    c->pull_rounds += E >= a.dense_emin;
+    c->bin_edges += E;
+  }
+  c->cnt[t & 1] = 0;
+  if (fuse) c->cnt[(t + 1) & 1] = en > 0;
+  c->etotal = (long long)en;
+  c->enext = 0;
+  c->dsteps += 1;
+  const bool go = fuse && en > 0;
+  c->dense = !go ? DN_LIST : dense_pays(a, (long long)en) ? DN_READY : DN_CONVERT;
+  c->cd_dirty = (1 << (t & 1)) | (go ? 1 << ((t + 1) & 1) : 0);
+  c->round = t + 1;
+}
+
+// Back to the list form: the frontier is listed from the coefficients, and
+// the other array is cleared.
+__device__ void dense_convert(const PlainArgs& a, DenseLds& L) {
+  Ctl* c = a.ctl;
+  const int t = c->round;
+  const double* const cd = a.cd[t & 1];
+  double* const old = a.cd[(t + 1) & 1];
+  int32_t* const F = (t & 1) ? a.fbuf1 : a.fbuf0;
+  if (threadIdx.x == 0) L.nfn = 0;
+  __syncthreads();
+  for (int64_t i0 = (int64_t)blockIdx.x * kBlock; i0 < a.n; i0 += (int64_t)gridDim.x * kBlock) {
+    const int64_t i = i0 + threadIdx.x;
+    bool in = false;
+    if (i < a.n) {
+      in = cd[i] != 0.0;
+      old[i] = 0.0;
+    }
+    wave_append(in, (int32_t)i, L.fn, &L.nfn);
+    block_flush(&c->fill, F, a.n, L.fn, &L.nfn, &L.base, &c->fault);
+  }
+  if (last_block(&c->done[DONE_DENSE], &L.base, false) && threadIdx.x < 64) {
+    const int nf = dense_count(a, t);
+    if (threadIdx.x != 0) return;
+    if (atomicAdd(&c->fill, 0) != nf) c->fault = 1;
+    c->cnt[t & 1] = nf;
+    c->fill = 0;
+    c->dsteps += 1;
+    c->dense = DN_LIGHT;
+    c->cd_dirty = 1 << (t & 1);
+  }
+}
+
+template <int MODE>
+__device__ __forceinline__ void dense_body(const PlainArgs& a, int slot) {
+  __shared__ DenseLds L;
+  const Ctl* c = a.ctl;
+  const int k = blockIdx.x;  // (the grid has at most one workgroup per block)
+  // the block and all of the control block that a round needs, at once
+  DenseBlk b = a.dblk[k];
+  DenseCtl q{c->max_rounds, c->opt_rule, c->cd_dirty, c->hk_N, c->eps,
+             c->cs,         c->cn,       c->keep,     c->beta, c->hk_t, c->hk_A};
+  const CtlHead h = ctl_head(c);
+  asm volatile("" : "+s"(b.row), "+s"(b.nrows), "+s"(b.lid), "+s"(b.len), "+s"(b.first));
+  asm volatile("" : "+s"(q.max_rounds), "+s"(q.opt_rule), "+s"(q.cd_dirty), "+s"(q.hk_N),
+               "+s"(q.eps), "+s"(q.cs), "+s"(q.cn), "+s"(q.keep), "+s"(q.beta), "+s"(q.hk_t),
+               "+s"(q.hk_A));
+  const int nf = (h.round & 1) ? h.cnt1 : h.cnt0;
+  if (h.status != ST_PUSH || nf <= 0) return;
+  if (h.dense == DN_READY)
+    dense_round<MODE>(a, slot, L, k, b, h.round, nf, h.selfed, q);
+  else if (h.dense == DN_CONVERT)
+    dense_convert(a, L);
+}
+__global__ __launch_bounds__(kBlock) void k_dense(PlainArgs a, int slot) {
+  dense_body<kModePR>(a, slot);
+}
+__global__ __launch_bounds__(kBlock) void k_hk_dense(PlainArgs a) { dense_body<kModeHK>(a, -1); }
+
+// Entry into the dense form: the frontier's coefficients into cd[t & 1]
+// (all 0 before); the next launch runs the round.  HK-PR: the level's
+// residuals, which the self step has read, are cleared here (the dense form
+// keeps none).
+template <int MODE>
+__device__ void dense_enter(const PlainArgs& a, int t, int nf, int* s_last) {
+  Ctl* c = a.ctl;
+  const int32_t* F = (t & 1) ? a.fbuf1 : a.fbuf0;
+  double* const cd = a.cd[t & 1];
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < nf; i += gridDim.x * kBlock)
+    cd[F[i]] = a.coef[i];
+  if (MODE == kModeHK) {
+    const int np = c->hk_tlc[t % 3];
+    const int32_t* Lp = a.hk_tl[t % 3];
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < np; i += gridDim.x * kBlock)
+      *hk_res(a, t, Lp[i]) = 0.0;
+  }
+  if (last_block(&c->done[DONE_DENSE], s_last, false) && threadIdx.x == 0) {
+    if (MODE == kModeHK) {
+      c->hk_tlc[0] = 0;
+      c->hk_tlc[1] = 0;
+      c->hk_tlc[2] = 0;
+    } else if (dense_fuses<MODE>(c, t)) {
+      c->cnt[(t + 1) & 1] = 0;  // what the self step listed is counted again by its row
+    }
+    c->cd_dirty |= 1 << (t & 1);
+    if (c->dsteps == 0) c->pairs0 = c->steps;
+    c->dense = DN_READY;
+  }
+}
+
+__device__ __forceinline__ bool dense_wanted(const PlainArgs& a, const Ctl* c, int t) {
+  return dense_pays(a, c->etotal) && !((c->cd_dirty >> (t & 1)) & 1);
+}
+
 // The self launch of PR-Nibble.  A frontier of at most one scan block goes
 // to loop_rounds, run by the workgroup that arrives last: the loop rewrites
 // the control block, and by then every other workgroup has read the state
@@ -610,16 +1028,29 @@ __global__ __launch_bounds__(kBlock) void k_self(PlainArgs a, int slot) {
   const int32_t st = c->status;
   const int32_t t = c->round;
   int32_t nf = c->cnt[t & 1];
+  if (c->dense != DN_LIST) return;  // k_dense's
   if ((int64_t)nf > a.n) nf = (int32_t)a.n;
   if (st == ST_PUSH && nf > 0 && nf <= kScanBlock && t < c->max_rounds && c->beta >= 1.0) {
     __shared__ int s_last;
     if (last_block(&c->done[DONE_SELF], &s_last, false)) loop_rounds(a, slot, t, nf);
     return;
   }
-  self_body<kModePR>(a, slot);
+  self_body<kModePR, false>(a, slot);
 }
-__global__ __launch_bounds__(kBlock) void k_hk_self(PlainArgs a) { self_body<kModeHK>(a, -1); }
-__global__ __launch_bounds__(kBlock) void k_nb_self(PlainArgs a) { self_body<kModeNB>(a, -1); }
+__global__ __launch_bounds__(kBlock) void k_hk_self(PlainArgs a) {
+  if (a.ctl->dense != DN_LIST) return;
+  self_body<kModeHK, false>(a, -1);
+}
+__global__ __launch_bounds__(kBlock) void k_nb_self(PlainArgs a) {
+  self_body<kModeNB, false>(a, -1);
+}
+// The entries of a round that the dense form has handed back.
+__global__ __launch_bounds__(kBlock) void k_light_self(PlainArgs a, int slot) {
+  if (a.ctl->dense == DN_LIGHT) self_body<kModePR, true>(a, slot);
+}
+__global__ __launch_bounds__(kBlock) void k_hk_light_self(PlainArgs a) {
+  if (a.ctl->dense == DN_LIGHT) self_body<kModeHK, true>(a, -1);
+}
 
 // ------------------------------------------------- binned edge scatter
 //
@@ -665,12 +1096,8 @@ union ScatterShared {
   BinSortLds bs;
 };
 
-__device__ __forceinline__ bool pull_round(const PlainArgs& a, long long E) {
-  return a.pull != nullptr && a.nbins > 0 && E >= a.bin_emin && E >= a.pull_emin;
-}
 __device__ __forceinline__ bool bin_round(const PlainArgs& a, long long E) {
-  return a.nbins > 0 && E >= a.bin_emin && E <= (long long)a.bin_cmax * kBinChunk &&
-         !pull_round(a, E);
+  return a.nbins > 0 && E >= a.bin_emin && E <= (long long)a.bin_cmax * kBinChunk;
 }
 
 // Exclusive scan over the workgroup of one int per thread; sh holds
@@ -797,35 +1224,25 @@ __device__ void bin_sort_chunks(const PlainArgs& a, int nf, BinSortLds& L) {
   }
 }
 
-// Pass B of a binned round, or the pull form of a round that covers at
-// least half the graph's arcs, then the round's close.  Exits at once when
-// the round was neither (k_scatter then closed it).
-//   Pass B: each item gathers its bin's runs of (neighbour, entry) pairs
-//   from pass A and adds the entries' coefficients into an LDS array over
-//   the bin's vertices.
-//   Pull: each item walks a slice of its bin's own vertices' arcs (CSR rows
-//   in order) and adds the coefficient of every neighbour whose pull record
-//   carries this round's epoch (the frontier), with no pairs and no pass A.
-// Then every touched destination gets one update (plain when the item owns
-// the whole bin, atomic otherwise), on which its threshold crossing and
-// first touch are decided.
+// Pass B of a binned round, then the round's close (exits at once when the
+// round was not binned; k_scatter then closed it).  Each item gathers its
+// bin's runs of (neighbour, entry) pairs from pass A and adds the entries'
+// coefficients into an LDS array over the bin's vertices.  Then every touched
+// destination gets one update (plain when the item owns the whole bin, atomic
+// otherwise), on which its threshold crossing and first touch are decided.
 __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
   Ctl* c = a.ctl;
   int t, nf;
   if (!push_active(c, a.n, &t, &nf)) return;
-  if (t >= c->max_rounds || c->selfed != t) return;
+  if (t >= c->max_rounds || c->selfed != t || c->dense != DN_LIST) return;
   const long long E = c->etotal;
-  const bool pull = pull_round(a, E);
-  if (!pull && !bin_round(a, E)) return;
+  if (!bin_round(a, E)) return;
   __shared__ double acc[kBinWidth];          // the item's sums, zero between items
   __shared__ int32_t s_list[kBinWidth];      // first touches of the item (offsets in the bin)
   __shared__ int s_items[kMaxBins + 1];      // first item of each bin
-  // pass B: start of the item's run in each chunk, and the exclusive prefix
-  // of the run lengths; pull: the bin's row offsets from its first arc
-  __shared__ int s_runs[2 * kBinItemChunks + 1];
-  static_assert(2 * kBinItemChunks + 1 >= kBinWidth + 1, "a bin's row offsets fit");
-  int* const s_rs = s_runs;
-  int* const s_rp = s_runs + kBinItemChunks;
+  // start of the item's run in each chunk, and the exclusive prefix of the
+  // run lengths
+  __shared__ int s_rs[kBinItemChunks], s_rp[kBinItemChunks];
   __shared__ int sh[kBlock / 64 + 1];
   __shared__ int s_nl, s_fb, s_tb, s_last;
   constexpr int kBinsPT = kMaxBins / kBlock;
@@ -836,14 +1253,12 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
   const int nb = a.nbins;
   const int C = (int)((E + kBinChunk - 1) / kBinChunk);
   const double eps = c->eps;
-  const unsigned pull_ep = pull ? *a.pull_epoch : 0u;
   int32_t* Fn = (t & 1) ? a.fbuf0 : a.fbuf1;
   int32_t* cntn = &c->cnt[(t + 1) & 1];
   for (int j = threadIdx.x; j < kBinWidth; j += kBlock) acc[j] = 0.0;
   // items per bin: the bin's expected share of the round's edges (E vol_b /
   // 2m) over kBinQ, at least enough that an item spans <= kBinItemChunks
-  // chunks, at most one per chunk (pull: the bin's arcs vol_b over kBinQ);
-  // every workgroup computes the same table
+  // chunks, at most one per chunk; every workgroup computes the same table
   {
     const int smin = (C + kBinItemChunks - 1) / kBinItemChunks;
     int loc[kBinsPT];
@@ -853,13 +1268,10 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
       const int b = (int)threadIdx.x * kBinsPT + k;
       int it = 0;
       if (b < nb) {
-        const double expect =
-            pull ? (double)a.bin_vol[b] : (double)E * (double)a.bin_vol[b] / (double)a.vol_total;
+        const double expect = (double)E * (double)a.bin_vol[b] / (double)a.vol_total;
         it = (int)ceil(expect / (double)kBinQ);
-        if (!pull) {
-          it = it > smin ? it : smin;
-          it = it < C ? it : C;
-        }
+        it = it > smin ? it : smin;
+        it = it < C ? it : C;
         it = it > 1 ? it : 1;
       }
       loc[k] = it;
@@ -892,110 +1304,65 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
     const int vlo = a.bin_lo[b];
     const int W = a.bin_lo[b + 1] - vlo;
     const bool own = S == 1;
-    if (pull) {
-      // the slice of the bin's arcs: rows vlo .. vlo + Wn (the last bin may
-      // end past n), arcs A0 .. A1 of the CSR
-      const int Wn = (int)((int64_t)vlo + W < a.n ? W : a.n - vlo);
-      const long long A0 = a.off[vlo], A1 = a.off[vlo + Wn];
-      const long long j0 = A0 + (A1 - A0) * sl / S, j1 = A0 + (A1 - A0) * (sl + 1) / S;
-      for (int r = threadIdx.x; r <= Wn; r += kBlock) s_runs[r] = (int)(a.off[vlo + r] - A0);
-      __syncthreads();
-      constexpr int kU = 4;
-      for (long long e0 = j0; e0 < j1; e0 += kBlock * kU) {
-        int32_t u[kU];
+    const int c0 = (int)((long long)sl * C / S), c1 = (int)((long long)(sl + 1) * C / S);
+    const int nc = c1 - c0;
+    // the item's runs
+    int rl[kRunsPT];
+    int lsum = 0;
 #pragma unroll
-        for (int q = 0; q < kU; q++) {
-          const long long e = e0 + q * kBlock + (int)threadIdx.x;
-          u[q] = e < j1 ? a.nbr[e] : -1;
-        }
-        double cf[kU];
+    for (int k = 0; k < kRunsPT; k++) {
+      const int q = (int)threadIdx.x * kRunsPT + k;
+      rl[k] = 0;
+      if (q < nc) {
+        const int st = a.bin_T[(size_t)b * a.bin_cmax + c0 + q];
+        const int en = a.bin_T[(size_t)(b + 1) * a.bin_cmax + c0 + q];
+        s_rs[q] = (c0 + q) * kBinChunk + st;
+        rl[k] = en - st;
+        if (rl[k] < 0 || en > kBinChunk) { c->fault = 1; rl[k] = 0; }
+      }
+      lsum += rl[k];
+    }
+    int L;
+    int ex = block_excl_scan_int(lsum, &L, sh);
 #pragma unroll
-        for (int q = 0; q < kU; q++) {
-          cf[q] = 0.0;
-          if (u[q] >= 0) {
-            const PullRec pr = a.pull[u[q]];
-            if (pr.stamp == pull_ep) cf[q] = pr.coef;
+    for (int k = 0; k < kRunsPT; k++) {
+      const int q = (int)threadIdx.x * kRunsPT + k;
+      if (q < nc) s_rp[q] = ex;
+      ex += rl[k];
+    }
+    __syncthreads();
+    // add every contribution into the LDS array; the first toucher of an
+    // offset lists it
+    constexpr int kU = 4;
+    for (int j0 = 0; j0 < L; j0 += kBlock * kU) {
+      int2 pr[kU];
+#pragma unroll
+      for (int u = 0; u < kU; u++) {
+        const int j = j0 + u * kBlock + (int)threadIdx.x;
+        pr[u] = make_int2(-1, 0);
+        if (j < L) {
+          int l2 = 0, h2 = nc - 1;
+          while (l2 < h2) {
+            const int mid = (l2 + h2 + 1) >> 1;
+            if (s_rp[mid] <= j) l2 = mid; else h2 = mid - 1;
           }
-        }
-#pragma unroll
-        for (int q = 0; q < kU; q++) {
-          bool first = false;
-          int jl = 0;
-          if (cf[q] != 0.0) {
-            // the row holding arc e: the last row whose first arc is <= e
-            const int rel = (int)(e0 + q * kBlock + (int)threadIdx.x - A0);
-            int l2 = 0, h2 = Wn - 1;
-            while (l2 < h2) {
-              const int mid = (l2 + h2 + 1) >> 1;
-              if (s_runs[mid] <= rel) l2 = mid; else h2 = mid - 1;
-            }
-            jl = l2;
-            first = atomicAdd(&acc[jl], cf[q]) == 0.0;
-          }
-          wave_append(first, jl, s_list, &s_nl);
+          pr[u] = a.bin_pairs[s_rs[l2] + (j - s_rp[l2])];
         }
       }
-    } else {
-      const int c0 = (int)((long long)sl * C / S), c1 = (int)((long long)(sl + 1) * C / S);
-      const int nc = c1 - c0;
-      // the item's runs
-      int rl[kRunsPT];
-      int lsum = 0;
+      double cf[kU];
 #pragma unroll
-      for (int k = 0; k < kRunsPT; k++) {
-        const int q = (int)threadIdx.x * kRunsPT + k;
-        rl[k] = 0;
-        if (q < nc) {
-          const int st = a.bin_T[(size_t)b * a.bin_cmax + c0 + q];
-          const int en = a.bin_T[(size_t)(b + 1) * a.bin_cmax + c0 + q];
-          s_rs[q] = (c0 + q) * kBinChunk + st;
-          rl[k] = en - st;
-          if (rl[k] < 0 || en > kBinChunk) { c->fault = 1; rl[k] = 0; }
+      for (int u = 0; u < kU; u++) cf[u] = pr[u].x >= 0 && pr[u].y < nf ? a.coef[pr[u].y] : 0.0;
+#pragma unroll
+      for (int u = 0; u < kU; u++) {
+        const int jl = pr[u].x - vlo;
+        bool first = false;
+        if (pr[u].x >= 0) {
+          // (contributions are positive, so exactly one addition per touched
+          // offset returns 0; an impossible zero one is not listed)
+          if (jl >= 0 && jl < W) first = atomicAdd(&acc[jl], cf[u]) == 0.0 && cf[u] != 0.0;
+          else c->fault = 1;
         }
-        lsum += rl[k];
-      }
-      int L;
-      int ex = block_excl_scan_int(lsum, &L, sh);
-#pragma unroll
-      for (int k = 0; k < kRunsPT; k++) {
-        const int q = (int)threadIdx.x * kRunsPT + k;
-        if (q < nc) s_rp[q] = ex;
-        ex += rl[k];
-      }
-      __syncthreads();
-      // add every contribution into the LDS array; the first toucher of an
-      // offset lists it
-      constexpr int kU = 4;
-      for (int j0 = 0; j0 < L; j0 += kBlock * kU) {
-        int2 pr[kU];
-#pragma unroll
-        for (int u = 0; u < kU; u++) {
-          const int j = j0 + u * kBlock + (int)threadIdx.x;
-          pr[u] = make_int2(-1, 0);
-          if (j < L) {
-            int l2 = 0, h2 = nc - 1;
-            while (l2 < h2) {
-              const int mid = (l2 + h2 + 1) >> 1;
-              if (s_rp[mid] <= j) l2 = mid; else h2 = mid - 1;
-            }
-            pr[u] = a.bin_pairs[s_rs[l2] + (j - s_rp[l2])];
-          }
-        }
-        double cf[kU];
-#pragma unroll
-        for (int u = 0; u < kU; u++) cf[u] = pr[u].x >= 0 && pr[u].y < nf ? a.coef[pr[u].y] : 0.0;
-#pragma unroll
-        for (int u = 0; u < kU; u++) {
-          const int jl = pr[u].x - vlo;
-          bool first = false;
-          if (pr[u].x >= 0) {
-            // (contributions are positive, so exactly one addition per touched
-            // offset returns 0; an impossible zero one is not listed)
-            if (jl >= 0 && jl < W) first = atomicAdd(&acc[jl], cf[u]) == 0.0 && cf[u] != 0.0;
-            else c->fault = 1;
-          }
-          wave_append(first, jl, s_list, &s_nl);
-        }
+        wave_append(first, jl, s_list, &s_nl);
       }
     }
     __syncthreads();
@@ -1065,11 +1432,9 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
       c->pushes += nf;
       c->edges += E;
       c->bin_rounds += 1;
-      if (pull) c->pull_rounds += 1;
       c->bin_edges += E;
       c->cnt[t & 1] = 0;
       c->round = t + 1;
-      if (a.pull_epoch) *a.pull_epoch += 1u;
       if (slot >= 0) a.work_log[2 * slot + 1] = 1;
     }
   }
@@ -1099,25 +1464,20 @@ __device__ __forceinline__ void scatter_body(const PlainArgs& a, int slot, Scatt
   if (!push_active(c, a.n, &t, &nf)) return;
   if (HK ? t >= c->hk_N : t >= c->max_rounds) return;
   if (c->selfed != t) return;  // no entries built for this round (a self loop stopped before it)
-  // which launch pairs of a first chunk carry rounds that could bin or pull
-  // (the host queues k_bin_apply behind those pairs only); without
-  // k_bin_apply behind it the round takes the atomic form
-  if (MODE == kModePR && pair >= 0 && blockIdx.x == 0 && threadIdx.x == 0 &&
-      (pull_round(a, c->etotal) || bin_round(a, c->etotal)))
-    c->bin_pairs |= 1u << pair;
-  if (MODE == kModePR && !apply) {
-    // (falls through to the atomic form)
-  } else if (MODE == kModePR && pull_round(a, c->etotal)) {
-    // a pull round: the frontier's coefficients, stamped with the round's
-    // epoch, for k_bin_apply to pull (which also closes the round)
-    const unsigned ep = *a.pull_epoch;
-    const int32_t* F = (t & 1) ? a.fbuf1 : a.fbuf0;
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < nf; i += gridDim.x * kBlock)
-      a.pull[F[i]] = PullRec{a.coef[i], ep, 0};
+  if (MODE != kModeNB && c->dense != DN_LIST) return;  // k_dense's
+  if (MODE != kModeNB && dense_wanted(a, c, t)) {
+    dense_enter<MODE>(a, t, nf, &sm.at.last);
     return;
-  } else if (MODE == kModePR && bin_round(a, c->etotal)) {
-    bin_sort_chunks(a, nf, sm.bs);  // pass A; k_bin_apply adds and closes the round
-    return;
+  }
+  // which launch pairs of a first chunk carry rounds that could bin (the
+  // host queues k_bin_apply behind those pairs only); without k_bin_apply
+  // behind it such a round takes the atomic form
+  if (MODE == kModePR && bin_round(a, c->etotal)) {
+    if (pair >= 0 && blockIdx.x == 0 && threadIdx.x == 0) c->bin_pairs |= 1u << pair;
+    if (apply) {
+      bin_sort_chunks(a, nf, sm.bs);  // pass A; k_bin_apply adds and closes the round
+      return;
+    }
   }
   int32_t* const s_start = sm.at.start;
   int64_t* const s_row = sm.at.row;
@@ -1226,7 +1586,6 @@ __device__ __forceinline__ void scatter_body(const PlainArgs& a, int slot, Scatt
       c->edges += E;
       c->cnt[t & 1] = 0;
       c->round = t + 1;
-      if (a.pull_epoch) *a.pull_epoch += 1u;
       if (slot >= 0) a.work_log[2 * slot + 1] = 1;
     }
   }
@@ -1366,12 +1725,14 @@ __global__ __launch_bounds__(kBlock) void k_nb_finish(PlainArgs a, int32_t R, in
   }
 }
 
-// After the last HK-PR level: residuals can remain only on the vertices the
-// last two levels touched (every earlier level was cleared by the self
-// kernel two levels later); clear both arrays there.
+// After the last HK-PR level (nothing before it): residuals can remain only
+// on the vertices the last two levels touched (every earlier level was
+// cleared by the self kernel two levels later, and the dense form keeps
+// none); clear both arrays there.
 __global__ __launch_bounds__(kBlock) void k_hk_clear(PlainArgs a) {
   Ctl* c = a.ctl;
   const int J = c->round;
+  if (c->cnt[J & 1] > 0 && J < c->hk_N) return;
   for (int q = 0; q < 2; q++) {
     const int lv = J - q;
     if (lv < 0) continue;
@@ -1497,10 +1858,17 @@ __global__ __launch_bounds__(kBlock) void k_sweep_keys(PlainArgs a, long long bo
     e.seg = 0;
     a.sbuf[0][i] = e;
   }
+  // a push that ended in the dense form leaves its last coefficients
+  const int dirty = c->cd_dirty;
+  for (int k = 0; k < 2; k++)
+    if ((dirty >> k) & 1)
+      for (int64_t i = blockIdx.x * kBlock + threadIdx.x; i < a.n; i += gridDim.x * kBlock)
+        a.cd[k][i] = 0.0;
   if (last_block(&c->done[DONE_KEYS], &s_last, false)) {
     if (threadIdx.x == 0) {
       c->N = N;
       c->sort_flip = 0;
+      c->cd_dirty = 0;
       c->status = ST_SWEEPING;
     }
   }
@@ -1852,6 +2220,44 @@ hipError_t launch_hk_clear(hipStream_t s, const PlainArgs& a, int grid) {
   return hipGetLastError();
 }
 
+// At most one workgroup per block of rows, at most 2048 (the whole chip).
+static int dense_grid(const PlainArgs& a) {
+  constexpr int most = kDenseGroup * kDenseGroups;
+  return a.ndblk < most ? a.ndblk : most;
+}
+
+hipError_t launch_dense(hipStream_t s, const PlainArgs& a, hipEvent_t t0, hipEvent_t t1,
+                        int slot) {
+  if (slot >= kMaxChunk || a.ndblk < 1) return hipErrorInvalidValue;
+  if (t0)
+    hipExtLaunchKernelGGL(k_dense, dim3(dense_grid(a)), dim3(kBlock), 0, s, t0, t1, 0, a, slot);
+  else
+    hipLaunchKernelGGL(k_dense, dim3(dense_grid(a)), dim3(kBlock), 0, s, a, slot);
+  return hipGetLastError();
+}
+
+hipError_t launch_light_self(hipStream_t s, const PlainArgs& a, int grid, hipEvent_t t0,
+                             hipEvent_t t1, int slot) {
+  if (slot >= kMaxChunk) return hipErrorInvalidValue;
+  if (t0)
+    hipExtLaunchKernelGGL(k_light_self, dim3(grid), dim3(kBlock), 0, s, t0, t1, 0, a, slot);
+  else
+    hipLaunchKernelGGL(k_light_self, dim3(grid), dim3(kBlock), 0, s, a, slot);
+  return hipGetLastError();
+}
+
+hipError_t launch_hk_light(hipStream_t s, const PlainArgs& a, int grid_self, int grid_scatter) {
+  hipLaunchKernelGGL(k_hk_light_self, dim3(grid_self), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_hk_scatter, dim3(grid_scatter), dim3(kBlock), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_hk_dense(hipStream_t s, const PlainArgs& a) {
+  if (a.ndblk < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_hk_dense, dim3(dense_grid(a)), dim3(kBlock), 0, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_self(hipStream_t s, const PlainArgs& a, int grid, hipEvent_t t0, hipEvent_t t1,
                        int slot) {
   if (slot >= kMaxChunk) return hipErrorInvalidValue;
@@ -1865,7 +2271,7 @@ hipError_t launch_self(hipStream_t s, const PlainArgs& a, int grid, hipEvent_t t
 hipError_t launch_scatter(hipStream_t s, const PlainArgs& a, int grid, hipEvent_t t0,
                           hipEvent_t t1, int slot, int grid_bin, int pair, bool apply_wanted) {
   if (slot >= kMaxChunk || pair >= 32) return hipErrorInvalidValue;
-  // k_bin_apply only where a round can be binned or pulled (an empty
+  // k_bin_apply only where a round can be binned (an empty
   // launch still costs a dispatch every round)
   const bool apply = apply_wanted && bins_possible(a);
   const int ap = apply ? 1 : 0;

@@ -63,6 +63,7 @@ struct Captured {
   int gs = -1, gc = -1, gw = -1, rounds = -1;
   long long emin = 0;  // plain rounds: the binning threshold the graph's arguments carry
   uint32_t mask = ~0u;  // plain first chunks: pairs followed by k_bin_apply (bit i: pair i)
+  int dense = 0;        // plain rounds: dense launches behind the pairs
   bool matches(int s, int c, int w, int r, long long e = 0, uint32_t m = ~0u) const {
     return exec && gs == s && gc == c && gw == w && rounds == r && emin == e && mask == m;
   }
@@ -150,11 +151,14 @@ struct plc_graph {
   int plain_self = 0, plain_scatter = 0, plain_sweep = 0;
   int batch_self = 0, batch_scatter = 0, batch_sweep = 0;
   BatchEngine* batch = nullptr;
-  std::map<int, Captured> chunk_g;  // plain path: R rounds of (self, scatter), by R
-  // plain path: a query's first chunk of R rounds, by (R << 32 | mask); its
-  // pairs queue k_bin_apply as the mask says and report rounds that could
-  // bin (a mask that comes back finds its graph still recorded)
+  // plain path: chunks of (self, scatter) pairs and dense launches behind
+  // them, by (pairs << 16 | dense launches)
+  std::map<uint32_t, Captured> chunk_g;
+  // plain path: a query's first chunk, by that key << 32 | mask; its pairs
+  // queue k_bin_apply as the mask says and report rounds that could bin (a
+  // mask that comes back finds its graph still recorded)
   std::map<uint64_t, Captured> first_g;
+  int hk_pairs = 0, hk_dense = -1;  // HK-PR: pairs and dense launches the last query used
   std::map<int64_t, Captured> sweep_g;  // plain path: the sweep, by sort bound (power of 2)
 };
 
@@ -179,10 +183,12 @@ struct plc_ctx {
   double clock_ns = 10.0;         // nanoseconds per tick of the kernels' constant-rate clock
   uint32_t cur_flags = 0;         // plain path: flags of the running query
   int32_t cur_pipe = 0;           // plain path: plc_result_info.pipelined of the running query
-  std::deque<int> round_hist;  // plain path: working self launches of the last queries
+  // plain path: per query of the last ones, the self launches that found work
+  // before its first dense round, and its dense launches that did work
+  std::deque<int> round_hist, dense_hist;
   std::deque<int> support_hist;  // plain path: support sizes of the last queries
   // plain path: Ctl::bin_pairs of the last queries whose first chunk reported
-  // them (the pairs of a first chunk whose rounds could bin or pull)
+  // them (the pairs of a first chunk whose rounds could bin)
   std::deque<uint32_t> pair_hist;
   std::chrono::steady_clock::time_point q_t0;  // plain path: start of the running query
   std::chrono::steady_clock::time_point next_t0;  // plain path: start of the queued next query
@@ -328,6 +334,44 @@ static void graph_release_blocks(plc_ctx* ctx, plc_graph* g) {
   g->blocks.clear();
 }
 
+// Blocks of the dense round: consecutive rows while they have at most
+// kDenseArcs arcs and kDenseRows rows, and rows times the longest row stays
+// within kDenseSpan (no lane sums more than kDenseSpan / 256 products of a
+// row); a longer row is cut into pieces of kDenseArcs arcs.
+static void dense_blocks(const std::vector<int64_t>& off, std::vector<plc::DenseBlk>* out,
+                         int32_t* nlong) {
+  const int64_t n = (int64_t)off.size() - 1;
+  *nlong = 0;
+  for (int64_t v = 0; v < n;) {
+    int64_t d = off[v + 1] - off[v];
+    if (d > plc::kDenseArcs) {
+      const int32_t pieces = (int32_t)((d + plc::kDenseArcs - 1) / plc::kDenseArcs);
+      for (int32_t k = 0; k < pieces; k++) {
+        const int64_t e = (int64_t)k * plc::kDenseArcs;
+        out->push_back(plc::DenseBlk{(int32_t)v, pieces, *nlong,
+                                     (int32_t)std::min<int64_t>(plc::kDenseArcs, d - e),
+                                     (long long)(off[v] + e)});
+      }
+      (*nlong)++;
+      v++;
+      continue;
+    }
+    int64_t w = v, arcs = 0, top = 0;
+    while (w < n && w - v < plc::kDenseRows) {
+      d = off[w + 1] - off[w];
+      const int64_t m = std::max(top, d);
+      if (arcs + d > plc::kDenseArcs || (w > v && (w - v + 1) * m > plc::kDenseSpan)) break;
+      arcs += d;
+      top = m;
+      w++;
+    }
+    if (arcs > 0)  // (isolated vertices take part in no round)
+      out->push_back(plc::DenseBlk{(int32_t)v, (int32_t)(w - v), -1, (int32_t)arcs,
+                                   (long long)off[v]});
+    v = w;
+  }
+}
+
 extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
                                      const void* offsets, int32_t offsets_bits,
                                      const int32_t* nbrs, uint32_t flags, plc_graph** out) {
@@ -470,18 +514,36 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
     a.bin_pairs = static_cast<int2*>(take(8 * (size_t)a.bin_cmax * plc::kBinChunk));
     a.nbins = nb;
     a.bin_emin = ctx->opt.bin_min_edges > 0 ? ctx->opt.bin_min_edges : plc::kBinEmin;
-    // the pull form for rounds over at least half the arcs (records cleared
-    // by the graph init kernel)
-    a.pull = static_cast<plc::PullRec*>(take(sizeof(plc::PullRec) * (size_t)n));
-    a.pull_epoch = static_cast<unsigned*>(take(256));
-    a.pull_emin = std::max<long long>(1, (num_arcs + 1) / 2);
   } else {
     a.nbins = 0;
     a.bin_cmax = 0;
     a.bin_emin = 0;
-    a.pull = nullptr;
-    a.pull_epoch = nullptr;
-    a.pull_emin = 0;
+  }
+  // Dense rounds (same graphs and option): the two coefficient arrays
+  // (cleared by the graph init kernel) and the blocks of rows.  Without room
+  // for the blocks the graph does without the form.
+  std::vector<plc::DenseBlk> dblk;
+  int32_t nlong = 0;
+  if (bins_on) {
+    dense_blocks(off, &dblk, &nlong);
+    double* cd = static_cast<double*>(take(16 * N));
+    void* blk = nullptr;
+    const size_t acc_at = (sizeof(plc::DenseBlk) * dblk.size() + 255) & ~(size_t)255;
+    const size_t grp_at = (acc_at + 12 * (size_t)(nlong + 1) + 255) & ~(size_t)255;
+    if (!nomem && !dblk.empty())
+      blk = ctx->arena.alloc(grp_at + sizeof(plc::DenseGrp) * plc::kDenseGroups);
+    if (blk) {
+      g->blocks.push_back(blk);
+      a.cd[0] = cd;
+      a.cd[1] = cd + N;
+      a.dense_free = ctx->opt.bin_min_edges == 0;
+      a.dense_emin = std::max<long long>(1, (num_arcs + 1) / 2);
+      a.ndblk = (int32_t)dblk.size();
+      a.dblk = static_cast<plc::DenseBlk*>(blk);
+      a.dacc = reinterpret_cast<double*>(static_cast<char*>(blk) + acc_at);
+      a.dcnt = reinterpret_cast<unsigned*>(a.dacc + nlong + 1);
+      a.dgrp = reinterpret_cast<plc::DenseGrp*>(static_cast<char*>(blk) + grp_at);
+    }
   }
   if (nomem) {
     graph_release_blocks(ctx, g);
@@ -532,6 +594,12 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
                       s) != hipSuccess ||
        hipMemcpyAsync((void*)a.bin_vol, bin_vol.data(), 8 * bin_vol.size(),
                       hipMemcpyHostToDevice, s) != hipSuccess))
+    return fail();
+  if (a.cd[0] &&
+      (hipMemcpyAsync((void*)a.dblk, dblk.data(), sizeof(plc::DenseBlk) * dblk.size(),
+                      hipMemcpyHostToDevice, s) != hipSuccess ||
+       hipMemsetAsync(a.dacc, 0, 12 * (size_t)(nlong + 1), s) != hipSuccess ||
+       hipMemsetAsync(a.dgrp, 0, sizeof(plc::DenseGrp) * plc::kDenseGroups, s) != hipSuccess))
     return fail();
   if (hipMemsetAsync(a.ctl, 0, sizeof(Ctl), s) != hipSuccess) return fail();
   for (int k = 0; k < plc::NUM_SCANS; k++)
@@ -610,7 +678,7 @@ static bool capture(plc_ctx* ctx, Captured& c, F&& body) {
 }
 
 // The launch pairs of a first chunk that queue k_bin_apply: those whose
-// rounds could bin or pull in any of the last queries (all of them until a
+// rounds could bin in any of the last queries (all of them until a
 // query has reported, or when the context fixed the binning threshold;
 // pairs from 32 on always queue it).  Binned rounds sit
 // at the same few pairs from query to query (those of the largest frontiers),
@@ -628,39 +696,52 @@ static uint32_t first_chunk_mask(const plc_ctx* ctx) {
   return m;
 }
 
-// Graph of R plain rounds (self, scatter).  first: a query's first chunk,
-// whose pair i reports in Ctl::bin_pairs a round that could bin or pull and
-// queues k_bin_apply only where bit i of first_chunk_mask is set (always
-// from pair 32 on).
-static Captured* plain_chunk_graph(plc_ctx* ctx, plc_graph* g, int R, bool first = false) {
+// The launches of a chunk: `pairs` (self, scatter) pairs, then `dense` dense
+// launches (each a round of a query that has gone dense by then; they exit
+// at once otherwise).  light: the first pair takes up a round handed back by
+// the dense form.
+struct Chunk {
+  int pairs = 0, dense = 0;
+  bool light = false;
+  uint32_t key() const { return (uint32_t)light << 31 | (uint32_t)pairs << 16 | (uint32_t)dense; }
+};
+
+// Graph of a chunk of plain rounds.  first: a query's first chunk, whose pair
+// i reports in Ctl::bin_pairs a round that could bin and queues k_bin_apply
+// only where bit i of first_chunk_mask is set (always from pair 32 on).
+static Captured* plain_chunk_graph(plc_ctx* ctx, plc_graph* g, Chunk ch, bool first = false) {
   const int gs = shape(g->plain_self, ctx->grid_self);
   const int gc = shape(g->plain_scatter, ctx->grid_scatter);
   const uint32_t mask = first ? first_chunk_mask(ctx) : ~0u;
-  const uint64_t key = ((uint64_t)R << 32) | mask;
+  const uint64_t key = ((uint64_t)ch.key() << 32) | mask;
   if (first && g->first_g.size() >= kFirstGraphs && !g->first_g.count(key)) {
     for (auto& kv : g->first_g) captured_free(kv.second);  // bound the recorded masks
     g->first_g.clear();
   }
-  Captured& c = first ? g->first_g[key] : g->chunk_g[R];
-  if (c.matches(gs, gc, 0, R, g->args.bin_emin, mask)) return &c;
+  Captured& c = first ? g->first_g[key] : g->chunk_g[ch.key()];
+  if (c.matches(gs, gc, 0, ch.pairs, g->args.bin_emin, mask) && c.dense == ch.dense) return &c;
   captured_free(c);
   c.gs = gs;
   c.gc = gc;
   c.gw = 0;
-  c.rounds = R;
+  c.rounds = ch.pairs;
+  c.dense = ch.dense;
   c.emin = g->args.bin_emin;
   c.mask = mask;
   const PlainArgs& a = g->args;
   const bool ok = capture(ctx, c, [&](hipStream_t cs) -> hipError_t {
     hipError_t r;
-    for (int i = 0; i < R; i++) {
+    for (int i = 0; i < ch.pairs; i++) {
       const bool tracked = first && i < 32;
       const bool apply = !tracked || ((mask >> i) & 1u);
-      if ((r = plc::launch_self(cs, a, gs)) != hipSuccess) return r;
+      r = ch.light && i == 0 ? plc::launch_light_self(cs, a, gs) : plc::launch_self(cs, a, gs);
+      if (r != hipSuccess) return r;
       if ((r = plc::launch_scatter(cs, a, gc, nullptr, nullptr, -1, ctx->grid_bin,
                                    tracked ? i : -1, apply)) != hipSuccess)
         return r;
     }
+    for (int i = 0; i < ch.dense; i++)
+      if ((r = plc::launch_dense(cs, a)) != hipSuccess) return r;
     return hipSuccess;
   });
   return ok ? &c : nullptr;
@@ -685,14 +766,15 @@ static Captured* plain_sweep_graph(plc_ctx* ctx, plc_graph* g, int64_t max_count
   return ok ? &c : nullptr;
 }
 
-// Queue `rounds` rounds as direct launches; with timing on, each kernel
-// carries start and stop events on its own dispatch timestamps
-// (ctx->ev_self[i], ctx->ev_scatter[i] for round i of the chunk) and marks
-// a.work_log[2i] / [2i + 1] when it did work.  first: a query's first chunk,
-// with the same k_bin_apply launches and reports as its graph (so the timed
-// launches are the ones the graphs replay).
-
-static hipError_t queue_rounds(plc_ctx* ctx, const plc_graph* g, int rounds, bool beta,
+// Queue a chunk as direct launches; with timing on, each kernel carries start
+// and stop events on its own dispatch timestamps (ctx->ev_self[i],
+// ctx->ev_scatter[i] for pair i of the chunk, the dense launches counted on
+// from the pairs) and marks a.work_log[2i] / [2i + 1] when it did work.
+// first: a query's first chunk, with the same k_bin_apply launches and
+// reports as its graph (so the timed launches are the ones the graphs
+// replay).  beta: the ranking before and the carry after each round, which
+// may be a dense one (one launch).
+static hipError_t queue_rounds(plc_ctx* ctx, const plc_graph* g, Chunk ch, bool beta,
                                bool first = false) {
   const PlainArgs& a = g->args;
   hipStream_t s = ctx->stream;
@@ -700,30 +782,51 @@ static hipError_t queue_rounds(plc_ctx* ctx, const plc_graph* g, int rounds, boo
   const int gc = shape(g->plain_scatter, ctx->grid_scatter);
   const int gw = shape(g->plain_sweep, ctx->grid_sweep);
   const uint32_t mask = first && !beta ? first_chunk_mask(ctx) : ~0u;
-  for (int i = 0; i < rounds; i++) {
-    hipError_t r;
+  hipError_t r;
+  if (ctx->timing) {
+    const size_t slots = (size_t)(ch.pairs + ch.dense);
+    while (ctx->ev_self.size() < slots) ctx->ev_self.emplace_back();
+    while (ctx->ev_scatter.size() < slots) ctx->ev_scatter.emplace_back();
+    for (size_t k = 0; k < slots; k++) {
+      if ((r = ev_pair(ctx->ev_self[k])) != hipSuccess) return r;
+      if ((r = ev_pair(ctx->ev_scatter[k])) != hipSuccess) return r;
+    }
+  }
+  for (int i = 0; i < ch.pairs; i++) {
     const bool tracked = first && !beta && i < 32;
     const int pair = tracked ? i : -1;
     const bool apply = !tracked || ((mask >> i) & 1u);
     if (beta && (r = plc::launch_beta_pre(s, a, gw, g->n)) != hipSuccess) return r;
+    const bool light = ch.light && i == 0;
     if (ctx->timing) {
-      size_t k = (size_t)i;
-      while (ctx->ev_self.size() <= k) ctx->ev_self.emplace_back();
-      while (ctx->ev_scatter.size() <= k) ctx->ev_scatter.emplace_back();
-      if ((r = ev_pair(ctx->ev_self[k])) != hipSuccess) return r;
-      if ((r = ev_pair(ctx->ev_scatter[k])) != hipSuccess) return r;
-      if ((r = plc::launch_self(s, a, gs, ctx->ev_self[k].a, ctx->ev_self[k].b, i)) != hipSuccess)
-        return r;
+      const size_t k = (size_t)i;
+      r = light ? plc::launch_light_self(s, a, gs, ctx->ev_self[k].a, ctx->ev_self[k].b, i)
+                : plc::launch_self(s, a, gs, ctx->ev_self[k].a, ctx->ev_self[k].b, i);
+      if (r != hipSuccess) return r;
       if ((r = plc::launch_scatter(s, a, gc, ctx->ev_scatter[k].a, ctx->ev_scatter[k].b, i,
                                    ctx->grid_bin, pair, apply)) != hipSuccess)
         return r;
     } else {
-      if ((r = plc::launch_self(s, a, gs)) != hipSuccess) return r;
+      r = light ? plc::launch_light_self(s, a, gs) : plc::launch_self(s, a, gs);
+      if (r != hipSuccess) return r;
       if ((r = plc::launch_scatter(s, a, gc, nullptr, nullptr, -1, ctx->grid_bin, pair,
                                    apply)) != hipSuccess)
         return r;
     }
+    if (beta && plc::dense_possible(a) && (r = plc::launch_dense(s, a)) != hipSuccess) return r;
     if (beta && (r = plc::launch_beta_post(s, a, gw)) != hipSuccess) return r;
+  }
+  for (int i = 0; i < ch.dense; i++) {
+    if (ctx->timing) {
+      // (a dense launch takes the next self step too: no time of its own)
+      const size_t k = (size_t)(ch.pairs + i);
+      if ((r = hipEventRecord(ctx->ev_self[k].a, s)) != hipSuccess) return r;
+      if ((r = hipEventRecord(ctx->ev_self[k].b, s)) != hipSuccess) return r;
+      r = plc::launch_dense(s, a, ctx->ev_scatter[k].a, ctx->ev_scatter[k].b, (int)k);
+    } else {
+      r = plc::launch_dense(s, a);
+    }
+    if (r != hipSuccess) return r;
   }
   return hipSuccess;
 }
@@ -741,52 +844,82 @@ static hipError_t queue_sweep(plc_ctx* ctx, plc_graph* g, int64_t bound);
 // rounds, and pairs queued past the end of the push exit at once but still
 // cost a dispatch each, so the first chunk is the upper quartile of the
 // last queries' counts of working self launches and later chunks are short.
-static int first_chunk(const plc_ctx* ctx) {
-  int chunk = 16;
-  if (!ctx->round_hist.empty()) {
-    std::vector<int> hs(ctx->round_hist.begin(), ctx->round_hist.end());
-    std::sort(hs.begin(), hs.end());
-    chunk = hs[(3 * hs.size()) / 4];
+// (The dense launches behind the pairs likewise.  Without history a graph
+// whose every arc costs no more than a round's other launches goes dense
+// with its first large frontier, so few pairs are queued.)
+static int upper_quartile(const std::deque<int>& hist) {
+  std::vector<int> hs(hist.begin(), hist.end());
+  std::sort(hs.begin(), hs.end());
+  return hs[(3 * hs.size()) / 4];
+}
+
+constexpr int kDenseStep = 8;  // dense launches are queued in multiples of this
+
+static Chunk first_chunk(const plc_ctx* ctx, const plc_graph* g, bool beta = false) {
+  const bool dense = plc::dense_possible(g->args) && !beta;
+  Chunk ch;
+  if (ctx->round_hist.empty()) {
+    const bool small = dense && g->args.dense_free && g->arcs <= plc::kDenseBase;
+    ch.pairs = small ? 2 : 16;
+    ch.dense = small ? 2 * kDenseStep : 0;
+  } else {
+    ch.pairs = upper_quartile(ctx->round_hist);
+    ch.dense = dense ? upper_quartile(ctx->dense_hist) : 0;
   }
-  return std::max(2, std::min(plc::kMaxChunk, chunk));
+  ch.pairs = std::max(2, std::min(plc::kMaxChunk / 2, ch.pairs));
+  ch.dense = std::min(plc::kMaxChunk / 2, (ch.dense + kDenseStep - 1) / kDenseStep * kDenseStep);
+  return ch;
+}
+
+// The next chunk of a query that needs more than its first, by its state.
+static Chunk next_chunk(const Ctl& h, Chunk queued) {
+  Chunk ch;
+  if (h.dense == plc::DN_READY || h.dense == plc::DN_CONVERT) {
+    ch.dense = std::max(2 * kDenseStep, std::min(64, queued.dense / 2));
+    ch.dense = (ch.dense + kDenseStep - 1) / kDenseStep * kDenseStep;
+  } else {
+    ch.pairs = std::max(2, std::min(64, queued.pairs / 3));
+    ch.light = h.dense == plc::DN_LIGHT;
+  }
+  return ch;
 }
 
 // Queue query q's guarded initialisation and first chunk behind the running
 // query's read-back, so that the GPU works on it while the host takes that
-// read-back.  Returns the chunk's pair count (0: nothing queued, -1: error).
-static int prelaunch(plc_ctx* ctx, plc_graph* g, const plc_query& q) {
-  if (!ctx->use_graphs || ctx->timing) return 0;
-  const int R = first_chunk(ctx);
-  Captured* cg = plain_chunk_graph(ctx, g, R, true);
-  if (!cg) return 0;
+// read-back.  Returns the chunk (no pairs: nothing queued; pairs < 0: error).
+static Chunk prelaunch(plc_ctx* ctx, plc_graph* g, const plc_query& q) {
+  if (!ctx->use_graphs || ctx->timing) return Chunk{};
+  const Chunk ch = first_chunk(ctx, g);
+  Captured* cg = plain_chunk_graph(ctx, g, ch, true);
+  if (!cg) return Chunk{};
   hipStream_t s = ctx->stream;
   if (plc::launch_query_init_guarded(s, g->args, q.seed, (int32_t)q.rule, q.alpha, q.eps,
                                      ctx->opt.max_rounds) != hipSuccess ||
       hipGraphLaunch(cg->exec, s) != hipSuccess) {
     ctx->broken = true;
-    return -1;
+    return Chunk{-1, 0};
   }
-  return R;
+  return ch;
 }
 
 // One plain query: from q.seed, or, with set non-null, from the nset
-// distinct seeds in set (q.seed is then ignored).  pre > 0: its guarded
-// initialisation and first chunk of pre pairs are already queued.  next
+// distinct seeds in set (q.seed is then ignored).  pre.pairs > 0: its guarded
+// initialisation and first chunk, pre, are already queued.  next
 // (may be null): the following query, queued behind this one's first
-// read-back; *next_pre receives its chunk (0 when it must start afresh).
+// read-back; *next_pre receives its chunk (no pairs when it must start afresh).
 static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64_t* id_out,
                           plc_result_info* info_out, const int32_t* set = nullptr,
-                          int32_t nset = 0, double beta = 1.0, int pre = 0,
-                          const plc_query* next = nullptr, int* next_pre = nullptr,
+                          int32_t nset = 0, double beta = 1.0, Chunk pre = Chunk{},
+                          const plc_query* next = nullptr, Chunk* next_pre = nullptr,
                           int pipe_in = 0, int* next_pipe = nullptr) {
-  ctx->q_t0 = pre > 0 ? ctx->next_t0 : std::chrono::steady_clock::now();
+  ctx->q_t0 = pre.pairs > 0 ? ctx->next_t0 : std::chrono::steady_clock::now();
   ctx->cur_flags = q.flags;
   ctx->cur_pipe = pipe_in;
-  if (next_pre) *next_pre = 0;
+  if (next_pre) *next_pre = Chunk{};
   if (next_pipe) *next_pipe = 0;
   hipStream_t s = ctx->stream;
   const PlainArgs& a = g->args;
-  if (pre > 0) {
+  if (pre.pairs > 0) {
     // (queued by the previous query's run)
   } else if (set) {
     HIPCHK(ctx, hipMemcpyAsync(a.fbuf0, set, 4 * (size_t)nset, hipMemcpyHostToDevice, s));
@@ -797,8 +930,8 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
                                        ctx->opt.max_rounds, beta));
   }
   const bool use_beta = beta < 1.0;
-  int queued = 0;
-  int chunk = pre > 0 ? pre : first_chunk(ctx);
+  Chunk queued;
+  Chunk chunk = pre.pairs > 0 ? pre : first_chunk(ctx, g, use_beta);
   // Each chunk is followed by the sweep, queued for the largest recent
   // support (its kernels exit at once unless the push has ended with a
   // support within that bound), so a typical query needs one read-back.
@@ -809,22 +942,22 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
     while (spec_bound < mx) spec_bound <<= 1;
   }
   bool swept = false;
-  bool reports = pre > 0;  // the first chunk reports Ctl::bin_pairs
+  bool reports = pre.pairs > 0;  // the first chunk reports Ctl::bin_pairs
   Ctl& h = *ctx->ctl_host;
   for (bool first = true;; first = false) {
-    const int R = chunk;
-    if (!(first && pre > 0)) {
+    const int R = chunk.pairs + chunk.dense;
+    if (!(first && pre.pairs > 0)) {
       // while timing is on, rounds are launched directly (graphs carry no
       // events) (the beta variant's rounds are launched directly too)
       Captured* cg = ctx->use_graphs && !ctx->timing && !use_beta
-                         ? plain_chunk_graph(ctx, g, R, first)
+                         ? plain_chunk_graph(ctx, g, chunk, first)
                          : nullptr;
       if (first && !use_beta) reports = true;  // graph or direct launches, both tracked
       if (ctx->timing) HIPCHK(ctx, hipMemsetAsync(a.work_log, 0, 4 * 2 * (size_t)R, s));
       if (cg)
         HIPCHK(ctx, hipGraphLaunch(cg->exec, s));
       else
-        HIPCHK(ctx, queue_rounds(ctx, g, R, use_beta, first));
+        HIPCHK(ctx, queue_rounds(ctx, g, chunk, use_beta, first));
     }
     if (spec_bound) HIPCHK(ctx, queue_sweep(ctx, g, spec_bound));
     const EventPair* ev_s = ctx->ev_self.data();
@@ -833,7 +966,7 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
     if (ctx->timing)
       HIPCHK(ctx, hipMemcpyAsync(ctx->work_log_h.data(), a.work_log, 4 * 2 * (size_t)R,
                                  hipMemcpyDeviceToHost, s));
-    int held = 0;  // pairs of the next query's chunk queued behind this read-back
+    Chunk held;  // the next query's chunk, if queued behind this read-back
     if (first && next && spec_bound && !set && !use_beta) {
       if (!ctx->rb_event &&
           hipEventCreateWithFlags(&ctx->rb_event, hipEventDisableTiming) != hipSuccess)
@@ -841,14 +974,14 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
       if (ctx->rb_event) {
         HIPCHK(ctx, hipEventRecord(ctx->rb_event, s));
         held = prelaunch(ctx, g, *next);
-        if (held < 0) return PLC_E_HIP;
+        if (held.pairs < 0) return PLC_E_HIP;
       }
     }
-    if (held > 0)
+    if (held.pairs > 0)
       HIPCHK(ctx, hipEventSynchronize(ctx->rb_event));
     else
       HIPCHK(ctx, hipStreamSynchronize(s));
-    if (held > 0) {
+    if (held.pairs > 0) {
       if (h.status == plc::ST_SWEPT) {
         // the next query started behind this one: its time counts from here,
         // when this one is known to be done
@@ -866,7 +999,8 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
           return PLC_E_HIP;
         }
         if (next_pipe) *next_pipe = 2;
-        queued += held;
+        queued.pairs += held.pairs;
+        queued.dense += held.dense;
       }
     }
     if (ctx->timing) {
@@ -887,7 +1021,8 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
         }
       }
     }
-    queued += R;
+    queued.pairs += chunk.pairs;
+    queued.dense += chunk.dense;
     if (h.status == plc::ST_SWEPT) { swept = true; break; }  // pushed and swept
     if (h.status == plc::ST_LIMIT) break;  // watchdog: sweep the partial p
     if (h.status != plc::ST_PUSH || h.fault) {  // unexpected state: device-side fault
@@ -895,10 +1030,12 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
       return PLC_E_HIP;
     }
     if (h.cnt[h.round & 1] == 0) break;     // next frontier empty: the push is done
-    chunk = std::max(2, std::min(64, queued / 3));
+    chunk = next_chunk(h, queued);
   }
-  ctx->round_hist.push_back(h.steps);
+  ctx->round_hist.push_back(h.dsteps > 0 && !use_beta ? h.pairs0 : h.steps);
   if (ctx->round_hist.size() > 16) ctx->round_hist.pop_front();
+  ctx->dense_hist.push_back(use_beta ? 0 : h.dsteps);
+  if (ctx->dense_hist.size() > 16) ctx->dense_hist.pop_front();
   ctx->support_hist.push_back(swept ? h.N : h.support_cnt);
   if (ctx->support_hist.size() > 16) ctx->support_hist.pop_front();
   if (reports) {
@@ -1030,7 +1167,7 @@ extern "C" plc_status plc_run(plc_ctx* ctx, plc_graph* g, const plc_query* q, in
   if (ctx->broken) return PLC_E_HIP;
   (void)hipSetDevice(ctx->device);
   plc_status first = PLC_OK;
-  int pre = 0;   // the current query's queued first chunk (see run_one)
+  Chunk pre;     // the current query's queued first chunk (see run_one)
   int pipe = 0;  // the current query's plc_result_info.pipelined
   for (int32_t i = 0; i < count; i++) {
     if (!query_ok(g, q[i])) {
@@ -1044,7 +1181,8 @@ extern "C" plc_status plc_run(plc_ctx* ctx, plc_graph* g, const plc_query* q, in
     }
     // the next query (when valid) is queued behind this one's first read-back
     const plc_query* nq = i + 1 < count && query_ok(g, q[i + 1]) ? &q[i + 1] : nullptr;
-    int next_pre = 0, next_pipe = 0;
+    Chunk next_pre;
+    int next_pipe = 0;
     plc_status st = run_one(ctx, g, q[i], ids ? &ids[i] : nullptr, infos ? &infos[i] : nullptr,
                             nullptr, 0, 1.0, pre, nq, &next_pre, pipe, &next_pipe);
     pre = next_pre;
@@ -1122,11 +1260,30 @@ extern "C" plc_status plc_run_hkpr(plc_ctx* ctx, plc_graph* g, int32_t seed, int
   // PR-Nibble sample the shape was tuned on: at least CU/2 workgroups)
   const int gs = std::max(shape(g->plain_self, ctx->grid_self), ctx->num_cu / 2);
   const int gc = shape(g->plain_scatter, ctx->grid_scatter);
-  for (int32_t j = 0; j < N; j++) HIPCHK(ctx, plc::launch_hk_level(s, a, gs, gc));
-  HIPCHK(ctx, plc::launch_hk_clear(s, a, shape(g->plain_sweep, ctx->grid_sweep)));
+  // levels as pairs, then as dense launches, as many of each as the last
+  // query used (every level either way the first time); then, with a
+  // read-back, whatever is left in the form the push is held in
   Ctl& h = *ctx->ctl_host;
-  HIPCHK(ctx, hipMemcpyAsync(&h, a.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
-  HIPCHK(ctx, hipStreamSynchronize(s));
+  const bool dense = plc::dense_possible(a);
+  const bool known = g->hk_dense >= 0;
+  int np = known && g->hk_dense > 0 ? std::min(N, g->hk_pairs) : N;
+  int nd = !dense ? 0 : known ? std::min(N, g->hk_dense) : N;
+  bool light = false;
+  for (;;) {
+    if (light) HIPCHK(ctx, plc::launch_hk_light(s, a, gs, gc));
+    for (int j = 0; j < np; j++) HIPCHK(ctx, plc::launch_hk_level(s, a, gs, gc));
+    for (int j = 0; j < nd; j++) HIPCHK(ctx, plc::launch_hk_dense(s, a));
+    HIPCHK(ctx, plc::launch_hk_clear(s, a, shape(g->plain_sweep, ctx->grid_sweep)));
+    HIPCHK(ctx, hipMemcpyAsync(&h, a.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+    HIPCHK(ctx, hipStreamSynchronize(s));
+    if (h.status != plc::ST_PUSH || h.fault || h.cnt[h.round & 1] == 0 || h.round >= N) break;
+    const bool in_dense = h.dense == plc::DN_READY || h.dense == plc::DN_CONVERT;
+    np = in_dense ? 0 : N - h.round;
+    nd = in_dense ? N - h.round + 1 : 0;  // (one may be the way back)
+    light = h.dense == plc::DN_LIGHT;
+  }
+  g->hk_pairs = h.dsteps > 0 ? h.pairs0 : h.steps;
+  g->hk_dense = h.dsteps;
   if (h.status != plc::ST_PUSH || h.cnt[h.round & 1] != 0 || h.fault) {
     ctx->broken = true;
     return PLC_E_HIP;

@@ -39,7 +39,7 @@ enum : int32_t { SCAN_FRONTIER = 0, SCAN_VOL = 1, SCAN_CUT = 2, NUM_SCANS = 3 };
 // Last-workgroup counters.
 enum : int32_t {
   DONE_SCATTER = 0, DONE_KEYS = 1, DONE_SORT = 2, DONE_FINISH = 3, DONE_SELF = 4, DONE_BIN = 5,
-  NUM_DONE = 8
+  DONE_DENSE = 6, NUM_DONE = 8
 };
 
 // Where the running sweep writes its results (the library's own buffers,
@@ -56,16 +56,26 @@ struct SweepOut {
 // Device control block of one plain-path query.  Written by kernels only,
 // except at query start (k_query_init) and read back by the host.
 struct __align__(64) Ctl {
-  // query parameters
-  double cs, cn, keep, eps;
-  int32_t seed, rule, max_rounds, opt_rule;  // opt_rule = 1 for the optimized rule
-  // round state
+  // round state, which every launch reads first (ctl_head: one 64-byte line)
   int32_t status;
   int32_t round;          // rounds pushed so far; frontier of round t is fbuf[t&1], size cnt[t&1]
   int32_t cnt[2];
+  int32_t dense;          // DN_*: how the current round's frontier is held
+  int32_t selfed;         // the round whose entries the last self step built (or -1)
   int32_t ntiles;         // edge tiles of the current round (or of the sweep's edges)
-  uint32_t bin_pairs;     // bit i: the round of a first chunk's launch pair i could bin or pull
+  int32_t max_rounds;
   long long etotal;       // sum of degrees of the current frontier (or vol(S_N) in the sweep)
+  double eps;
+  int32_t cd_dirty;       // bit k: a.cd[k] may hold nonzeros
+  int32_t opt_rule;       // 1 for the optimized rule
+  uint32_t bin_pairs;     // bit i: the round of a first chunk's launch pair i could bin
+  int32_t rule;
+  // query parameters (the next line)
+  double cs, cn, keep;
+  double beta;            // fraction of the active set pushed per round (end of Sec. 3.3)
+  double hk_t, hk_A;      // HK-PR (Sec. 3.4): t, e^-t * eps,
+  int32_t hk_N, seed;     // and the Taylor degree
+  long long pad0;
   long long pushes, edges;
   int32_t support_cnt;    // |support list|
   int32_t touched_cnt;    // |touched list|
@@ -83,41 +93,59 @@ struct __align__(64) Ctl {
   long long kstar;
   double phi;
   SweepOut out;           // result destinations of the running sweep
-  // HK-PR (Sec. 3.4): Taylor degree, t, e^-t * eps, and the lengths of the
-  // three rotating per-level touched lists (level k uses list k % 3; Nibble
-  // uses the same lists and arrays for its vectors)
-  int32_t hk_N;
+  // lengths of HK-PR's three rotating per-level touched lists (level k uses
+  // list k % 3; Nibble uses the same lists and arrays for its vectors)
   int32_t hk_tlc[3];
-  double hk_t, hk_A;
-  // beta variant of PR-Nibble (end of Sec. 3.3): the fraction of the active
-  // set pushed per round, and this round's active count and pushed count
-  double beta;
+  int32_t pad3;
+  // beta variant of PR-Nibble: this round's active count and pushed count
   int32_t beta_nf, beta_k;
-  // round bookkeeping: `selfed` is the round whose entries the last self
-  // step built (the scatter pushes only that round); `steps` counts self
-  // launches that did work; loop_rounds / loop_pushes / loop_edges count
-  // the small rounds a self launch ran on its own
-  int32_t selfed, steps;
+  // round bookkeeping: `steps` counts self launches that did work;
+  // loop_rounds / loop_pushes / loop_edges count the small rounds a self
+  // launch ran on its own
+  int32_t steps, pad2;
   int32_t loop_rounds;
   int32_t init_held;  // a queued guarded initialisation found the previous query unfinished
   long long loop_pushes, loop_edges;
   // rounds whose scatter went through the destination bins, and their edges
   int32_t bin_rounds;
-  int32_t pull_rounds;  // among bin_rounds: rounds in the pull form
+  int32_t pull_rounds;  // among bin_rounds: rounds in the dense form
   long long bin_edges;
   // constant-rate clock (wall_clock64) at the query's initialisation and at
   // the end of its sweep
   long long t_start, t_end;
+  // dense rounds: the next round's edges as they are counted (edges << 16 |
+  // groups of workgroups done), the frontier list's length while it is rebuilt, `steps`
+  // before the first dense round, dense launches that did work, and how many
+  // of them ran a round whose self step an earlier one took (in `steps` too)
+  unsigned long long enext;
+  int32_t fill;
+  int32_t pairs0, dsteps, dself;
+};
+
+// Ctl::dense.  LIST: frontier list (the other forms).  READY: the round's
+// self step is done and cd[t & 1] holds its coefficients, 0 off the frontier
+// (cnt[t & 1] is then only known to be positive).
+// CONVERT: the same, but the round goes back to the list form; LIGHT: the
+// list has been rebuilt, the entries not yet.
+enum : int32_t { DN_LIST = 0, DN_READY = 1, DN_CONVERT = 2, DN_LIGHT = 3 };
+
+// One block of the dense round: nrows consecutive rows from row on (at most
+// kDenseRows, kDenseArcs arcs), or, with lid >= 0, one piece of the arcs of a
+// row longer than kDenseArcs (nrows pieces in all).
+struct __align__(32) DenseBlk {
+  int32_t row, nrows, lid, len;
+  long long first;  // first arc and number of arcs
+};
+
+// A dense round's book for kDenseGroup workgroups, a line of its own: edges
+// of the next frontier << 16 | workgroups done, and its vertices (by parity
+// of the round they are pushed in).
+struct __align__(128) DenseGrp {
+  unsigned long long word;
+  int32_t nf[2];
 };
 
 // Arguments shared by the plain-path kernels (all device pointers).
-// Per-vertex pull record: the vertex's coefficient cn rho / d in the round
-// whose epoch is stamped.
-struct __align__(16) PullRec {
-  double coef;
-  uint32_t stamp;
-  int32_t pad;
-};
 
 struct PlainArgs {
   int64_t n;
@@ -172,15 +200,22 @@ struct PlainArgs {
   const long long* bin_vol;    // [nbins] sum of degrees over the bin
   int32_t* bin_T;              // [(nbins + 1) x bin_cmax]: start of bin b's run in chunk c
   int2* bin_pairs;             // [bin_cmax x kBinChunk]: (neighbour, entry) by bin per chunk
-  // Pull form of a binned round, for rounds of at least pull_emin edges
-  // (half the graph's arcs): each bin sums, over its own vertices' arcs, the
-  // coefficients of the neighbours on the round's frontier, which the
-  // round's scatter launch stamps with the round's epoch.  The epoch advances
-  // at every round close and is never reset, so records of earlier rounds
-  // and queries never match.  pull = null turns it off.
-  PullRec* pull;               // [n]
-  unsigned* pull_epoch;
-  long long pull_emin;
+  // Dense rounds: every row sums the coefficients of its neighbours from a
+  // dense array (0 off the frontier) and takes its own next self step in the
+  // same launch; cd[t & 1] is read and cd[(t + 1) & 1] written by round t.
+  // dblk covers all rows; rows cut into pieces meet in dacc / dcnt (one per
+  // such row, 0 between launches).  cd[0] = null turns it off.  dense_free:
+  // the threshold was left to the library, so the form follows the cost
+  // rule of dense_pays; otherwise rounds of at least bin_emin edges that
+  // cover half the arcs (dense_emin) are dense.
+  double* cd[2];               // [n] each
+  const DenseBlk* dblk;        // [ndblk]
+  int32_t ndblk;
+  int32_t dense_free;
+  double* dacc;
+  unsigned* dcnt;
+  DenseGrp* dgrp;              // [kDenseGroups]
+  long long dense_emin;
 };
 
 // Launch configuration.
@@ -216,12 +251,23 @@ constexpr long long kBinOff = 1ll << 62;  // a threshold no round reaches: binni
 // larger graphs use the atomic scatter only (their width-bound bins alone
 // would crowd out the volume-balanced ones)
 constexpr long long kBinMaxVertices = (long long)kMaxBins * 3 / 4 * kBinWidth;
+// Dense rounds: rows and arcs of one block, and the cost rule (dense_pays).
+constexpr int kDenseRows = 256;
+constexpr int kDenseArcs = 2048;
+constexpr int kDenseSpan = 16384;  // rows of a block x its longest row, at most
+constexpr int kDenseGroup = 32;    // workgroups that count themselves on one line
+constexpr int kDenseGroups = 64;
+constexpr long long kDenseBase = 1 << 20;
+constexpr int kDenseRatio = 4;
 static_assert(kBinChunk <= 65536 && kMaxBins <= 32768, "pass A packs (bin, rank) in 32 bits");
 
-// Whether a round of this graph can be binned or pulled (both need bins and
+// Whether a round of this graph can be binned or dense (both need bins and
 // a reachable threshold); otherwise k_bin_apply never has work and the
 // scatter closes every round itself.
 inline bool bins_possible(const PlainArgs& a) { return a.nbins > 0 && a.bin_emin < kBinOff; }
+inline bool dense_possible(const PlainArgs& a) {
+  return a.cd[0] != nullptr && a.bin_emin < kBinOff;
+}
 
 // Host-side launchers (return hipError_t of the launch).
 hipError_t launch_graph_init(hipStream_t s, const PlainArgs& a);
@@ -260,13 +306,23 @@ hipError_t launch_nb_finish(hipStream_t s, const PlainArgs& a, int32_t R, int32_
 // a.work_log[2 slot] (self) or a.work_log[2 slot + 1] (scatter).
 hipError_t launch_self(hipStream_t s, const PlainArgs& a, int grid, hipEvent_t t0 = nullptr,
                        hipEvent_t t1 = nullptr, int slot = -1);
+// One dense round, or the way back to the list form (exits at once while the
+// push is held as a list).
+hipError_t launch_dense(hipStream_t s, const PlainArgs& a, hipEvent_t t0 = nullptr,
+                        hipEvent_t t1 = nullptr, int slot = -1);
+// The self step of a round handed back to the list form (its scatter
+// follows as after any other).
+hipError_t launch_light_self(hipStream_t s, const PlainArgs& a, int grid, hipEvent_t t0 = nullptr,
+                             hipEvent_t t1 = nullptr, int slot = -1);
+hipError_t launch_hk_dense(hipStream_t s, const PlainArgs& a);
+hipError_t launch_hk_light(hipStream_t s, const PlainArgs& a, int grid_self, int grid_scatter);
 // The scatter of a PR-Nibble round: k_scatter (the atomic scatter, or pass A
 // of the binned scatter for rounds of a.bin_emin edges and more), then
 // k_bin_apply (pass B; exits at once after an atomic round).  With t0 set,
 // t0 stamps k_scatter's start and t1 the end of the last kernel queued.
 // apply = false leaves k_bin_apply out (t1 then stamps k_scatter's end): the
 // round then takes the atomic form whatever its size.  pair in [0, 32): the launch pair's index in a first chunk; a round
-// that could bin or pull sets bit pair of the control block's bin_pairs.
+// that could bin sets bit pair of the control block's bin_pairs.
 hipError_t launch_scatter(hipStream_t s, const PlainArgs& a, int grid, hipEvent_t t0 = nullptr,
                           hipEvent_t t1 = nullptr, int slot = -1, int grid_bin = 1024,
                           int pair = -1, bool apply = true);
