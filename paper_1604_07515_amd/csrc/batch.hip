@@ -1329,7 +1329,6 @@ static hipError_t sweep_kernels(hipStream_t s, const BatchArgs& a, int nseg, int
   sa.buf[1] = a.sbuf[1];
   sa.count = &a.ctl->sw_total;
   sa.flip = &a.ctl->sort_flip;
-  sa.done = &a.ctl->done[0];
   sa.active = nullptr;
   sa.active_value = 0;
   sa.rank = nullptr;

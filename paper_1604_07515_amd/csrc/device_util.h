@@ -75,16 +75,38 @@ __device__ __forceinline__ void atomic_st64(unsigned long long* p, unsigned long
 
 constexpr long kSpinLimit = 1L << 24;
 
-// Clear the other buffer's slots used by the previous launch (all workgroups
-// share the work).  Call once per workgroup at kernel start.
-__device__ __forceinline__ void scan_clear_prev(ScanSite* site, unsigned long long* desc2,
-                                                int cap) {
+// Clear the other buffer's slots used by the previous launch (the first
+// `members` workgroups share the work; 0: all of them).  Call once per
+// workgroup at kernel start.
+__device__ __forceinline__ void scan_clear_prev(const ScanSite* site, unsigned long long* desc2,
+                                                int cap, int members = 0) {
   unsigned par = site->parity;
   int prev = site->prev_nblk;
   if (prev > cap) prev = cap;
   unsigned long long* other = desc2 + (size_t)(par ^ 1u) * cap;
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < prev; j += gridDim.x * blockDim.x)
+  const int m = members > 0 ? members : (int)gridDim.x;
+  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < prev; j += m * blockDim.x)
     other[j] = 0ull;
+}
+
+// Scans of few blocks: workgroup b takes block b and the workgroups past them
+// leave at once, so the dispenser's word, which every workgroup of the launch
+// adds to otherwise (~10 ns each, one after another), is touched only by the
+// nblk of them as they finish (scan_retire).  Up to kScanFixed blocks: one
+// per CU, so that all of them are resident together and none waits for one
+// that cannot start.
+constexpr int kScanFixed = 256;
+__device__ __forceinline__ bool scan_fixed(int nblk) {
+  return nblk <= kScanFixed && nblk <= (int)gridDim.x;
+}
+// One thread per workgroup, after the workgroup's last use of the site.
+// Returns true in the last of them.
+__device__ __forceinline__ bool scan_retire(ScanSite* site, int nblk) {
+  if (atomicAdd(&site->ticket, 1u) != (unsigned)nblk - 1) return false;
+  site->ticket = 0;
+  site->parity ^= 1u;
+  site->prev_nblk = nblk;
+  return true;
 }
 
 // Decoupled look-back for block b, by the 64 lanes of wave 0 together (call
@@ -214,6 +236,28 @@ __device__ __forceinline__ void wave_append(bool pred, int32_t v, int32_t* buf, 
   if (pred) buf[base + __popcll(m & lanemask_lt())] = v;
 }
 
+// The same for up to K values per lane, those of the bits set in pred: one
+// LDS atomic per wave for all of them (each is a round trip to LDS, one after
+// another otherwise).
+template <int K>
+__device__ __forceinline__ void wave_append_all(unsigned pred, const int32_t (&v)[K],
+                                                int32_t* buf, int* cnt) {
+  int n = __popc(pred);  // inclusive scan of the lanes' counts
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(n, o);
+    if ((int)PLC_LANE >= o) n += y;
+  }
+  const int tot = __shfl(n, 63);
+  if (tot == 0) return;
+  int base = 0;
+  if (PLC_LANE == 63) base = atomicAdd(cnt, tot);
+  int at = __shfl(base, 63) + n - __popc(pred);
+#pragma unroll
+  for (int k = 0; k < K; k++)
+    if ((pred >> k) & 1u) buf[at++] = v[k];
+}
+
 // Workgroup-aggregated append of the values staged in an LDS buffer:
 // one global atomic per call.  Every thread must call it.  Writes
 // dst[base + j] = buf[j] for j < *count (slots >= cap raise *fault).
@@ -231,6 +275,33 @@ __device__ __forceinline__ void block_flush(int32_t* counter, int32_t* dst, int6
   }
   __syncthreads();
   if (threadIdx.x == 0) *count = 0;
+  __syncthreads();
+}
+
+// Two lists at once (block_flush for each): the two reservations are in
+// flight together and share the barriers.
+__device__ __forceinline__ void block_flush2(int32_t* ctr0, int32_t* dst0, const int32_t* buf0,
+                                             int* cnt0, int32_t* ctr1, int32_t* dst1,
+                                             const int32_t* buf1, int* cnt1, int64_t cap,
+                                             int* s_base /* 2 */, int* fault) {
+  __syncthreads();
+  const int n0 = *cnt0, n1 = *cnt1;
+  if (threadIdx.x < 2) {
+    const int m = threadIdx.x == 0 ? n0 : n1;
+    s_base[threadIdx.x] = m > 0 ? atomicAdd(threadIdx.x == 0 ? ctr0 : ctr1, m) : 0;
+  }
+  __syncthreads();
+  const long long b0 = s_base[0], b1 = s_base[1];
+  for (int j = threadIdx.x; j < n0; j += blockDim.x) {
+    if (b0 + j < cap) dst0[b0 + j] = buf0[j]; else *fault = 1;
+  }
+  for (int j = threadIdx.x; j < n1; j += blockDim.x) {
+    if (b1 + j < cap) dst1[b1 + j] = buf1[j]; else *fault = 1;
+  }
+  if (threadIdx.x == 0) {
+    *cnt0 = 0;
+    *cnt1 = 0;
+  }
   __syncthreads();
 }
 

@@ -36,8 +36,8 @@
 //
 // The sweep: k_sweep_keys, the sort (sort.hip; its block-sort launch also
 // gathers the nonzeros of r over the touched list and resets r, on the
-// workgroups that hold no tile), k_vol_scan, k_cut_count, k_cut_scan (which
-// also resets p and the ranks) and a one-workgroup k_sweep_finish.
+// workgroups that hold no tile), k_vol_scan, k_cut_count and k_cut_scan (which
+// also resets p and the ranks, and takes the best prefix).
 //
 // Arithmetic matches the paper's updates evaluated in a fixed way: the
 // constants cs, cn, keep are rounded once, p[v] + cs*rho, keep*rho and
@@ -75,6 +75,7 @@ __global__ void k_graph_init(PlainArgs a) {
 
 __device__ __forceinline__ void reset_round_book(Ctl* c) {
   c->init_held = 0;
+  c->pend = 0;
   c->selfed = -1;
   c->steps = 0;
   c->loop_rounds = 0;
@@ -224,22 +225,37 @@ __global__ void k_query_init_set(PlainArgs a, int32_t nseeds, int32_t rule, doub
 // loads each field behind the test of the one before, a chain of cache
 // misses at the start of every launch.
 struct CtlHead {
-  int32_t status, round, cnt0, cnt1, dense, selfed;
+  int32_t status, round, cnt0, cnt1, dense, selfed, max_rounds;
+  double beta;
+  __device__ int nf() const { return (round & 1) ? cnt1 : cnt0; }
 };
 __device__ __forceinline__ CtlHead ctl_head(const Ctl* c) {
-  CtlHead h{c->status, c->round, c->cnt[0], c->cnt[1], c->dense, c->selfed};
+  CtlHead h{c->status, c->round, c->cnt[0], c->cnt[1], c->dense, c->selfed, c->max_rounds,
+            c->beta};
   asm volatile("" : "+s"(h.status), "+s"(h.round), "+s"(h.cnt0), "+s"(h.cnt1), "+s"(h.dense),
-               "+s"(h.selfed));
+               "+s"(h.selfed), "+s"(h.max_rounds), "+s"(h.beta));
+  return h;
+}
+// The same with what else of that line the scatter takes.
+struct CtlEdges {
+  int32_t ntiles;
+  long long etotal;
+  double eps;
+};
+__device__ __forceinline__ CtlHead ctl_head(const Ctl* c, CtlEdges* edges) {
+  CtlEdges q{c->ntiles, c->etotal, c->eps};
+  const CtlHead h = ctl_head(c);
+  asm volatile("" : "+s"(q.ntiles), "+s"(q.etotal), "+s"(q.eps));
+  *edges = q;
   return h;
 }
 
-__device__ __forceinline__ bool push_active(const Ctl* c, int64_t ncap, int* t_out, int* nf_out) {
-  if (c->status != ST_PUSH) return false;
-  int t = c->round;
-  int nf = c->cnt[t & 1];
-  if (nf <= 0) return false;
+__device__ __forceinline__ bool push_active(const CtlHead& h, int64_t ncap, int* t_out,
+                                            int* nf_out) {
+  int nf = h.nf();
+  if (h.status != ST_PUSH || nf <= 0) return false;
   if ((int64_t)nf > ncap) nf = (int)ncap;
-  *t_out = t;
+  *t_out = h.round;
   *nf_out = nf;
   return true;
 }
@@ -276,35 +292,43 @@ __device__ __forceinline__ double* hk_res(const PlainArgs& a, int k, int32_t v) 
 //   LIGHT (a round handed back by the dense form): the self step was taken
 //     there; the entries take their coefficients from cd[t & 1], which is
 //     cleared again.
-template <int MODE, bool LIGHT>
-__device__ __forceinline__ void self_body(const PlainArgs& a, int slot) {
+template <int MODE, bool LIGHT, int NT>
+__device__ __forceinline__ void self_body(const PlainArgs& a, int slot, const CtlHead& h) {
   constexpr bool HK = MODE == kModeHK;
+  constexpr int kItems = kScanBlock / NT;  // entries per thread
   constexpr bool LEVELS = MODE != kModePR;
   Ctl* c = a.ctl;
   int t, nf;
-  if (!push_active(c, a.n, &t, &nf)) return;
+  if (!push_active(h, a.n, &t, &nf)) return;
   if (LEVELS) {
-    if (t >= (HK ? c->hk_N : c->max_rounds)) return;  // (the host queues no more)
+    if (t >= (HK ? c->hk_N : h.max_rounds)) return;  // (the host queues no more)
     if (t >= 1) {
       const int lp = (t + 2) % 3;
       const int np = c->hk_tlc[lp];
       const int32_t* Lp = a.hk_tl[lp];
-      for (int i = blockIdx.x * kBlock + threadIdx.x; i < np; i += gridDim.x * kBlock)
+      for (int i = blockIdx.x * NT + threadIdx.x; i < np; i += gridDim.x * NT)
         *hk_res(a, t + 1, Lp[i]) = 0.0;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) c->hk_tlc[(t + 1) % 3] = 0;
-  } else if (t >= c->max_rounds) {
+  } else if (t >= h.max_rounds) {
     if (blockIdx.x == 0 && threadIdx.x == 0) { c->limited = 1; c->status = ST_LIMIT; }
     return;
   }
-  __shared__ long long sh[kBlock / 64 + 1];
+  __shared__ long long sh[NT / 64 + 1];
   __shared__ long long s_excl;
   __shared__ int s_tk[2];
   __shared__ int32_t s_sup[kScanBlock];
   __shared__ int32_t s_stay[LEVELS ? 1 : kScanBlock];
   __shared__ int s_nsup, s_nstay, s_base;
+  const int nblk = (nf + kScanBlock - 1) / kScanBlock;
+  // a frontier of one scan block is handled by workgroup 0 alone, with no
+  // ticket and no look-back (its exclusive prefix is 0; no descriptor is
+  // published and the scan site is left as it was)
+  const bool solo = nblk == 1 && !LIGHT;
+  const bool fixed = !LIGHT && scan_fixed(nblk);
+  if (fixed && (int)blockIdx.x >= nblk) return;
   ScanSite* site = &c->scan[SCAN_FRONTIER];
-  scan_clear_prev(site, a.desc[SCAN_FRONTIER], a.desc_cap);
+  scan_clear_prev(site, a.desc[SCAN_FRONTIER], a.desc_cap, fixed ? nblk : 0);
   unsigned long long* desc = a.desc[SCAN_FRONTIER] + (size_t)site->parity * a.desc_cap;
   const int32_t* F = (t & 1) ? a.fbuf1 : a.fbuf0;
   int32_t* Fn = (t & 1) ? a.fbuf0 : a.fbuf1;
@@ -313,79 +337,86 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot) {
   const bool opt = LEVELS || c->opt_rule != 0;
   const bool hk_last = HK && t + 1 == c->hk_N;
   const double hk_t = HK ? c->hk_t : 0.0;
-  const int nblk = (nf + kScanBlock - 1) / kScanBlock;
-  // a frontier of one scan block is handled by workgroup 0 alone, with no
-  // ticket and no look-back (its exclusive prefix is 0; no descriptor is
-  // published and the scan site is left as it was)
-  const bool solo = nblk == 1 && !LIGHT;
-  if (solo && blockIdx.x != 0) return;
   double* const cd = LIGHT ? a.cd[t & 1] : nullptr;
   if (threadIdx.x == 0) { s_nsup = 0; s_nstay = 0; }
   __syncthreads();
 
   for (int pass = 0;; pass++) {
     int b;
-    if (solo) {
+    if (fixed) {
       if (pass > 0) break;
-      b = 0;
+      b = blockIdx.x;
     } else {
       bool last;
       b = scan_ticket(site, nblk, s_tk, &last);
       if (b >= nblk) break;
     }
-    // each thread takes kScanItems consecutive entries: one workgroup scan
-    // of the per-thread sums, then a serial prefix inside the thread
-    const int i0 = b * kScanBlock + (int)threadIdx.x * kScanItems;
-    int32_t dk[kScanItems];
-    long long dsum = 0;
+    // each thread takes kItems consecutive entries: one workgroup scan
+    // of the per-thread sums, then a serial prefix inside the thread.  All
+    // loads of the thread's entries go out together, before any store (entry
+    // by entry they were a chain of 6 us for a block, 2 us so).
+    const int i0 = b * kScanBlock + (int)threadIdx.x * kItems;
+    int32_t dk[kItems], vk[kItems];
+    const int mine = nf - i0;  // entries of this thread (may be < 0, or more than it takes)
+    if (mine >= kItems) {
+      if constexpr (kItems == 4) {
+        const int4 f = *reinterpret_cast<const int4*>(F + i0);
+        vk[0] = f.x; vk[1] = f.y; vk[2] = f.z; vk[3] = f.w;
+      } else {
 #pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
-      const int i = i0 + k;
-      int32_t d = 0;
-      int32_t v = 0;
-      bool stay = false, sup = false;
-      if (i < nf) {
-        v = F[i];
-        double rho = 0.0;
-        if (LIGHT) {
-          const VRec rec = a.vr[v];
-          d = rec.deg;
-          stay = !opt && rec.r >= eps * (double)d;  // (r is keep rho already)
-        } else if (LEVELS) {
-          rho = *hk_res(a, t, v);
-          d = a.vr[v].deg;
-        } else {
-          VRec rec = a.vr[v];
-          rho = rec.r;
-          d = rec.deg;
-        }
-        double pold = MODE == kModeNB || LIGHT ? 1.0 : a.p[v];
-        if (LIGHT) {
-          a.coef[i] = cd[v];
-          cd[v] = 0.0;
-        } else if (MODE == kModeNB) {
-          a.coef[i] = rho / (2.0 * (double)d);
-          a.sp[i] = rho / 2.0;
-        } else if (HK) {
-          a.p[v] = pold + rho;
-          a.coef[i] = hk_last ? rho / (double)d : (hk_t * rho) / ((double)(t + 1) * (double)d);
-        } else {
-          a.p[v] = pold + cs * rho;
-          double nr = opt ? -0.0 : keep * rho;
-          a.vr[v].r = nr;
-          a.coef[i] = (cn * rho) / (double)d;
-          stay = !opt && nr >= eps * (double)d;
-        }
-        a.rowp[i] = a.off[v];
-        sup = pold == 0.0;
+        for (int k = 0; k < kItems; k++) vk[k] = F[i0 + k];
       }
-      wave_append(stay, v, s_stay, &s_nstay);
-      wave_append(sup, v, s_sup, &s_nsup);
+    } else {
+#pragma unroll
+      for (int k = 0; k < kItems; k++) vk[k] = F[k < mine ? i0 + k : 0];
+    }
+    VRec rec[kItems];
+    double xk[kItems], pk[kItems];
+    int64_t rk[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; k++) {
+      const int32_t v = vk[k];
+      rec[k] = a.vr[v];
+      xk[k] = LIGHT ? cd[v] : LEVELS && (t & 1) ? a.hk_r1[v] : rec[k].r;
+      pk[k] = MODE == kModeNB || LIGHT ? 1.0 : a.p[v];
+      rk[k] = a.off[v];
+    }
+    long long dsum = 0;
+    unsigned sup = 0, stay = 0;  // bit k: entry k
+#pragma unroll
+    for (int k = 0; k < kItems; k++) {
+      const int i = i0 + k;
+      const int32_t v = vk[k];
+      dk[k] = 0;
+      if (k >= mine) continue;
+      const int32_t d = rec[k].deg;
+      const double rho = xk[k];
       dk[k] = d;
       dsum += d;
+      if (pk[k] == 0.0) sup |= 1u << k;
+      if (LIGHT) {
+        a.coef[i] = rho;  // (the coefficient itself)
+        cd[v] = 0.0;
+        if (!opt && rec[k].r >= eps * (double)d) stay |= 1u << k;  // (r is keep rho already)
+      } else if (MODE == kModeNB) {
+        a.coef[i] = rho / (2.0 * (double)d);
+        a.sp[i] = rho / 2.0;
+      } else if (HK) {
+        a.p[v] = pk[k] + rho;
+        a.coef[i] = hk_last ? rho / (double)d : (hk_t * rho) / ((double)(t + 1) * (double)d);
+      } else {
+        a.p[v] = pk[k] + cs * rho;
+        const double nr = opt ? -0.0 : keep * rho;
+        a.vr[v].r = nr;
+        a.coef[i] = (cn * rho) / (double)d;
+        if (!opt && nr >= eps * (double)d) stay |= 1u << k;
+      }
+      a.rowp[i] = rk[k];
     }
+    if (!opt) wave_append_all<kItems>(stay, vk, s_stay, &s_nstay);
+    if (MODE != kModeNB && !LIGHT) wave_append_all<kItems>(sup, vk, s_sup, &s_nsup);
     long long agg;
-    const long long ex = block_excl_scan<kBlock>(dsum, &agg, sh);
+    const long long ex = block_excl_scan<NT>(dsum, &agg, sh);
     if (solo) {
       if (threadIdx.x == 0) s_excl = 0;
     } else if (threadIdx.x < 64) {
@@ -395,7 +426,7 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot) {
     __syncthreads();
     long long s = s_excl + ex;
 #pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
+    for (int k = 0; k < kItems; k++) {
       const int i = i0 + k;
       if (i < nf) {
         a.estart[i] = s;
@@ -411,10 +442,11 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot) {
       c->steps += 1;
       if (slot >= 0) a.work_log[2 * slot] = 1;
     }
-    if (MODE != kModeNB)
+    if (MODE != kModeNB && !LIGHT)
       block_flush(&c->support_cnt, a.support, a.n, s_sup, &s_nsup, &s_base, &c->fault);
     if (!opt) block_flush(cntn, Fn, a.n, s_stay, &s_nstay, &s_base, &c->fault);
   }
+  if (fixed && !solo && threadIdx.x == 0) (void)scan_retire(site, nblk);
   // (every workgroup has read the state it decided on by the time the last
   // one gets here)
   if (LIGHT && last_block(&c->done[DONE_DENSE], &s_base, false) && threadIdx.x == 0) {
@@ -446,7 +478,7 @@ __device__ __forceinline__ void st_agent(T* p, T v) {
 // workgroup is the only writer of the list, so the base is its own count.
 __device__ __forceinline__ void local_append(int32_t* dst, int64_t cap, int32_t* mirror,
                                              const int32_t* buf, int n, int base, int* fault) {
-  for (int j = threadIdx.x; j < n; j += kBlock) {
+  for (int j = threadIdx.x; j < n; j += kSelfBlk) {
     const long long slot = (long long)base + j;
     if (slot < cap) dst[slot] = buf[j]; else *fault = 1;
     if (mirror && slot < kScanBlock) mirror[slot] = buf[j];
@@ -466,15 +498,17 @@ __device__ __forceinline__ void local_append(int32_t* dst, int64_t cap, int32_t*
 // after kLoopMaxRounds rounds.
 __device__ void loop_rounds(const PlainArgs& a, int slot, int t, int nf) {
   Ctl* c = a.ctl;
+  constexpr int kItems = kScanBlock / kSelfBlk;  // entries per thread
   __shared__ int32_t s_F[2][kScanBlock];  // this round's and the next round's frontier
   __shared__ int32_t s_est[kScanBlock];   // entry i: first edge in the round's edge sequence
   __shared__ int64_t s_row[kScanBlock];   //          off[v]
   __shared__ double s_cf[kScanBlock];     //          cn rho / d(v)
+  __shared__ unsigned short s_own[kLoopPass];  // edge of the pass: its entry's place
   __shared__ int32_t s_fn[kLoopPass];     // crossings of one pass
   __shared__ int32_t s_tv[kLoopPass];     // first touches of one pass
   __shared__ int32_t s_sup[kScanBlock];
   __shared__ int32_t s_stay[kScanBlock];
-  __shared__ long long sh[kBlock / 64 + 1];
+  __shared__ long long sh[kSelfBlk / 64 + 1];
   __shared__ int s_nfn, s_ntv, s_nsup, s_nstay;
   if (threadIdx.x == 0) {
     s_nfn = 0;
@@ -494,41 +528,49 @@ __device__ void loop_rounds(const PlainArgs& a, int slot, int t, int nf) {
   for (int it = 0;; it++) {
     const int32_t* F = it > 0 ? s_F[cur] : (t & 1) ? a.fbuf1 : a.fbuf0;
     int32_t* Fn = (t & 1) ? a.fbuf0 : a.fbuf1;
-    // vertexMap(Frontier, UpdateSelf) and the degree scan
-    const int i0 = (int)threadIdx.x * kScanItems;
-    int32_t dk[kScanItems];
-    double ck[kScanItems];
-    int64_t rk[kScanItems];
-    long long dsum = 0;
+    // vertexMap(Frontier, UpdateSelf) and the degree scan.  Thread j's entries
+    // are the frontier's j, j + kSelfBlk, ... (a small frontier is one entry per
+    // thread), kept at places per j, per j + 1, ...: a place past the frontier
+    // holds an entry of no edges.  All loads go out before any store.
+    const int per = (nf + kSelfBlk - 1) / kSelfBlk;
+    int32_t dk[kItems], vk[kItems];
+    double ck[kItems], xk[kItems], pk[kItems];
+    int64_t rk[kItems];
+    const int mine = (nf - (int)threadIdx.x + kSelfBlk - 1) / kSelfBlk;  // (may be < 0)
 #pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
-      const int i = i0 + k;
-      int32_t d = 0;
-      int32_t v = 0;
-      bool stay = false, sup = false;
-      ck[k] = 0.0;
+    for (int k = 0; k < kItems; k++) vk[k] = k < mine ? F[k * kSelfBlk + (int)threadIdx.x] : 0;
+#pragma unroll
+    for (int k = 0; k < kItems; k++) {
+      dk[k] = 0;
+      xk[k] = 0.0;
+      pk[k] = 0.0;
       rk[k] = 0;
-      if (i < nf) {
-        v = F[i];
-        d = a.vr[v].deg;
-        double* rp = &a.vr[v].r;
-        const double rho = ld_agent(rp);
-        const double pold = a.p[v];
-        a.p[v] = pold + cs * rho;
-        const double nr = opt ? -0.0 : keep * rho;
-        st_agent(rp, nr);
-        ck[k] = (cn * rho) / (double)d;
-        rk[k] = a.off[v];
-        stay = !opt && nr >= eps * (double)d;
-        sup = pold == 0.0;
+      if (k < mine) {
+        dk[k] = a.vr[vk[k]].deg;
+        xk[k] = ld_agent(&a.vr[vk[k]].r);
+        pk[k] = a.p[vk[k]];
+        rk[k] = a.off[vk[k]];
       }
-      wave_append(stay, v, s_stay, &s_nstay);
-      wave_append(sup, v, s_sup, &s_nsup);
-      dk[k] = d;
-      dsum += d;
     }
+    long long dsum = 0;
+    unsigned sup = 0, stay = 0;  // bit k: entry k
+#pragma unroll
+    for (int k = 0; k < kItems; k++) {
+      ck[k] = 0.0;
+      if (k >= mine) continue;
+      const double rho = xk[k];
+      const double nr = opt ? -0.0 : keep * rho;
+      dsum += dk[k];
+      ck[k] = (cn * rho) / (double)dk[k];
+      if (!opt && nr >= eps * (double)dk[k]) stay |= 1u << k;
+      if (pk[k] == 0.0) sup |= 1u << k;
+      a.p[vk[k]] = pk[k] + cs * rho;
+      st_agent(&a.vr[vk[k]].r, nr);
+    }
+    if (!opt) wave_append_all<kItems>(stay, vk, s_stay, &s_nstay);
+    wave_append_all<kItems>(sup, vk, s_sup, &s_nsup);
     long long agg;
-    const long long ex = block_excl_scan<kBlock>(dsum, &agg, sh);
+    const long long ex = block_excl_scan<kSelfBlk>(dsum, &agg, sh);
     E = agg;
     const int nstay = s_nstay, nsup = s_nsup;
     local_append(a.support, cap, nullptr, s_sup, nsup, scnt, &c->fault);
@@ -536,16 +578,24 @@ __device__ void loop_rounds(const PlainArgs& a, int slot, int t, int nf) {
     scnt += nsup;
     nnext = nstay;
     if (E > kLoopEdges) {
-      // too large for one workgroup: entries in memory for the scatter launch
+      // too large for one workgroup: entries in memory for the scatter
+      // launch, at consecutive places (those of no edges left out: the
+      // threads before this one hold per entries each, or the frontier's
+      // rest), and the frontier in the same order
+      int32_t* const Fo = (t & 1) ? a.fbuf1 : a.fbuf0;
       long long s = ex;
+      const int full = nf - (per - 1) * kSelfBlk;  // threads with per entries
+      const int j = (int)threadIdx.x;
+      int i = j <= full ? j * per : full * per + (j - full) * (per - 1);
 #pragma unroll
-      for (int k = 0; k < kScanItems; k++) {
-        const int i = i0 + k;
-        if (i < nf) {
+      for (int k = 0; k < kItems; k++) {
+        if (k < mine) {
+          Fo[i] = vk[k];
           a.estart[i] = s;
           a.rowp[i] = rk[k];
           a.coef[i] = ck[k];
           mark_tiles(a.tile_start, a.tile_cap, s, dk[k], i, &c->fault);
+          i++;
         }
         s += dk[k];
       }
@@ -555,9 +605,9 @@ __device__ void loop_rounds(const PlainArgs& a, int slot, int t, int nf) {
     {
       long long s = ex;
 #pragma unroll
-      for (int k = 0; k < kScanItems; k++) {
-        const int i = i0 + k;
-        if (i < nf) {
+      for (int k = 0; k < kItems; k++) {
+        if (k < per) {
+          const int i = (int)threadIdx.x * per + k;
           s_est[i] = (int32_t)s;
           s_row[i] = rk[k];
           s_cf[i] = ck[k];
@@ -568,23 +618,39 @@ __device__ void loop_rounds(const PlainArgs& a, int slot, int t, int nf) {
     __syncthreads();
     if (threadIdx.x == 0) { s_nstay = 0; s_nsup = 0; }
     // edgeMap(G, Frontier, UpdateNgh), kLoopPass edges per pass
-    constexpr int kPer = kLoopPass / kBlock;
+    constexpr int kPer = kLoopPass / kSelfBlk;
     for (long long base = 0; base < E; base += kLoopPass) {
+      // the entry of every edge of the pass: one search per thread for the
+      // first of ept consecutive edges, the others follow from it; the edges
+      // are then taken kSelfBlk apart (see the scatter)
+      const int rest = (int)(E - base);
+      const int len = rest < kLoopPass ? rest : kLoopPass;
+      const int ept = (len + kSelfBlk - 1) / kSelfBlk;
+      {
+        const int r0 = (int)threadIdx.x * ept;
+        int lo = 0, hi = per * kSelfBlk - 1;
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (s_est[mid] <= (int)base + r0) lo = mid; else hi = mid - 1;
+        }
+        for (int k = 0; k < ept && r0 + k < len; k++) {
+          // (places of no edges are passed over)
+          while (lo + 1 < per * kSelfBlk && s_est[lo + 1] <= (int)base + r0 + k) lo++;
+          s_own[r0 + k] = (unsigned short)lo;
+        }
+      }
+      __syncthreads();
       int32_t w[kPer];
       double cf[kPer];
 #pragma unroll
       for (int k = 0; k < kPer; k++) {
-        const int rel = (int)base + k * kBlock + (int)threadIdx.x;
+        const int rel = k * kSelfBlk + (int)threadIdx.x;
         w[k] = -1;
         cf[k] = 0.0;
-        if (rel < E) {
-          int lo = 0, hi = nf - 1;
-          while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_est[mid] <= rel) lo = mid; else hi = mid - 1;
-          }
-          w[k] = a.nbr[s_row[lo] + (rel - s_est[lo])];
-          cf[k] = s_cf[lo];
+        if (rel < len) {
+          const int at = s_own[rel];
+          w[k] = a.nbr[s_row[at] + ((int)base + rel - s_est[at])];
+          cf[k] = s_cf[at];
         }
       }
       int32_t dw[kPer];
@@ -593,9 +659,16 @@ __device__ void loop_rounds(const PlainArgs& a, int slot, int t, int nf) {
       double old[kPer];
 #pragma unroll
       for (int k = 0; k < kPer; k++) old[k] = w[k] >= 0 ? unsafeAtomicAdd(&a.vr[w[k]].r, cf[k]) : 0.0;
+      unsigned cross = 0, touch = 0;  // bit k: edge k
 #pragma unroll
-      for (int k = 0; k < kPer; k++)
-        decide(w[k] >= 0, old[k], cf[k], eps * (double)dw[k], w[k], s_fn, &s_nfn, s_tv, &s_ntv);
+      for (int k = 0; k < kPer; k++) {
+        const double thr = eps * (double)dw[k];
+        if (w[k] < 0) continue;
+        if (old[k] < thr && old[k] + cf[k] >= thr) cross |= 1u << k;
+        if (__double_as_longlong(old[k]) == 0) touch |= 1u << k;
+      }
+      wave_append_all<kPer>(cross, w, s_fn, &s_nfn);
+      wave_append_all<kPer>(touch, w, s_tv, &s_ntv);
       __syncthreads();
       const int nfn = s_nfn, ntv = s_ntv;
       local_append(Fn, cap, s_F[cur ^ 1], s_fn, nfn, nnext, &c->fault);
@@ -632,8 +705,13 @@ __device__ void loop_rounds(const PlainArgs& a, int slot, int t, int nf) {
       c->etotal = E;
       c->ntiles = (int)((E + kEdgeTile - 1) / kEdgeTile);
     }
+    // The launch's other workgroups may only now read these words.  They leave
+    // where they see a frontier of at most a scan block, so no larger one is
+    // put there: the scatter launch does that (pend).
+    const bool large = !selfed && nf > kScanBlock;
     c->cnt[(t + 1) & 1] = nnext;  // stays of a round left to the scatter launch
-    c->cnt[t & 1] = nf;
+    c->cnt[t & 1] = large ? 0 : nf;
+    c->pend = large ? nf : 0;
     c->selfed = selfed ? t : -1;
     c->round = t;
     if (slot >= 0) a.work_log[2 * slot] = 1;
@@ -694,23 +772,24 @@ __device__ __forceinline__ int dense_count(const PlainArgs& a, int t) {
 }
 
 struct DenseCtl {
-  int32_t max_rounds, opt_rule, cd_dirty, hk_N;
-  double eps, cs, cn, keep, beta, hk_t, hk_A;
+  int32_t opt_rule, cd_dirty, hk_N;
+  double eps, cs, cn, keep, hk_t, hk_A;
 };
 
 // Round t in the dense form, k the workgroup's first block and b its record
 // (loaded ahead of the control block).
 template <int MODE>
 __device__ __forceinline__ void dense_round(const PlainArgs& a, int slot, DenseLds& L, int k,
-                                            DenseBlk b, int t, int nf, int selfed,
+                                            DenseBlk b, const CtlHead& h,
                                             const DenseCtl& q) {
   constexpr bool HK = MODE == kModeHK;
   Ctl* c = a.ctl;
+  const int t = h.round, nf = h.nf();
   const bool hk_last = HK && t + 1 == q.hk_N;
-  const bool fuse = HK ? !hk_last : t + 1 < q.max_rounds && q.beta >= 1.0;
+  const bool fuse = HK ? !hk_last : t + 1 < h.max_rounds && h.beta >= 1.0;
   // the list self step listed what stays, and beta carries what it did not
   // push: then only crossings join the list
-  const bool listed = !fuse && selfed == t;
+  const bool listed = !fuse && h.selfed == t;
   const bool wipe = (q.cd_dirty >> ((t + 1) & 1)) & 1;
   const bool opt = q.opt_rule != 0;
   const double cs = q.cs, cn = q.cn, keep = q.keep;
@@ -896,7 +975,7 @@ __device__ __forceinline__ void dense_round(const PlainArgs& a, int slot, DenseL
   }
   last = __shfl((int)last, 0) != 0;
   if (!last) return;
-  const bool own_self = selfed != t;  // the self step came with the previous dense round
+  const bool own_self = h.selfed != t;  // the self step came with the previous dense round
   const int counted = dense_count(a, t);
   if (tid != 0) return;
   const long long E = c->etotal;
@@ -965,17 +1044,16 @@ __device__ __forceinline__ void dense_body(const PlainArgs& a, int slot) {
   const int k = blockIdx.x;  // (the grid has at most one workgroup per block)
   // the block and all of the control block that a round needs, at once
   DenseBlk b = a.dblk[k];
-  DenseCtl q{c->max_rounds, c->opt_rule, c->cd_dirty, c->hk_N, c->eps,
-             c->cs,         c->cn,       c->keep,     c->beta, c->hk_t, c->hk_A};
+  DenseCtl q{c->opt_rule, c->cd_dirty, c->hk_N, c->eps,
+             c->cs, c->cn, c->keep, c->hk_t, c->hk_A};
   const CtlHead h = ctl_head(c);
   asm volatile("" : "+s"(b.row), "+s"(b.nrows), "+s"(b.lid), "+s"(b.len), "+s"(b.first));
-  asm volatile("" : "+s"(q.max_rounds), "+s"(q.opt_rule), "+s"(q.cd_dirty), "+s"(q.hk_N),
-               "+s"(q.eps), "+s"(q.cs), "+s"(q.cn), "+s"(q.keep), "+s"(q.beta), "+s"(q.hk_t),
+  asm volatile("" : "+s"(q.opt_rule), "+s"(q.cd_dirty), "+s"(q.hk_N),
+               "+s"(q.eps), "+s"(q.cs), "+s"(q.cn), "+s"(q.keep), "+s"(q.hk_t),
                "+s"(q.hk_A));
-  const int nf = (h.round & 1) ? h.cnt1 : h.cnt0;
-  if (h.status != ST_PUSH || nf <= 0) return;
+  if (h.status != ST_PUSH || h.nf() <= 0) return;
   if (h.dense == DN_READY)
-    dense_round<MODE>(a, slot, L, k, b, h.round, nf, h.selfed, q);
+    dense_round<MODE>(a, slot, L, k, b, h, q);
   else if (h.dense == DN_CONVERT)
     dense_convert(a, L);
 }
@@ -1015,41 +1093,41 @@ __device__ void dense_enter(const PlainArgs& a, int t, int nf, int* s_last) {
   }
 }
 
-__device__ __forceinline__ bool dense_wanted(const PlainArgs& a, const Ctl* c, int t) {
-  return dense_pays(a, c->etotal) && !((c->cd_dirty >> (t & 1)) & 1);
+__device__ __forceinline__ bool dense_wanted(const PlainArgs& a, const Ctl* c, int t,
+                                             long long E) {
+  return dense_pays(a, E) && !((c->cd_dirty >> (t & 1)) & 1);
 }
 
 // The self launch of PR-Nibble.  A frontier of at most one scan block goes
-// to loop_rounds, run by the workgroup that arrives last: the loop rewrites
-// the control block, and by then every other workgroup has read the state
-// it decided on (the same as the loop's) and left.
-__global__ __launch_bounds__(kBlock) void k_self(PlainArgs a, int slot) {
+// to loop_rounds, run by workgroup 0; the others leave.  (They used to be
+// counted out first, 256 additions to one word at ~10 ns each.)
+__global__ __launch_bounds__(kSelfBlk) void k_self(PlainArgs a, int slot) {
   Ctl* c = a.ctl;
-  const int32_t st = c->status;
-  const int32_t t = c->round;
-  int32_t nf = c->cnt[t & 1];
-  if (c->dense != DN_LIST) return;  // k_dense's
-  if ((int64_t)nf > a.n) nf = (int32_t)a.n;
-  if (st == ST_PUSH && nf > 0 && nf <= kScanBlock && t < c->max_rounds && c->beta >= 1.0) {
-    __shared__ int s_last;
-    if (last_block(&c->done[DONE_SELF], &s_last, false)) loop_rounds(a, slot, t, nf);
+  const CtlHead h = ctl_head(c);
+  if (h.dense != DN_LIST) return;  // k_dense's
+  const int32_t nf = h.nf();
+  if (h.status == ST_PUSH && nf > 0 && nf <= kScanBlock && h.round < h.max_rounds &&
+      h.beta >= 1.0) {
+    if (blockIdx.x == 0) loop_rounds(a, slot, h.round, nf);
     return;
   }
-  self_body<kModePR, false>(a, slot);
+  self_body<kModePR, false, kSelfBlk>(a, slot, h);
 }
 __global__ __launch_bounds__(kBlock) void k_hk_self(PlainArgs a) {
-  if (a.ctl->dense != DN_LIST) return;
-  self_body<kModeHK, false>(a, -1);
+  const CtlHead h = ctl_head(a.ctl);
+  if (h.dense == DN_LIST) self_body<kModeHK, false, kBlock>(a, -1, h);
 }
 __global__ __launch_bounds__(kBlock) void k_nb_self(PlainArgs a) {
-  self_body<kModeNB, false>(a, -1);
+  self_body<kModeNB, false, kBlock>(a, -1, ctl_head(a.ctl));
 }
 // The entries of a round that the dense form has handed back.
 __global__ __launch_bounds__(kBlock) void k_light_self(PlainArgs a, int slot) {
-  if (a.ctl->dense == DN_LIGHT) self_body<kModePR, true>(a, slot);
+  const CtlHead h = ctl_head(a.ctl);
+  if (h.dense == DN_LIGHT) self_body<kModePR, true, kBlock>(a, slot, h);
 }
 __global__ __launch_bounds__(kBlock) void k_hk_light_self(PlainArgs a) {
-  if (a.ctl->dense == DN_LIGHT) self_body<kModeHK, true>(a, -1);
+  const CtlHead h = ctl_head(a.ctl);
+  if (h.dense == DN_LIGHT) self_body<kModeHK, true, kBlock>(a, -1, h);
 }
 
 // ------------------------------------------------- binned edge scatter
@@ -1081,9 +1159,10 @@ struct ScatterLds {
   int32_t start[kEdgeTile + 1];
   int64_t row[kEdgeTile + 1];
   double coef[kEdgeTile + 1];
+  __align__(8) unsigned short own[kEdgeTile];
   int32_t fn[kEdgeTile];
   int32_t tv[kEdgeTile];
-  int nfn, ntv, base, last;
+  int nfn, ntv, base[2], last;
 };
 struct BinSortLds {
   int32_t start[kEdgeTile + 1];
@@ -1232,8 +1311,11 @@ __device__ void bin_sort_chunks(const PlainArgs& a, int nf, BinSortLds& L) {
 // otherwise), on which its threshold crossing and first touch are decided.
 __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
   Ctl* c = a.ctl;
-  int t, nf;
-  if (!push_active(c, a.n, &t, &nf)) return;
+  if (c->status != ST_PUSH) return;
+  const int t = c->round;
+  int nf = c->cnt[t & 1];
+  if (nf <= 0) return;
+  if ((int64_t)nf > a.n) nf = (int)a.n;
   if (t >= c->max_rounds || c->selfed != t || c->dense != DN_LIST) return;
   const long long E = c->etotal;
   if (!bin_round(a, E)) return;
@@ -1460,19 +1542,25 @@ __device__ __forceinline__ void scatter_body(const PlainArgs& a, int slot, Scatt
   constexpr bool HK = MODE == kModeHK;
   constexpr bool LEVELS = MODE != kModePR;
   Ctl* c = a.ctl;
+  CtlEdges q;
+  const CtlHead h = ctl_head(c, &q);
   int t, nf;
-  if (!push_active(c, a.n, &t, &nf)) return;
-  if (HK ? t >= c->hk_N : t >= c->max_rounds) return;
-  if (c->selfed != t) return;  // no entries built for this round (a self loop stopped before it)
-  if (MODE != kModeNB && c->dense != DN_LIST) return;  // k_dense's
-  if (MODE != kModeNB && dense_wanted(a, c, t)) {
+  if (MODE == kModePR && blockIdx.x == 0 && threadIdx.x == 0 && h.nf() == 0 && c->pend > 0) {
+    c->cnt[h.round & 1] = c->pend;  // (no entries yet: every workgroup leaves below)
+    c->pend = 0;
+  }
+  if (!push_active(h, a.n, &t, &nf)) return;
+  if (h.selfed != t) return;  // no entries built for this round (a self loop stopped before it)
+  if (MODE != kModeNB && h.dense != DN_LIST) return;  // k_dense's
+  if (t >= (HK ? c->hk_N : h.max_rounds)) return;
+  if (MODE != kModeNB && dense_wanted(a, c, t, q.etotal)) {
     dense_enter<MODE>(a, t, nf, &sm.at.last);
     return;
   }
   // which launch pairs of a first chunk carry rounds that could bin (the
   // host queues k_bin_apply behind those pairs only); without k_bin_apply
   // behind it such a round takes the atomic form
-  if (MODE == kModePR && bin_round(a, c->etotal)) {
+  if (MODE == kModePR && bin_round(a, q.etotal)) {
     if (pair >= 0 && blockIdx.x == 0 && threadIdx.x == 0) c->bin_pairs |= 1u << pair;
     if (apply) {
       bin_sort_chunks(a, nf, sm.bs);  // pass A; k_bin_apply adds and closes the round
@@ -1486,12 +1574,12 @@ __device__ __forceinline__ void scatter_body(const PlainArgs& a, int slot, Scatt
   int32_t* const s_tv = sm.at.tv;
   int& s_nfn = sm.at.nfn;
   int& s_ntv = sm.at.ntv;
-  int& s_base = sm.at.base;
+  int* const s_base = sm.at.base;
   int& s_last = sm.at.last;
-  const int ntiles = (int64_t)c->ntiles > a.tile_cap ? (int)a.tile_cap : c->ntiles;
-  const long long E = c->etotal;
+  const int ntiles = (int64_t)q.ntiles > a.tile_cap ? (int)a.tile_cap : q.ntiles;
+  const long long E = q.etotal;
   const bool hk_last = HK && t + 1 == c->hk_N;
-  const double eps = HK ? c->hk_A : c->eps;                   // threshold numerator factor
+  const double eps = HK ? c->hk_A : q.eps;                    // threshold numerator factor
   const int32_t* Fc = (t & 1) ? a.fbuf1 : a.fbuf0;            // this round's frontier
   const double den = HK && !hk_last ? a.hk_B[t + 1] : 1.0;    // threshold denominator
   int32_t* Fn = (t & 1) ? a.fbuf0 : a.fbuf1;
@@ -1526,6 +1614,31 @@ __device__ __forceinline__ void scatter_body(const PlainArgs& a, int slot, Scatt
       s_coef[j] = a.coef[i0 + j];
     }
     __syncthreads();
+    // The entry of every edge: each thread searches for the first of four
+    // consecutive edges and walks on from it.  The edges are then taken
+    // kBlock apart, so that a wave's 64 neighbours are consecutive (their
+    // loads, and the atomics on records of one line, go out together).
+    const int len = (int)(e1 - e0);
+    {
+      const int r0 = (int)threadIdx.x * kEdgesPerThread;
+      int lo = 0, hi = cnt - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (s_start[mid] <= r0) lo = mid; else hi = mid - 1;
+      }
+      ushort4 at;
+      at.x = lo;
+      // (every entry has an edge, so the next edge is at most one entry on)
+      if (lo + 1 < cnt && s_start[lo + 1] <= r0 + 1) lo++;
+      at.y = lo;
+      if (lo + 1 < cnt && s_start[lo + 1] <= r0 + 2) lo++;
+      at.z = lo;
+      if (lo + 1 < cnt && s_start[lo + 1] <= r0 + 3) lo++;
+      at.w = lo;
+      static_assert(kEdgesPerThread == 4 && kEdgeTile < 65536, "four 16-bit entries");
+      reinterpret_cast<ushort4*>(sm.at.own)[threadIdx.x] = at;
+    }
+    __syncthreads();
     // Four independent edges per thread: all neighbour loads, then all
     // degree loads and atomics, then the decisions, so latencies overlap.
     int32_t w[kEdgesPerThread];
@@ -1533,17 +1646,9 @@ __device__ __forceinline__ void scatter_body(const PlainArgs& a, int slot, Scatt
 #pragma unroll
     for (int k = 0; k < kEdgesPerThread; k++) {
       const int rel = k * kBlock + (int)threadIdx.x;
-      w[k] = -1;
-      cf[k] = 0.0;
-      if (e0 + rel < e1) {
-        int lo = 0, hi = cnt - 1;
-        while (lo < hi) {
-          int mid = (lo + hi + 1) >> 1;
-          if (s_start[mid] <= rel) lo = mid; else hi = mid - 1;
-        }
-        w[k] = a.nbr[s_row[lo] + (rel - s_start[lo])];
-        cf[k] = s_coef[lo];
-      }
+      const int at = sm.at.own[rel];
+      w[k] = rel < len ? a.nbr[s_row[at] + (rel - s_start[at])] : -1;
+      cf[k] = s_coef[at];
     }
     int32_t dw[kEdgesPerThread];
 #pragma unroll
@@ -1555,16 +1660,17 @@ __device__ __forceinline__ void scatter_body(const PlainArgs& a, int slot, Scatt
       if (w[k] >= 0) dst = !LEVELS ? &a.vr[w[k]].r : hk_last ? &a.p[w[k]] : hk_res(a, t + 1, w[k]);
       old[k] = dst ? unsafeAtomicAdd(dst, cf[k]) : 0.0;
     }
+    unsigned cross = 0, touch = 0;  // bit k: edge k
 #pragma unroll
     for (int k = 0; k < kEdgesPerThread; k++) {
-      if (hk_last)
-        wave_append(w[k] >= 0 && __double_as_longlong(old[k]) == 0, w[k], s_tv, &s_ntv);
-      else
-        decide(w[k] >= 0, old[k], cf[k], (eps * (double)dw[k]) / den, w[k], s_fn, &s_nfn, s_tv,
-               &s_ntv);
+      const double thr = (eps * (double)dw[k]) / den;
+      if (w[k] < 0) continue;
+      if (!hk_last && old[k] < thr && old[k] + cf[k] >= thr) cross |= 1u << k;
+      if (__double_as_longlong(old[k]) == 0) touch |= 1u << k;
     }
-    if (!hk_last) block_flush(cntn, Fn, a.n, s_fn, &s_nfn, &s_base, &c->fault);
-    block_flush(tv_cnt, tv_list, a.n, s_tv, &s_ntv, &s_base, &c->fault);
+    if (!hk_last) wave_append_all<kEdgesPerThread>(cross, w, s_fn, &s_nfn);
+    wave_append_all<kEdgesPerThread>(touch, w, s_tv, &s_ntv);
+    block_flush2(cntn, Fn, s_fn, &s_nfn, tv_cnt, tv_list, s_tv, &s_ntv, a.n, s_base, &c->fault);
     if (MODE == kModeNB) {
       // the kept halves of the entries whose first edge is in this tile
       for (int jj = threadIdx.x; jj < cnt; jj += kBlock) {
@@ -1576,8 +1682,7 @@ __device__ __forceinline__ void scatter_body(const PlainArgs& a, int slot, Scatt
         const double o = unsafeAtomicAdd(hk_res(a, t + 1, v), h);
         decide(true, o, h, eps * (double)a.vr[v].deg, v, s_fn, &s_nfn, s_tv, &s_ntv);
       }
-      block_flush(cntn, Fn, a.n, s_fn, &s_nfn, &s_base, &c->fault);
-      block_flush(tv_cnt, tv_list, a.n, s_tv, &s_ntv, &s_base, &c->fault);
+      block_flush2(cntn, Fn, s_fn, &s_nfn, tv_cnt, tv_list, s_tv, &s_ntv, a.n, s_base, &c->fault);
     }
   }
   if (last_block_of(&c->done[DONE_SCATTER], &s_last, false, (unsigned)busy)) {
@@ -1759,7 +1864,7 @@ __global__ __launch_bounds__(kBlock) void k_hk_clear(PlainArgs a) {
 __global__ __launch_bounds__(kBlock) void k_beta_keys(PlainArgs a) {
   Ctl* c = a.ctl;
   int t, nf;
-  if (!push_active(c, a.n, &t, &nf) || t >= c->max_rounds) {
+  if (!push_active(ctl_head(c), a.n, &t, &nf) || t >= c->max_rounds) {
     if (blockIdx.x == 0 && threadIdx.x == 0) { c->N = 0; c->beta_nf = 0; }
     return;
   }
@@ -1825,8 +1930,8 @@ __global__ __launch_bounds__(kBlock) void k_beta_carry(PlainArgs a) {
 
 // The sweep may start once the frontier is empty (or the watchdog fired).
 __device__ __forceinline__ bool sweep_ready(const Ctl* c) {
-  if (c->status == ST_LIMIT) return true;
-  return c->status == ST_PUSH && c->cnt[c->round & 1] == 0;
+  const CtlHead h = ctl_head(c);
+  return h.status == ST_LIMIT || (h.status == ST_PUSH && h.nf() == 0);
 }
 
 // Sort keys: non-increasing p/d is ascending order of the bit-inverted IEEE
@@ -1836,20 +1941,16 @@ __device__ __forceinline__ bool sweep_ready(const Ctl* c) {
 // a sweep queued with a larger bound.
 __global__ __launch_bounds__(kBlock) void k_sweep_keys(PlainArgs a, long long bound) {
   Ctl* c = a.ctl;
-  if (!sweep_ready(c) || (long long)c->support_cnt > bound) return;
+  const int scnt = c->support_cnt;
+  if (!sweep_ready(c) || (long long)scnt > bound) return;
   __shared__ int s_last;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    SweepOut o;
-    o.ids = a.sid;
-    o.p = a.sp;
-    o.rid = a.rid;
-    o.rval = a.rval;
-    o.rcap = a.n;
-    o.pad = 0;
-    c->out = o;
-  }
-  const int N = (int64_t)c->support_cnt > a.n ? (int)a.n : c->support_cnt;
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < N; i += gridDim.x * kBlock) {
+  const int N = (int64_t)scnt > a.n ? (int)a.n : scnt;
+  const int dirty = c->cd_dirty;
+  // the workgroups that have keys to form (all, to clear the coefficients)
+  const int want = (N + kBlock - 1) / kBlock;
+  const int busy = dirty || want > (int)gridDim.x ? (int)gridDim.x : want > 1 ? want : 1;
+  if ((int)blockIdx.x >= busy) return;
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < N; i += busy * kBlock) {
     int32_t v = a.support[i];
     double ratio = a.p[v] / (double)a.vr[v].deg;
     SortElem e;
@@ -1859,12 +1960,11 @@ __global__ __launch_bounds__(kBlock) void k_sweep_keys(PlainArgs a, long long bo
     a.sbuf[0][i] = e;
   }
   // a push that ended in the dense form leaves its last coefficients
-  const int dirty = c->cd_dirty;
   for (int k = 0; k < 2; k++)
     if ((dirty >> k) & 1)
       for (int64_t i = blockIdx.x * kBlock + threadIdx.x; i < a.n; i += gridDim.x * kBlock)
         a.cd[k][i] = 0.0;
-  if (last_block(&c->done[DONE_KEYS], &s_last, false)) {
+  if (last_block_of(&c->done[DONE_KEYS], &s_last, false, (unsigned)busy)) {
     if (threadIdx.x == 0) {
       c->N = N;
       c->sort_flip = 0;
@@ -1884,18 +1984,20 @@ __global__ __launch_bounds__(kBlock) void k_vol_scan(PlainArgs a) {
   const int N = c->N;
   if (N <= 0) return;
   const SortElem* el = a.sbuf[c->sort_flip & 1];
-  int32_t* const out_ids = c->out.ids;
-  double* const out_p = c->out.p;
+  int32_t* const out_ids = a.sid;
+  double* const out_p = a.sp;
   __shared__ long long sh[kBlock / 64 + 1];
   __shared__ long long s_excl;
   __shared__ int s_tk[2];
-  ScanSite* site = &c->scan[SCAN_VOL];
-  scan_clear_prev(site, a.desc[SCAN_VOL], a.desc_cap);
-  unsigned long long* desc = a.desc[SCAN_VOL] + (size_t)site->parity * a.desc_cap;
   const int nblk = (N + kScanBlock - 1) / kScanBlock;
-  for (;;) {
+  const bool fixed = scan_fixed(nblk);
+  if (fixed && (int)blockIdx.x >= nblk) return;
+  ScanSite* site = &c->scan[SCAN_VOL];
+  scan_clear_prev(site, a.desc[SCAN_VOL], a.desc_cap, fixed ? nblk : 0);
+  unsigned long long* desc = a.desc[SCAN_VOL] + (size_t)site->parity * a.desc_cap;
+  for (int pass = 0;; pass++) {
     bool last;
-    int b = scan_ticket(site, nblk, s_tk, &last);
+    const int b = fixed ? (pass == 0 ? (int)blockIdx.x : nblk) : scan_ticket(site, nblk, s_tk, &last);
     if (b >= nblk) break;
     // kScanItems consecutive positions per thread (see k_self)
     const int i0 = b * kScanBlock + (int)threadIdx.x * kScanItems;
@@ -1940,6 +2042,7 @@ __global__ __launch_bounds__(kBlock) void k_vol_scan(PlainArgs a) {
     }
     __syncthreads();
   }
+  if (fixed && threadIdx.x == 0) (void)scan_retire(site, nblk);
 }
 
 // For every support edge (v_k, w): count w with 1 <= rank[w] < k.  Then
@@ -1953,7 +2056,7 @@ __global__ __launch_bounds__(kBlock) void k_cut_count(PlainArgs a) {
   __shared__ int32_t s_start[kEdgeTile + 1];
   __shared__ int64_t s_row[kEdgeTile + 1];
   __shared__ int32_t s_cnt[kEdgeTile + 1];
-  const int32_t* const sid = c->out.ids;
+  const int32_t* const sid = a.sid;
   const int ntiles = (int64_t)c->ntiles > a.tile_cap ? (int)a.tile_cap : c->ntiles;
   const long long E = c->etotal;
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
@@ -2026,27 +2129,55 @@ __device__ void block_argmin(long long* s_bc, long long* s_bd, long long* s_bk) 
   }
 }
 
+// Reduce the per-block candidates of k_cut_scan (one workgroup; written by
+// the others of the launch: device-scope reads).
+__device__ void cut_final(const PlainArgs& a, Ctl* c, int N, long long* s_bc, long long* s_bd,
+                          long long* s_bk) {
+  const int nblk = (N + kScanBlock - 1) / kScanBlock;
+  long long mc = -1, md = 1, mk = 0;
+  for (int j = threadIdx.x; j < nblk; j += kBlock) {
+    const long long jc = ld_agent(&a.bbest[3 * j]), jd = ld_agent(&a.bbest[3 * j + 1]),
+                    jk = ld_agent(&a.bbest[3 * j + 2]);
+    if (cand_better(jc, jd, jk, mc, md, mk)) { mc = jc; md = jd; mk = jk; }
+  }
+  s_bc[threadIdx.x] = mc; s_bd[threadIdx.x] = md; s_bk[threadIdx.x] = mk;
+  __syncthreads();
+  block_argmin(s_bc, s_bd, s_bk);
+  if (threadIdx.x == 0) {
+    long long bk = s_bk[0];
+    c->kstar = bk > 0 ? bk : 0;
+    c->best_cut = bk > 0 ? s_bc[0] : 0;
+    c->best_den = bk > 0 ? s_bd[0] : 0;
+    c->best_vol = bk > 0 ? a.svol[bk - 1] : 0;
+    c->phi = bk > 0 ? (double)s_bc[0] / (double)s_bd[0] : 0.0;
+  }
+}
+
 // Inclusive prefix of the boundary deltas gives |boundary(S_k)|; with vol_k
 // the conductance of every prefix follows.  Each block publishes its best
 // prefix (smallest cut/den by exact comparison, first k on ties, den = 0
-// excluded); k_sweep_finish reduces the candidates.
+// excluded), and resets p and the rank of its vertices, which no later step
+// reads (r was reset by the block sort's side job).  The last workgroup
+// reduces the candidates and marks the sweep finished.
 __global__ __launch_bounds__(kBlock) void k_cut_scan(PlainArgs a) {
   Ctl* c = a.ctl;
   if (c->status != ST_SWEEPING) return;
   const int N = c->N;
-  if (N <= 0) return;
   __shared__ long long sh[kBlock / 64 + 1];
   __shared__ long long s_excl;
   __shared__ int s_tk[2];
+  __shared__ int s_last;
   __shared__ long long s_bc[kBlock], s_bd[kBlock], s_bk[kBlock];
-  ScanSite* site = &c->scan[SCAN_CUT];
-  scan_clear_prev(site, a.desc[SCAN_CUT], a.desc_cap);
-  unsigned long long* desc = a.desc[SCAN_CUT] + (size_t)site->parity * a.desc_cap;
   const int nblk = (N + kScanBlock - 1) / kScanBlock;
+  const bool fixed = scan_fixed(nblk);
+  if (fixed && (int)blockIdx.x >= (nblk > 1 ? nblk : 1)) return;
+  ScanSite* site = &c->scan[SCAN_CUT];
+  scan_clear_prev(site, a.desc[SCAN_CUT], a.desc_cap, fixed && nblk > 0 ? nblk : 0);
+  unsigned long long* desc = a.desc[SCAN_CUT] + (size_t)site->parity * a.desc_cap;
   const long long vt = c->vol_total;
-  for (;;) {
+  for (int pass = 0; N > 0; pass++) {
     bool last;
-    int b = scan_ticket(site, nblk, s_tk, &last);
+    const int b = fixed ? (pass == 0 ? (int)blockIdx.x : nblk) : scan_ticket(site, nblk, s_tk, &last);
     if (b >= nblk) break;
     // kScanItems consecutive positions per thread (see k_self)
     const int i0 = b * kScanBlock + (int)threadIdx.x * kScanItems;
@@ -2057,6 +2188,15 @@ __global__ __launch_bounds__(kBlock) void k_cut_scan(PlainArgs a) {
       const int i = i0 + k;
       dk[k] = i < N ? (long long)a.sdeg[i] - 2ll * a.scnt[i] : 0;
       dsum += dk[k];
+    }
+#pragma unroll
+    for (int k = 0; k < kScanItems; k++) {
+      const int i = b * kScanBlock + k * kBlock + (int)threadIdx.x;
+      if (i < N) {
+        const int32_t v = a.sid[i];
+        a.vr[v].rank = 0;
+        a.p[v] = 0.0;
+      }
     }
     long long agg;
     const long long ex = block_excl_scan<kBlock>(dsum, &agg, sh);
@@ -2081,51 +2221,23 @@ __global__ __launch_bounds__(kBlock) void k_cut_scan(PlainArgs a) {
     __syncthreads();
     block_argmin(s_bc, s_bd, s_bk);
     if (threadIdx.x == 0) {
-      a.bbest[3 * b] = s_bc[0];
-      a.bbest[3 * b + 1] = s_bd[0];
-      a.bbest[3 * b + 2] = s_bk[0];
+      // (exchanges that have returned are in place for the last workgroup)
+      unsigned long long* bb = reinterpret_cast<unsigned long long*>(a.bbest) + 3 * (size_t)b;
+      const unsigned long long o0 = atomicExch(&bb[0], (unsigned long long)s_bc[0]);
+      const unsigned long long o1 = atomicExch(&bb[1], (unsigned long long)s_bd[0]);
+      const unsigned long long o2 = atomicExch(&bb[2], (unsigned long long)s_bk[0]);
+      asm volatile("" : : "v"(o0), "v"(o1), "v"(o2) : "memory");
     }
     __syncthreads();
   }
-  // p and the sweep rank of every support vertex are read by no later
-  // kernel (k_vol_scan read p, k_cut_count the rank): reset them
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < N; i += gridDim.x * kBlock) {
-    const int32_t v = a.support[i];
-    a.vr[v].rank = 0;
-    a.p[v] = 0.0;
+  if (fixed) {
+    if (threadIdx.x == 0) s_last = nblk < 1 || scan_retire(site, nblk);
+    __syncthreads();
+    if (!s_last) return;
+  } else if (!last_block(&c->done[DONE_FINISH], &s_last, false)) {
+    return;
   }
-}
-
-// Reduce the per-block candidates of k_cut_scan (one workgroup).
-__device__ void cut_final(const PlainArgs& a, Ctl* c, int N) {
-  const int nblk = (N + kScanBlock - 1) / kScanBlock;
-  __shared__ long long s_bc[kBlock], s_bd[kBlock], s_bk[kBlock];
-  long long mc = -1, md = 1, mk = 0;
-  for (int j = threadIdx.x; j < nblk; j += kBlock) {
-    long long jc = a.bbest[3 * j], jd = a.bbest[3 * j + 1], jk = a.bbest[3 * j + 2];
-    if (cand_better(jc, jd, jk, mc, md, mk)) { mc = jc; md = jd; mk = jk; }
-  }
-  s_bc[threadIdx.x] = mc; s_bd[threadIdx.x] = md; s_bk[threadIdx.x] = mk;
-  __syncthreads();
-  block_argmin(s_bc, s_bd, s_bk);
-  if (threadIdx.x == 0) {
-    long long bk = s_bk[0];
-    c->kstar = bk > 0 ? bk : 0;
-    c->best_cut = bk > 0 ? s_bc[0] : 0;
-    c->best_den = bk > 0 ? s_bd[0] : 0;
-    c->best_vol = bk > 0 ? a.svol[bk - 1] : 0;
-    c->phi = bk > 0 ? (double)s_bc[0] / (double)s_bd[0] : 0.0;
-  }
-}
-
-// One workgroup reduces k_cut_scan's per-block candidates to the best
-// prefix and marks the sweep finished.  The query's dense state is reset by
-// then: r of every touched vertex by the block sort's side job, p and the
-// sweep rank of every support vertex by k_cut_scan.
-__global__ __launch_bounds__(kBlock) void k_sweep_finish(PlainArgs a) {
-  Ctl* c = a.ctl;
-  if (c->status != ST_SWEEPING) return;
-  if (c->N > 0) cut_final(a, c, c->N);
+  if (N > 0) cut_final(a, c, N, s_bc, s_bd, s_bk);
   if (threadIdx.x == 0) {
     c->t_end = (long long)wall_clock64();
     c->status = ST_SWEPT;
@@ -2172,7 +2284,6 @@ hipError_t launch_beta_pre(hipStream_t s, const PlainArgs& a, int grid, int64_t 
   sa.buf[1] = a.sbuf[1];
   sa.count = &a.ctl->N;
   sa.flip = &a.ctl->sort_flip;
-  sa.done = &a.ctl->done[DONE_SORT];
   sa.active = nullptr;
   sa.active_value = 0;
   sa.rank = nullptr;
@@ -2262,9 +2373,9 @@ hipError_t launch_self(hipStream_t s, const PlainArgs& a, int grid, hipEvent_t t
                        int slot) {
   if (slot >= kMaxChunk) return hipErrorInvalidValue;
   if (t0)
-    hipExtLaunchKernelGGL(k_self, dim3(grid), dim3(kBlock), 0, s, t0, t1, 0, a, slot);
+    hipExtLaunchKernelGGL(k_self, dim3(grid), dim3(kSelfBlk), 0, s, t0, t1, 0, a, slot);
   else
-    hipLaunchKernelGGL(k_self, dim3(grid), dim3(kBlock), 0, s, a, slot);
+    hipLaunchKernelGGL(k_self, dim3(grid), dim3(kSelfBlk), 0, s, a, slot);
   return hipGetLastError();
 }
 
@@ -2343,7 +2454,6 @@ hipError_t launch_sweep(hipStream_t s, const PlainArgs& a, int grid, int64_t max
   sa.buf[1] = a.sbuf[1];
   sa.count = &a.ctl->N;
   sa.flip = &a.ctl->sort_flip;
-  sa.done = &a.ctl->done[DONE_SORT];
   sa.active = &a.ctl->status;
   sa.active_value = ST_SWEEPING;
   // the volume prefix is written only after the sort: its words hold the
@@ -2369,7 +2479,6 @@ hipError_t launch_sweep(hipStream_t s, const PlainArgs& a, int grid, int64_t max
   // each workgroup to about one
   hipLaunchKernelGGL(k_cut_count, dim3(4 * grid), dim3(kBlock), 0, s, a);
   hipLaunchKernelGGL(k_cut_scan, dim3(grid), dim3(kBlock), 0, s, a);
-  hipLaunchKernelGGL(k_sweep_finish, dim3(1), dim3(kBlock), 0, s, a);
   return hipGetLastError();
 }
 

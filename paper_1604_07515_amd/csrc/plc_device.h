@@ -42,17 +42,6 @@ enum : int32_t {
   DONE_DENSE = 6, NUM_DONE = 8
 };
 
-// Where the running sweep writes its results (the library's own buffers,
-// set by k_sweep_keys; the host copies them into the query's result block).
-struct SweepOut {
-  int32_t* ids;     // [N] support in sweep order
-  double* p;        // [N] p in sweep order
-  int32_t* rid;     // [rcap] ids of the nonzeros of r
-  double* rval;     // [rcap] their values
-  long long rcap;   // capacity of rid and rval
-  long long pad;
-};
-
 // Device control block of one plain-path query.  Written by kernels only,
 // except at query start (k_query_init) and read back by the host.
 struct __align__(64) Ctl {
@@ -75,7 +64,10 @@ struct __align__(64) Ctl {
   double beta;            // fraction of the active set pushed per round (end of Sec. 3.3)
   double hk_t, hk_A;      // HK-PR (Sec. 3.4): t, e^-t * eps,
   int32_t hk_N, seed;     // and the Taylor degree
-  long long pad0;
+  // a self launch's loop that left a frontier of more than a scan block: its
+  // size, while cnt of the round is still 0 (see loop_rounds)
+  int32_t pend;
+  int32_t pad0;
   long long pushes, edges;
   int32_t support_cnt;    // |support list|
   int32_t touched_cnt;    // |touched list|
@@ -92,7 +84,6 @@ struct __align__(64) Ctl {
   long long best_cut, best_vol, best_den;
   long long kstar;
   double phi;
-  SweepOut out;           // result destinations of the running sweep
   // lengths of HK-PR's three rotating per-level touched lists (level k uses
   // list k % 3; Nibble uses the same lists and arrays for its vectors)
   int32_t hk_tlc[3];
@@ -220,6 +211,7 @@ struct PlainArgs {
 
 // Launch configuration.
 constexpr int kBlock = 256;                      // threads per workgroup
+constexpr int kSelfBlk = 512;                    // threads per workgroup of k_self
 constexpr int kScanItems = 4;                    // items per thread in scan-type kernels
 constexpr int kScanBlock = kBlock * kScanItems;  // items per scan block
 constexpr int kEdgeTile = 1024;                  // edges per scatter / cut tile

@@ -13,10 +13,9 @@ struct __align__(16) SortElem {
 };
 
 struct SortArgs {
-  SortElem* buf[2];        // ping-pong buffers; *flip says which holds the data
+  SortElem* buf[2];        // ping-pong buffers; the elements come in buf[0]
   const int32_t* count;    // element count (device)
-  int32_t* flip;           // 0 or 1 (device); flipped by every merge launch that runs
-  unsigned* done;          // last-workgroup counter (device, zero between launches)
+  int32_t* flip;           // out (device): which buffer holds the sorted elements
   const int32_t* active;   // optional gate: the sort runs only if *active == active_value
   int32_t active_value;
   // Optional: one word per element for the small-count path (the per-element

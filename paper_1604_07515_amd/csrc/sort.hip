@@ -145,11 +145,19 @@ __device__ void side_job(const SortArgs& s, int ntiles) {
   }
 }
 
-__global__ __launch_bounds__(kBSBlk) void k_block_sort(SortArgs s) {
-  if (!sort_enabled(s)) return;
+// rank: one rank merge follows instead of merge passes.  Where the sorted
+// elements end up follows from the count, so nothing of the sort counts its
+// workgroups (512 additions to one word outlast the merging of 30,000
+// elements).
+__global__ __launch_bounds__(kBSBlk) void k_block_sort(SortArgs s, bool rank) {
   const int N = *s.count;
-  const int flip = *s.flip;
-  SortElem* buf = s.buf[flip];
+  if (!sort_enabled(s)) return;
+  SortElem* buf = s.buf[0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    int flip = 0;
+    for (long long L = kTileB; L < N; L <<= 1) flip = rank ? 1 : flip ^ 1;
+    *s.flip = flip;
+  }
   __shared__ SortElem sh[kTileB + kTileB / kBT];
   const int ntiles = (N + kTileB - 1) / kTileB;
   const int t = threadIdx.x;
@@ -251,15 +259,13 @@ static_assert(kRankMaxCount % kTileB == 0, "whole block-sort tiles");
 // writes the element out.  Tiles beyond tiles_max (a count above the bound
 // the launch was sized for) are taken in further turns.
 __global__ __launch_bounds__(kRankBlk) void k_rank_merge(SortArgs s, int tiles_max, int per) {
-  if (!sort_enabled(s)) return;
   const int N = *s.count;
+  if (!sort_enabled(s)) return;
   const int T = (N + kTileB - 1) / kTileB;
   if (T <= 1) return;
-  const int flip = *s.flip;
-  const SortElem* src = s.buf[flip];
-  SortElem* dst = s.buf[flip ^ 1];
+  const SortElem* src = s.buf[0];
+  SortElem* dst = s.buf[1];
   __shared__ SortElem sh[kTileB];
-  __shared__ int s_last;
   const int g = blockIdx.x % per;
   for (int j = blockIdx.x / per; j < T; j += tiles_max) {
     const int base = j * kTileB;
@@ -286,9 +292,6 @@ __global__ __launch_bounds__(kRankBlk) void k_rank_merge(SortArgs s, int tiles_m
       const unsigned long long old = atomicAdd(&s.rank[k], (1ull << 32) | (unsigned long long)lo);
       if ((int)(old >> 32) == T - 2) dst[(long long)(old & 0xffffffffull) + lo] = e;
     }
-  }
-  if (last_block(s.done, &s_last, false)) {
-    if (threadIdx.x == 0) *s.flip = flip ^ 1;
   }
 }
 
@@ -348,16 +351,14 @@ __device__ __forceinline__ SortElem staged_head(const SortElem* sm, int r0, int 
   return elem_sel(i < len, sm[li], kMaxElem);
 }
 
-__global__ __launch_bounds__(kSortBlk) void k_merge_pass(SortArgs s, int L) {
-  if (!sort_enabled(s)) return;
+__global__ __launch_bounds__(kSortBlk) void k_merge_pass(SortArgs s, int L, int from) {
   const int N = *s.count;
+  if (!sort_enabled(s)) return;
   if (L >= N) return;
-  const int flip = *s.flip;
-  const SortElem* src = s.buf[flip];
-  SortElem* dst = s.buf[flip ^ 1];
+  const SortElem* src = s.buf[from];
+  SortElem* dst = s.buf[from ^ 1];
   __shared__ SortElem sm[kTileS];
   __shared__ int s_cnt[4], s_done[2], s_res[2];
-  __shared__ int s_last;
   const int ntiles = (N + kTileS - 1) / kTileS;
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const long long o0 = (long long)tile * kTileS;
@@ -401,17 +402,15 @@ __global__ __launch_bounds__(kSortBlk) void k_merge_pass(SortArgs s, int L) {
     }
     __syncthreads();
   }
-  if (last_block(s.done, &s_last, false)) {
-    if (threadIdx.x == 0) *s.flip = flip ^ 1;
-  }
 }
 
 hipError_t launch_sort(hipStream_t st, const SortArgs& s, int64_t max_count, int grid) {
   // a side job takes the workgroups without a tile: two per CU fit the
   // tile's LDS, so up to that many keep the gather from outlasting the sort
   const int bs_grid = s.side_ids != nullptr && grid < kSideGrid ? kSideGrid : grid;
-  hipLaunchKernelGGL(k_block_sort, dim3(bs_grid), dim3(kBSBlk), 0, st, s);
-  if (s.rank != nullptr && max_count <= kRankMaxCount) {
+  const bool rank = s.rank != nullptr && max_count <= kRankMaxCount;
+  hipLaunchKernelGGL(k_block_sort, dim3(bs_grid), dim3(kBSBlk), 0, st, s, rank);
+  if (rank) {
     const int tiles = (int)((max_count + kTileB - 1) / kTileB);
     if (tiles > 1) {
       const int per = kRankGrid / tiles;
@@ -419,8 +418,9 @@ hipError_t launch_sort(hipStream_t st, const SortArgs& s, int64_t max_count, int
     }
     return hipGetLastError();
   }
-  for (int64_t L = kTileB; L < max_count; L <<= 1)
-    hipLaunchKernelGGL(k_merge_pass, dim3(grid), dim3(kSortBlk), 0, st, s, (int)L);
+  int from = 0;
+  for (int64_t L = kTileB; L < max_count; L <<= 1, from ^= 1)
+    hipLaunchKernelGGL(k_merge_pass, dim3(grid), dim3(kSortBlk), 0, st, s, (int)L, from);
   return hipGetLastError();
 }
 
