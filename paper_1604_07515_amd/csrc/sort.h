@@ -22,6 +22,7 @@ struct SortArgs {
   // rank accumulators of the one-launch merge); null selects merge passes
   // at every count.
   unsigned long long* rank;
+  bool segments = false;   // whether elements of more than one segment may meet
   // Optional side job of the block-sort launch, taken first by its
   // workgroups that hold no tile: for each id in side_ids[0 .. *side_count)
   // (at most side_out_cap of them), the double at side_val[id * side_stride]

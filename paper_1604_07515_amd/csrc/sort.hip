@@ -18,10 +18,11 @@
 // so the whole sequence is queued without a host round trip.
 //
 // Small counts (a bound of at most kRankMaxCount elements known when the
-// sort is queued) replace the merge passes with one launch: each element's
-// place is its position in its own block-sorted tile plus its count in
-// every other tile, found by a binary search in that tile held in LDS, and
-// the last of those additions places it.
+// sort is queued) sort tiles of 1024 instead, so that a support of a few
+// thousand vertices is on several CUs, and replace the merge passes with one
+// launch: each element's place is its position in its own tile plus its
+// count in every other tile, found by binary searches in tiles held in LDS,
+// and the last of those additions places it.
 //
 // The block-sort launch can carry a side job (SortArgs::side_ids) for its
 // workgroups that hold no tile: with supports of a few tiles most of the
@@ -89,19 +90,20 @@ __device__ __forceinline__ void cswap(SortElem& a, SortElem& b, bool up) {
 }
 
 constexpr int kSideItems = 4;                    // side-job entries per thread and step
-constexpr int kSideStep = kBSBlk * kSideItems;
 constexpr int kSideGrid = 512;                   // block-sort workgroups when a side job rides along
 
 // The block-sort launch's side job (SortArgs::side_ids), in steps of
-// kSideStep ids per workgroup: the workgroups are renumbered so that those
+// NT * kSideItems ids per workgroup of NT threads: the workgroups are renumbered so that those
 // holding no tile take the first steps; the ones that sorted a tile join
 // only when there are more steps than workgroups without one.  Each step
 // places its nonzeros with one workgroup scan and one global atomic.
+template <int NT>
 __device__ void side_job(const SortArgs& s, int ntiles) {
+  constexpr int kSideStep = NT * kSideItems;
   long long T = *s.side_count;
   if (T > s.side_out_cap) T = s.side_out_cap;
   if (T <= 0) return;
-  __shared__ long long sh[kBSBlk / 64 + 1];
+  __shared__ long long sh[NT / 64 + 1];
   __shared__ long long s_base;
   const int G = gridDim.x;
   const int busy = ntiles < G ? ntiles : G;
@@ -112,7 +114,7 @@ __device__ void side_job(const SortArgs& s, int ntiles) {
     double x[kSideItems];
 #pragma unroll
     for (int k = 0; k < kSideItems; k++) {
-      const long long i = base + k * kBSBlk + t;
+      const long long i = base + k * NT + t;
       v[k] = i < T ? s.side_ids[i] : -1;
     }
 #pragma unroll
@@ -125,7 +127,7 @@ __device__ void side_job(const SortArgs& s, int ntiles) {
       cnt += x[k] != 0.0;
     }
     long long tot;
-    const long long off = block_excl_scan<kBSBlk>(cnt, &tot, sh);
+    const long long off = block_excl_scan<NT>(cnt, &tot, sh);
     if (t == 0) s_base = tot > 0 ? atomicAdd(s.side_out_cnt, (int32_t)tot) : 0;
     __syncthreads();
     long long slot = s_base + off;
@@ -145,17 +147,16 @@ __device__ void side_job(const SortArgs& s, int ntiles) {
   }
 }
 
-// rank: one rank merge follows instead of merge passes.  Where the sorted
-// elements end up follows from the count, so nothing of the sort counts its
-// workgroups (512 additions to one word outlast the merging of 30,000
-// elements).
-__global__ __launch_bounds__(kBSBlk) void k_block_sort(SortArgs s, bool rank) {
+// Where the sorted elements end up follows from the count, so nothing of the
+// sort counts its workgroups (512 additions to one word outlast the merging
+// of 30,000 elements).
+__global__ __launch_bounds__(kBSBlk) void k_block_sort(SortArgs s) {
   const int N = *s.count;
   if (!sort_enabled(s)) return;
   SortElem* buf = s.buf[0];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     int flip = 0;
-    for (long long L = kTileB; L < N; L <<= 1) flip = rank ? 1 : flip ^ 1;
+    for (long long L = kTileB; L < N; L <<= 1) flip ^= 1;
     *s.flip = flip;
   }
   __shared__ SortElem sh[kTileB + kTileB / kBT];
@@ -234,65 +235,177 @@ __global__ __launch_bounds__(kBSBlk) void k_block_sort(SortArgs s, bool rank) {
       const int i = k * kBSBlk + t;
       if (base + i < N) {
         buf[base + i] = sh[lds_pad(i)];
-        if (s.rank != nullptr) s.rank[base + i] = (unsigned long long)i;
       }
     }
     __syncthreads();
   }
-  if (s.side_ids != nullptr) side_job(s, ntiles);
+  if (s.side_ids != nullptr) side_job<kBSBlk>(s, ntiles);
 }
 
 // ------------------------------------------------------ small-count path
 
+constexpr int kTileR = 1024;                           // elements per tile
+constexpr int kTSBlk = 512;                            // threads of the tile sort
 constexpr int kRankBlk = 512;                          // threads of the rank merge
-constexpr int kRankGrid = 512;                         // its workgroups, split among the tiles
-static_assert(kRankMaxCount % kTileB == 0, "whole block-sort tiles");
+constexpr int kRankTiles = 4;                          // tiles a workgroup holds in LDS
+constexpr int kRankSpan = kRankTiles * kTileR;
+constexpr int kRankGrid = 512;                         // its workgroups, at most
+static_assert(kRankMaxCount % kRankSpan == 0, "whole groups of tiles");
 
-// Places every element of the block-sorted tiles at its rank in the whole
-// order.  Workgroup (j, g) of the per workgroups of tile j holds tile j in
-// LDS and takes every per-th element outside it: each lane counts the
-// elements of tile j that precede its element (those not greater when tile
-// j comes first, those less when it comes later, so equal elements of
-// different tiles keep tile order) and adds the count to the element's rank
-// word (set by the block sort to its position in its own tile), whose upper
-// half counts the additions; the addition that completes the T - 1 of them
-// writes the element out.  Tiles beyond tiles_max (a count above the bound
-// the launch was sized for) are taken in further turns.
-__global__ __launch_bounds__(kRankBlk) void k_rank_merge(SortArgs s, int tiles_max, int per) {
+// An element with its key turned back into the ratio: the searches compare
+// millions of pairs, and two double comparisons (full rate) take the place of
+// two 64-bit integer ones.  Ratios are positive; the padding past the count
+// has ratio -1 and an id of its own, so that no two elements are equal.
+struct __align__(16) RankElem {
+  double ratio;
+  int32_t id, seg;
+};
+__device__ __forceinline__ RankElem rank_elem(const SortElem e) {
+  return RankElem{__longlong_as_double((long long)~e.key), e.id, e.seg};
+}
+// SEG: several segments (the plain path has one).
+template <bool SEG>
+__device__ __forceinline__ bool rank_lt(const RankElem a, const RankElem b) {
+  const bool r = (a.ratio > b.ratio) | ((a.ratio == b.ratio) & (a.id < b.id));
+  return SEG ? (a.seg < b.seg) | ((a.seg == b.seg) & r) : r;
+}
+
+// Tile sort: pairs, then runs of L merge into runs of 2 L by rank: an
+// element's place is its position plus its count in the sibling run, a
+// branch-free binary search in LDS (a merge-path round of the block sort
+// takes as many LDS round trips, and then one per output).  Runs past the
+// count are left unmerged.  On R-MAT 2^22 queries (30,000 elements, the side
+// job beside it) 13.7 us where the block sort of 4096-element tiles took 32,
+// which it took for 100 elements too (now 3.9).
+template <bool SEG>
+__global__ __launch_bounds__(kTSBlk) void k_tile_sort(SortArgs s) {
   const int N = *s.count;
   if (!sort_enabled(s)) return;
-  const int T = (N + kTileB - 1) / kTileB;
-  if (T <= 1) return;
+  SortElem* buf = s.buf[0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *s.flip = N > kTileR;
+  __shared__ RankElem sh[2][kTileR];
+  const int ntiles = (N + kTileR - 1) / kTileR;
+  const int t = threadIdx.x;
+  static_assert(kTileR == 2 * kTSBlk, "two elements per thread");
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int base = tile * kTileR;
+    const int len = N - base < kTileR ? N - base : kTileR;
+    {
+      const int i = 2 * t;
+      RankElem a{-1.0, i, INT32_MAX}, b{-1.0, i + 1, INT32_MAX};
+      if (i < len) a = rank_elem(buf[base + i]);
+      if (i + 1 < len) b = rank_elem(buf[base + i + 1]);
+      const bool sw = rank_lt<SEG>(b, a);
+      sh[0][sw ? i + 1 : i] = a;
+      sh[0][sw ? i : i + 1] = b;
+    }
+    __syncthreads();
+    int cur = 0;
+    for (int L = 2; L < len; L <<= 1, cur ^= 1) {
+      const RankElem* src = sh[cur];
+      RankElem* dst = sh[cur ^ 1];
+      const RankElem x0 = src[t], x1 = src[t + kTSBlk];
+      const RankElem* s0 = src + ((t & ~(L - 1)) ^ L);
+      const RankElem* s1 = src + (((t + kTSBlk) & ~(L - 1)) ^ L);
+      int c0 = 0, c1 = 0;
+      for (int h = L >> 1; h > 0; h >>= 1) {
+        const RankElem y0 = s0[c0 + h - 1], y1 = s1[c1 + h - 1];
+        c0 += rank_lt<SEG>(y0, x0) ? h : 0;
+        c1 += rank_lt<SEG>(y1, x1) ? h : 0;
+      }
+      c0 += rank_lt<SEG>(s0[c0], x0) ? 1 : 0;
+      c1 += rank_lt<SEG>(s1[c1], x1) ? 1 : 0;
+      dst[(t & ~(2 * L - 1)) + (t & (L - 1)) + c0] = x0;
+      dst[((t + kTSBlk) & ~(2 * L - 1)) + (t & (L - 1)) + c1] = x1;
+      __syncthreads();
+    }
+    static_assert((kTSBlk & (kTSBlk - 1)) == 0, "t and t + kTSBlk agree below a run's length");
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+      const int i = k * kTSBlk + t;
+      if (i < len) {
+        const RankElem e = sh[cur][i];
+        buf[base + i] =
+            SortElem{~(unsigned long long)__double_as_longlong(e.ratio), e.id, e.seg};
+        s.rank[base + i] = (unsigned long long)i;
+      }
+    }
+    __syncthreads();
+  }
+  if (s.side_ids != nullptr) side_job<kTSBlk>(s, ntiles);
+}
+
+// Places every element of the sorted tiles at its rank in the whole order.
+// Workgroup (j, g) of the per workgroups of tile group j holds the group's
+// kRankTiles tiles in LDS and takes every per-th element: each lane counts
+// the elements of those tiles (its own left out) that come before its
+// element, one search per tile in flight together, and adds the count to the
+// element's rank word (set by the tile sort to its position in its own tile),
+// whose upper half counts the groups; the addition that completes them
+// writes the element out.
+template <bool SEG>
+__global__ __launch_bounds__(kRankBlk) void k_rank_merge(SortArgs s, int groups_max, int per) {
+  const int N = *s.count;
+  if (!sort_enabled(s)) return;
+  if (N <= kTileR) return;
+  const int groups = (N + kRankSpan - 1) / kRankSpan;
   const SortElem* src = s.buf[0];
   SortElem* dst = s.buf[1];
-  __shared__ SortElem sh[kTileB];
+  __shared__ RankElem sh[kRankSpan];
   const int g = blockIdx.x % per;
-  for (int j = blockIdx.x / per; j < T; j += tiles_max) {
-    const int base = j * kTileB;
-    const int len = N - base < kTileB ? N - base : kTileB;
+  for (int j = blockIdx.x / per; j < groups; j += groups_max) {
+    const int base = j * kRankSpan;
+    const int len = N - base < kRankSpan ? N - base : kRankSpan;
     __syncthreads();
-    for (int x = threadIdx.x; x < len; x += kRankBlk) sh[x] = src[base + x];
+    for (int x = threadIdx.x; x < len; x += kRankBlk) sh[x] = rank_elem(src[base + x]);
     __syncthreads();
-    const int others = N - len;
-    for (int q = g * kRankBlk + threadIdx.x; q < others; q += per * kRankBlk) {
-      const int k = q < base ? q : q + len;
-      const SortElem e = src[k];
-      int lo = 0, hi = len;
-      if (k >= base) {
-        while (lo < hi) {
-          const int mid = (lo + hi) >> 1;
-          if (elem_lt(e, sh[mid])) hi = mid; else lo = mid + 1;
-        }
-      } else {
-        while (lo < hi) {
-          const int mid = (lo + hi) >> 1;
-          if (elem_lt(sh[mid], e)) lo = mid + 1; else hi = mid;
+    for (int q = g * kRankBlk + threadIdx.x; q < N; q += per * kRankBlk) {
+      const SortElem e = src[q];
+      const RankElem x = rank_elem(e);
+      const int own = q / kTileR - j * kRankTiles;
+      int n[kRankTiles], c[kRankTiles];
+#pragma unroll
+      for (int k = 0; k < kRankTiles; k++) {
+        const int r = len - k * kTileR;
+        n[k] = k == own ? 0 : r < kTileR ? r : kTileR;  // (<= 0: nothing to count)
+        c[k] = 0;
+      }
+      for (int h = kTileR; h > 0; h >>= 1) {
+#pragma unroll
+        for (int k = 0; k < kRankTiles; k++) {
+          const int at = c[k] + h - 1;
+          const RankElem y = sh[k * kTileR + (at < n[k] ? at : 0)];
+          c[k] += (at < n[k]) & rank_lt<SEG>(y, x) ? h : 0;
         }
       }
-      const unsigned long long old = atomicAdd(&s.rank[k], (1ull << 32) | (unsigned long long)lo);
-      if ((int)(old >> 32) == T - 2) dst[(long long)(old & 0xffffffffull) + lo] = e;
+      int lo = 0;
+#pragma unroll
+      for (int k = 0; k < kRankTiles; k++) lo += c[k];
+      if (groups == 1) {
+        dst[(q & (kTileR - 1)) + lo] = e;
+      } else {
+        const unsigned long long old =
+            atomicAdd(&s.rank[q], (1ull << 32) | (unsigned long long)lo);
+        if ((int)(old >> 32) == groups - 1) dst[(long long)(old & 0xffffffffull) + lo] = e;
+      }
     }
   }
+}
+
+template <bool SEG>
+static void rank_sort(hipStream_t st, const SortArgs& s, int64_t max_count) {
+  // a side job takes the workgroups without a tile: two per CU keep the
+  // gather from outlasting the sort
+  const int tiles = (int)((max_count + kTileR - 1) / kTileR);
+  const int grid = s.side_ids != nullptr ? kSideGrid : tiles;
+  hipLaunchKernelGGL(k_tile_sort<SEG>, dim3(grid), dim3(kTSBlk), 0, st, s);
+  if (tiles <= 1) return;
+  // one element per thread while that keeps to kRankGrid workgroups
+  const int groups = (int)((max_count + kRankSpan - 1) / kRankSpan);
+  const int want = (int)((max_count + kRankBlk - 1) / kRankBlk);
+  const int most = kRankGrid / groups;
+  const int per = want < most ? want : most;
+  hipLaunchKernelGGL(k_rank_merge<SEG>, dim3(groups * per), dim3(kRankBlk), 0, st, s, groups, per);
 }
 
 // ------------------------------------------------------------ merge passes
@@ -405,19 +518,12 @@ __global__ __launch_bounds__(kSortBlk) void k_merge_pass(SortArgs s, int L, int 
 }
 
 hipError_t launch_sort(hipStream_t st, const SortArgs& s, int64_t max_count, int grid) {
-  // a side job takes the workgroups without a tile: two per CU fit the
-  // tile's LDS, so up to that many keep the gather from outlasting the sort
-  const int bs_grid = s.side_ids != nullptr && grid < kSideGrid ? kSideGrid : grid;
-  const bool rank = s.rank != nullptr && max_count <= kRankMaxCount;
-  hipLaunchKernelGGL(k_block_sort, dim3(bs_grid), dim3(kBSBlk), 0, st, s, rank);
-  if (rank) {
-    const int tiles = (int)((max_count + kTileB - 1) / kTileB);
-    if (tiles > 1) {
-      const int per = kRankGrid / tiles;
-      hipLaunchKernelGGL(k_rank_merge, dim3(tiles * per), dim3(kRankBlk), 0, st, s, tiles, per);
-    }
+  if (s.rank != nullptr && max_count <= kRankMaxCount) {
+    if (s.segments) rank_sort<true>(st, s, max_count); else rank_sort<false>(st, s, max_count);
     return hipGetLastError();
   }
+  const int bs_grid = s.side_ids != nullptr && grid < kSideGrid ? kSideGrid : grid;
+  hipLaunchKernelGGL(k_block_sort, dim3(bs_grid), dim3(kBSBlk), 0, st, s);
   int from = 0;
   for (int64_t L = kTileB; L < max_count; L <<= 1, from ^= 1)
     hipLaunchKernelGGL(k_merge_pass, dim3(grid), dim3(kSortBlk), 0, st, s, (int)L, from);
