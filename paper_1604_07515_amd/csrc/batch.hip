@@ -37,6 +37,7 @@ constexpr int kMaxSlots = 1024;
 // hot vertices): sized so that four scatter workgroups fit in a CU's LDS.
 constexpr int kSlotRange = 128;
 constexpr int kHotB = 1024;
+static_assert(kMaxSlots <= kMaxSortSegs, "a segment per slot");
 static_assert(kHotB <= kHot, "the batched hot set is a prefix of the graph's");
 
 __device__ __forceinline__ int slot_of(const int32_t* pref, int B, long long g) {
@@ -104,8 +105,14 @@ struct DenseState {
   __device__ static int32_t hot_deg(const BatchArgs&, int32_t, int32_t d) { return d; }
   __device__ static VRec* find(const Slot& S, int32_t v) { return S.tab + v; }
   __device__ static VRec* insert(const BatchArgs&, const Slot& S, int32_t v) { return S.tab + v; }
-  __device__ static int32_t rank_of(const Slot& S, int32_t v) { return S.tab[v].rank; }
-  __device__ static int32_t rank_at(const VRec* tab, int32_t, int32_t v) { return tab[v].rank; }
+  // Lookup in two steps, as probe_start and probe_finish (see CompactState).
+  __device__ static int2 look_start(const TabView& t, int32_t v, uint32_t*) {
+    return make_int2(v, t.tab[v].rank);
+  }
+  __device__ static int32_t look_rank(const TabView&, int32_t, uint32_t, int2 kr) { return kr.y; }
+  __device__ static VRec* find_finish(const TabView& t, int32_t v, uint32_t, int2) {
+    return t.tab + v;
+  }
   __device__ static double* pp(const Slot& S, int32_t v, const VRec*) { return S.tp + v; }
   __device__ static int2 deg_hot(const BatchArgs&, const Slot& S, int32_t v) {
     return *reinterpret_cast<const int2*>(&S.tab[v].deg);
@@ -208,17 +215,28 @@ struct CompactState {
     const int32_t tag = rec->rank;
     return tag < -kHot ? -1 - kHot - tag : a.gdh[v].x;
   }
-  __device__ static int32_t rank_of(const Slot& S, int32_t v) { return rank_at(S.tab, S.tcap, v); }
-  __device__ static int32_t rank_at(const VRec* tab, int32_t tcap, int32_t v) {
-    const uint32_t cap = (uint32_t)tcap;
-    uint32_t h = home_of(v, cap);
+  // Lookup in two steps, so that a thread's first loads overlap: look_start
+  // loads the {key, rank or tag} word at v's home position, the others
+  // resolve it (0 / nullptr when v is not in the table).
+  __device__ static int2 look_start(const TabView& t, int32_t v, uint32_t* h) {
+    *h = home_of(v, (uint32_t)t.tcap);
+    return *reinterpret_cast<const int2*>(&t.tab[*h].deg);
+  }
+  __device__ static int32_t look_rank(const TabView& t, int32_t v, uint32_t h, int2 kr) {
+    return look_on(t, v, &h, &kr) ? kr.y : 0;
+  }
+  __device__ static VRec* find_finish(const TabView& t, int32_t v, uint32_t h, int2 kr) {
+    return look_on(t, v, &h, &kr) ? t.tab + h : nullptr;
+  }
+  __device__ static bool look_on(const TabView& t, int32_t v, uint32_t* h, int2* kr) {
+    const uint32_t cap = (uint32_t)t.tcap;
     for (uint32_t i = 0; i < cap; i++) {
-      const int2 kr = *reinterpret_cast<const int2*>(&tab[h].deg);  // {key, rank or tag}
-      if (kr.x == v) return kr.y;
-      if (kr.x == kEmptyKey) return 0;
-      h = probe_next(h, cap);
+      if (kr->x == v) return true;
+      if (kr->x == kEmptyKey) return false;
+      *h = probe_next(*h, cap);
+      *kr = *reinterpret_cast<const int2*>(&t.tab[*h].deg);
     }
-    return 0;
+    return false;
   }
   __device__ static double* pp(const Slot& S, int32_t, const VRec* rec) {
     return S.tp + (rec - S.tab);
@@ -360,88 +378,137 @@ __global__ __launch_bounds__(kMaxSlots) void k_b_plan(BatchArgs a) {
   }
 }
 
-template <class St>
-__global__ __launch_bounds__(kBlock) void k_b_self(BatchArgs a) {
+// vertexMap over the scheduled entries and the scan of their degrees.  A
+// thread takes kScanItems consecutive entries (one slot nearly always: its
+// state is loaded once) and has the loads of all of them in flight at each
+// step of the chain slot -> vertex -> record -> p, which is what bounds it.
+// Rounds of up to kScanFixed workgroups of one entry per thread are spread
+// that way over four times the CUs.  32 rounds of 40,000 entries on average
+// (R-MAT 2^22, 256 slots) took 19.2 us each, one entry after another, 18.4 in
+// blocks of 1024 entries with their loads together, and now 12.8; compact
+// tables (R-MAT 2^20, 128 slots, 61,000 entries) 34.7, now 26.0.
+struct BSelfLds {
+  int32_t pref[kMaxSlots + 1];
+  long long sh[kBlock / 64 + 1];
+  long long excl;
+  int tk[2];
+  int qlo, qhi;
+  int csup[kScanBlock], cstay[kScanBlock];
+  unsigned long long estay[kScanBlock];
+  int bsup[kScanBlock], bstay[kScanBlock];
+};
+
+template <class St, int IT>
+__device__ void b_self(const BatchArgs& a, int NF, BSelfLds& L) {
+  constexpr int kSpan = IT * kBlock;  // entries of a block
   BatchCtl* c = a.ctl;
-  const int NF = c->nf_total;
-  if (NF <= 0) return;
+  const int nblk = (NF + kSpan - 1) / kSpan;
+  const bool fixed = scan_fixed(nblk);
+  if (fixed && (int)blockIdx.x >= nblk) return;
   const int B = a.B;
-  __shared__ int32_t s_pref[kMaxSlots + 1];
-  __shared__ long long sh[kBlock / 64 + 1];
-  __shared__ long long s_excl;
-  __shared__ int s_tk[2];
-  __shared__ int s_qlo, s_qhi;
-  __shared__ int s_csup[kScanBlock], s_cstay[kScanBlock];
-  __shared__ unsigned long long s_estay[kScanBlock];
-  __shared__ int s_bsup[kScanBlock], s_bstay[kScanBlock];
+  int32_t* const s_pref = L.pref;
+  int *const s_csup = L.csup, *const s_cstay = L.cstay;
+  int *const s_bsup = L.bsup, *const s_bstay = L.bstay;
+  unsigned long long* const s_estay = L.estay;
   for (int j = threadIdx.x; j <= B; j += kBlock) s_pref[j] = a.fprefix[j];
   ScanSite* site = &c->scan[BSCAN_FRONTIER];
-  scan_clear_prev(site, a.desc[BSCAN_FRONTIER], a.desc_cap);
+  scan_clear_prev(site, a.desc[BSCAN_FRONTIER], a.desc_cap, fixed ? nblk : 0);
   unsigned long long* desc = a.desc[BSCAN_FRONTIER] + (size_t)site->parity * a.desc_cap;
-  const int nblk = (NF + kScanBlock - 1) / kScanBlock;
   __syncthreads();
 
-  for (;;) {
+  for (int pass = 0;; pass++) {
     bool last;
-    int b = scan_ticket(site, nblk, s_tk, &last);
+    const int b = fixed ? (pass == 0 ? (int)blockIdx.x : nblk) : scan_ticket(site, nblk, L.tk, &last);
     if (b >= nblk) break;
-    if (threadIdx.x == 0) {
-      long long g0 = (long long)b * kScanBlock;
-      long long g1 = g0 + kScanBlock - 1 < NF - 1 ? g0 + kScanBlock - 1 : NF - 1;
-      s_qlo = slot_of(s_pref, B, g0);
-      s_qhi = slot_of(s_pref, B, g1);
+    const int g0 = b * kSpan + (int)threadIdx.x * IT;
+    // the entries' slots (ascending), the block's first and last
+    int qk[IT];
+    {
+      int q = g0 < NF ? slot_of(s_pref, B, g0) : 0;
+#pragma unroll
+      for (int k = 0; k < IT; k++) {
+        if (g0 + k < NF)
+          while (s_pref[q + 1] <= g0 + k) q++;
+        qk[k] = q;
+      }
+      if (threadIdx.x == 0) L.qlo = qk[0];
+#pragma unroll
+      for (int k = 0; k < IT; k++)
+        if (g0 + k == NF - 1 || (g0 + k < NF && g0 + k == b * kSpan + kSpan - 1))
+          L.qhi = qk[k];
     }
     __syncthreads();
-    const int qlo = s_qlo;
-    const int range = s_qhi - qlo + 1;  // <= kScanBlock: each entry is one slot
+    const int qlo = L.qlo;
+    const int range = L.qhi - qlo + 1;  // <= kSpan: each entry is one slot
     for (int j = threadIdx.x; j < range; j += kBlock) {
       s_csup[j] = 0;
       s_cstay[j] = 0;
       s_estay[j] = 0ull;
     }
     __syncthreads();
-    int32_t vk[kScanItems], dk[kScanItems], qk[kScanItems], rsup[kScanItems], rstay[kScanItems];
+    int32_t vk[IT], dk[IT], rsup[IT], rstay[IT];
+    VRec* rp[IT];
+    double rho[IT], pold[IT];
+    long long row[IT];
     long long dsum = 0;
 #pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
-      const long long g = (long long)b * kScanBlock + k * kBlock + threadIdx.x;
+    for (int k = 0; k < IT; k++) {
       vk[k] = -1;
+      if (g0 + k < NF) {
+        const Slot& S = a.slots[qk[k]];
+        vk[k] = S.fb[S.par][g0 + k - s_pref[qk[k]]];
+      }
+    }
+    TabView tv[IT];
+    uint32_t hk[IT];
+    int2 kr[IT];
+#pragma unroll
+    for (int k = 0; k < IT; k++) {
+      row[k] = 0;
+      if (vk[k] < 0) continue;
+      const Slot& S = a.slots[qk[k]];
+      tv[k] = TabView{S.tab, S.tcap};
+      if (St::kCompact) kr[k] = St::look_start(tv[k], vk[k], &hk[k]);
+      row[k] = a.off[vk[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < IT; k++)
+      rp[k] = vk[k] >= 0 ? St::find_finish(tv[k], vk[k], hk[k], kr[k]) : nullptr;
+#pragma unroll
+    for (int k = 0; k < IT; k++) {
+      rho[k] = 0.0;
+      pold[k] = 0.0;
       dk[k] = 0;
-      qk[k] = 0;
+      if (rp[k]) {
+        rho[k] = rp[k]->r;
+        dk[k] = St::deg_rec(a, vk[k], rp[k]);
+        pold[k] = *St::pp(a.slots[qk[k]], vk[k], rp[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < IT; k++) {
       rsup[k] = -1;
       rstay[k] = -1;
-      if (g < NF) {
-        const int q = slot_of(s_pref, B, g);
-        const Slot& S = a.slots[q];
-        const int i = (int)(g - s_pref[q]);
-        const int32_t v = S.fb[S.par][i];
-        VRec* rp = St::find(S, v);
-        double rho = 0.0;
-        int32_t d = 0;
-        if (rp) {
-          rho = rp->r;
-          d = St::deg_rec(a, v, rp);
-          double* pv = St::pp(S, v, rp);
-          const double pold = *pv;
-          *pv = pold + S.cs * rho;
-          const double nr = S.opt ? -0.0 : S.keep * rho;
-          rp->r = nr;
-          if (pold == 0.0) rsup[k] = atomicAdd(&s_csup[q - qlo], 1);
-          if (!S.opt && nr >= S.eps * (double)d) {
-            rstay[k] = atomicAdd(&s_cstay[q - qlo], 1);
-            atomicAdd(&s_estay[q - qlo], (unsigned long long)d);
-          }
-        } else {
-          c->fault = 1;  // a frontier vertex always has a record
+      if (vk[k] < 0) continue;
+      const int q = qk[k];
+      const Slot& S = a.slots[q];
+      const int32_t d = dk[k];
+      if (rp[k]) {
+        *St::pp(S, vk[k], rp[k]) = pold[k] + S.cs * rho[k];
+        const double nr = S.opt ? -0.0 : S.keep * rho[k];
+        rp[k]->r = nr;
+        if (pold[k] == 0.0) rsup[k] = atomicAdd(&s_csup[q - qlo], 1);
+        if (!S.opt && nr >= S.eps * (double)d) {
+          rstay[k] = atomicAdd(&s_cstay[q - qlo], 1);
+          atomicAdd(&s_estay[q - qlo], (unsigned long long)d);
         }
-        a.coef[g] = d > 0 ? (S.cn * rho) / (double)d : 0.0;
-        a.rowp[g] = a.off[v];
-        a.eslot[g] = q;
-        vk[k] = v;
-        dk[k] = d;
-        qk[k] = q;
+      } else {
+        c->fault = 1;  // a frontier vertex always has a record
       }
-      dsum += dk[k];
+      a.coef[g0 + k] = d > 0 ? (S.cn * rho[k]) / (double)d : 0.0;
+      a.rowp[g0 + k] = row[k];
+      a.eslot[g0 + k] = q;
+      dsum += d;
     }
     __syncthreads();
     for (int j = threadIdx.x; j < range; j += kBlock) {
@@ -453,9 +520,16 @@ __global__ __launch_bounds__(kBlock) void k_b_self(BatchArgs a) {
         atomicAdd((unsigned long long*)&S.edge_next[nxt], s_estay[j]);
       }
     }
+    long long agg;
+    const long long ex = block_excl_scan<kBlock>(dsum, &agg, L.sh);
+    if (threadIdx.x < 64) {
+      const long long ex0 = scan_lookback(desc, b, agg, &c->fault);
+      if (threadIdx.x == 0) L.excl = ex0;
+    }
     __syncthreads();
+    long long s = L.excl + ex;
 #pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
+    for (int k = 0; k < IT; k++) {
       if (vk[k] < 0) continue;
       const Slot& S = a.slots[qk[k]];
       if (rsup[k] >= 0) {
@@ -466,34 +540,29 @@ __global__ __launch_bounds__(kBlock) void k_b_self(BatchArgs a) {
         const long long pos = (long long)s_bstay[qk[k] - qlo] + rstay[k];
         if (pos < S.list_cap) S.fb[S.par ^ 1][pos] = vk[k]; else c->fault = 1;
       }
-    }
-    long long agg;
-    (void)block_excl_scan<kBlock>(dsum, &agg, sh);
-    if (threadIdx.x < 64) {
-      const long long ex0 = scan_lookback(desc, b, agg, &c->fault);
-      if (threadIdx.x == 0) s_excl = ex0;
-    }
-    __syncthreads();
-    long long run = s_excl;
-    for (int k = 0; k < kScanItems; k++) {
-      const long long g = (long long)b * kScanBlock + k * kBlock + threadIdx.x;
-      long long tot;
-      long long ex = block_excl_scan<kBlock>(dk[k], &tot, sh);
-      if (g < NF) {
-        const long long s = run + ex;
-        a.estart[g] = s;
-        long long t0 = (s + kEdgeTile - 1) / kEdgeTile;
-        long long t1 = (s + dk[k] - 1) / kEdgeTile;
-        if (t1 >= a.tile_cap) { c->fault = 1; t1 = a.tile_cap - 1; }
-        for (long long tt = t0; tt <= t1; tt++) a.tile_start[tt] = (int32_t)g;
-      }
-      run += tot;
+      a.estart[g0 + k] = s;
+      const long long t0 = (s + kEdgeTile - 1) / kEdgeTile;
+      long long t1 = (s + dk[k] - 1) / kEdgeTile;
+      if (t1 >= a.tile_cap) { c->fault = 1; t1 = a.tile_cap - 1; }
+      for (long long tt = t0; tt <= t1; tt++) a.tile_start[tt] = g0 + k;
+      s += dk[k];
     }
     if (b == nblk - 1 && threadIdx.x == 0) {
-      if (run != c->e_total) c->fault = 1;  // planned and scanned edge counts must agree
+      if (L.excl + agg != c->e_total) c->fault = 1;  // planned and scanned edges must agree
     }
     __syncthreads();
   }
+  if (fixed && threadIdx.x == 0) (void)scan_retire(site, nblk);
+}
+
+template <class St>
+__global__ __launch_bounds__(kBlock) void k_b_self(BatchArgs a) {
+  const int NF = a.ctl->nf_total;
+  if (NF <= 0) return;
+  __shared__ BSelfLds L;
+  const int n1 = (NF + kBlock - 1) / kBlock;
+  if (scan_fixed(n1) && n1 <= a.desc_cap) b_self<St, 1>(a, NF, L);
+  else b_self<St, kScanItems>(a, NF, L);
 }
 
 // Append w to slot q's next frontier and/or touched list with direct global
@@ -917,93 +986,139 @@ __global__ __launch_bounds__(kBlock) void k_sw_keys(BatchArgs a) {
   }
 }
 
-template <class St>
-__global__ __launch_bounds__(kBlock) void k_sw_rank(BatchArgs a) {
+// One workgroup-wide step of a scan over a concatenation of `total` elements
+// (kScanItems consecutive ones per thread): body(i0, x) fills the thread's
+// values for the elements i0 .. i0 + kScanItems, then out(i, s, x) gets each
+// with the sum of all values before it, and at the end fin(sum of all).
+// Up to kScanFixed blocks go to the workgroups of the same numbers.
+template <class Load, class Out, class Fin>
+__device__ __forceinline__ void b_scan(const BatchArgs& a, int site_id, long long total,
+                                       Load&& load, Out&& out, Fin&& fin) {
   BatchCtl* c = a.ctl;
-  const long long total = c->sw_total;
-  const SortElem* el = a.sbuf[c->sort_flip & 1];
-  for (long long k = (long long)blockIdx.x * kBlock + threadIdx.x; k < total;
-       k += (long long)gridDim.x * kBlock) {
-    const SortElem e = el[k];
-    const SweepSeg& sg = a.segs[e.seg];
-    const Slot& S = a.slots[sg.slot];
-    const long long i = k - sg.elem_off;
-    VRec* rp = St::find(S, e.id);
-    if (!rp) {
-      c->fault = 1;
-      continue;
-    }
-    rp->rank = (int32_t)(i + 1);
-    a.sdeg[k] = St::deg_hot(a, S, e.id).x;
-    if (sg.out_ids) {
-      sg.out_ids[i] = e.id;
-      sg.out_p[i] = *St::pp(S, e.id, rp);
-    }
-    a.scnt[k] = 0;
-  }
-}
-
-// Inclusive scan of src[k] (or of sdeg - 2*scnt when cut) into dst, and,
-// for the volume scan, the edge-tile map over the concatenated supports.
-template <bool CUT>
-__global__ __launch_bounds__(kBlock) void k_sw_scan(BatchArgs a) {
-  BatchCtl* c = a.ctl;
-  const long long total = c->sw_total;
-  if (total <= 0) return;
   __shared__ long long sh[kBlock / 64 + 1];
   __shared__ long long s_excl;
   __shared__ int s_tk[2];
-  const int site_id = CUT ? BSCAN_CUT : BSCAN_VOL;
-  ScanSite* site = &c->scan[site_id];
-  scan_clear_prev(site, a.desc[site_id], a.desc_cap);
-  unsigned long long* desc = a.desc[site_id] + (size_t)site->parity * a.desc_cap;
   const int nblk = (int)((total + kScanBlock - 1) / kScanBlock);
-  for (;;) {
+  const bool fixed = scan_fixed(nblk);
+  if (fixed && (int)blockIdx.x >= nblk) return;
+  ScanSite* site = &c->scan[site_id];
+  scan_clear_prev(site, a.desc[site_id], a.desc_cap, fixed ? nblk : 0);
+  unsigned long long* desc = a.desc[site_id] + (size_t)site->parity * a.desc_cap;
+  for (int pass = 0;; pass++) {
     bool last;
-    int b = scan_ticket(site, nblk, s_tk, &last);
+    const int b = fixed ? (pass == 0 ? (int)blockIdx.x : nblk) : scan_ticket(site, nblk, s_tk, &last);
     if (b >= nblk) break;
+    const long long i0 = (long long)b * kScanBlock + (long long)threadIdx.x * kScanItems;
     long long xk[kScanItems];
     long long xsum = 0;
-    for (int k = 0; k < kScanItems; k++) {
-      const long long i = (long long)b * kScanBlock + k * kBlock + threadIdx.x;
-      xk[k] = 0;
-      if (i < total) xk[k] = CUT ? (long long)a.sdeg[i] - 2ll * a.scnt[i] : (long long)a.sdeg[i];
-      xsum += xk[k];
-    }
+    load(i0, xk);
+#pragma unroll
+    for (int k = 0; k < kScanItems; k++) xsum += xk[k];
     long long agg;
-    (void)block_excl_scan<kBlock>(xsum, &agg, sh);
+    const long long ex = block_excl_scan<kBlock>(xsum, &agg, sh);
     if (threadIdx.x < 64) {
       const long long ex0 = scan_lookback(desc, b, agg, &c->fault);
       if (threadIdx.x == 0) s_excl = ex0;
     }
     __syncthreads();
-    long long run = s_excl;
+    long long s = s_excl + ex;
+#pragma unroll
     for (int k = 0; k < kScanItems; k++) {
-      const long long i = (long long)b * kScanBlock + k * kBlock + threadIdx.x;
-      long long tot;
-      long long ex = block_excl_scan<kBlock>(xk[k], &tot, sh);
-      if (i < total) {
-        const long long s = run + ex;
-        if (CUT) {
-          a.scut[i] = s + xk[k];
-        } else {
-          a.svol[i] = s + xk[k];
-          long long t0 = (s + kEdgeTile - 1) / kEdgeTile;
-          long long t1 = (s + xk[k] - 1) / kEdgeTile;
-          if (t1 >= a.tile_cap) { c->fault = 1; t1 = a.tile_cap - 1; }
-          for (long long tt = t0; tt <= t1; tt++) a.tile_start[tt] = (int32_t)i;
-        }
-      }
-      run += tot;
+      if (i0 + k < total) out(i0 + k, s, xk[k]);
+      s += xk[k];
     }
-    if (!CUT && b == nblk - 1 && threadIdx.x == 0) {
-      c->sw_etotal = run;
-      c->sw_ntiles = (int)((run + kEdgeTile - 1) / kEdgeTile);
-    }
+    if (b == nblk - 1 && threadIdx.x == 0) fin(s_excl + agg);
     __syncthreads();
   }
+  if (fixed && threadIdx.x == 0) (void)scan_retire(site, nblk);
 }
 
+// Rank map, degrees, p and ids in sweep order, the inclusive volume prefix
+// over the concatenated supports and their edge-tile map.  The state lookups
+// of a thread's elements are in flight together; as a pass of its own and a
+// scan it took 119 us on the supports of 256 queries (R-MAT 2^22, 1.2 M
+// elements) and 23.4 on those of 13 (R-MAT 2^20, compact), together 127 and
+// 21.3 with one launch and one read of the degrees less.
+template <class St>
+__global__ __launch_bounds__(kBlock) void k_sw_vol(BatchArgs a) {
+  BatchCtl* c = a.ctl;
+  const long long total = c->sw_total;
+  if (total <= 0) return;
+  const SortElem* el = a.sbuf[c->sort_flip & 1];
+  b_scan(a, BSCAN_VOL, total,
+      [&](long long i0, long long* x) {
+        SortElem e[kScanItems];
+        VRec* rp[kScanItems];
+#pragma unroll
+        for (int k = 0; k < kScanItems; k++) {
+          e[k].seg = -1;
+          if (i0 + k < total) e[k] = el[i0 + k];
+        }
+        TabView tv[kScanItems];
+        uint32_t h[kScanItems];
+        int2 kr[kScanItems];
+#pragma unroll
+        for (int k = 0; k < kScanItems; k++) {
+          x[k] = 0;
+          if (e[k].seg < 0) continue;
+          const Slot& S = a.slots[a.segs[e[k].seg].slot];
+          tv[k] = TabView{S.tab, S.tcap};
+          x[k] = St::deg_hot(a, S, e[k].id).x;
+          if (St::kCompact) kr[k] = St::look_start(tv[k], e[k].id, &h[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < kScanItems; k++) {
+          rp[k] = e[k].seg >= 0 ? St::find_finish(tv[k], e[k].id, h[k], kr[k]) : nullptr;
+          if (e[k].seg >= 0 && !rp[k]) {
+            c->fault = 1;
+            x[k] = 0;
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < kScanItems; k++) {
+          if (e[k].seg < 0) continue;
+          a.sdeg[i0 + k] = (int32_t)x[k];
+          a.scnt[i0 + k] = 0;
+          if (!rp[k]) continue;
+          const SweepSeg& sg = a.segs[e[k].seg];
+          const long long i = i0 + k - sg.elem_off;
+          rp[k]->rank = (int32_t)(i + 1);
+          if (sg.out_ids) {
+            sg.out_ids[i] = e[k].id;
+            sg.out_p[i] = *St::pp(a.slots[sg.slot], e[k].id, rp[k]);
+          }
+        }
+      },
+      [&](long long i, long long s, long long x) {
+        a.svol[i] = s + x;
+        const long long t0 = (s + kEdgeTile - 1) / kEdgeTile;
+        long long t1 = (s + x - 1) / kEdgeTile;
+        if (t1 >= a.tile_cap) { c->fault = 1; t1 = a.tile_cap - 1; }
+        for (long long tt = t0; tt <= t1; tt++) a.tile_start[tt] = (int32_t)i;
+      },
+      [&](long long all) {
+        c->sw_etotal = all;
+        c->sw_ntiles = (int)((all + kEdgeTile - 1) / kEdgeTile);
+      });
+}
+
+// Inclusive prefix of the boundary changes d - 2 * count.
+__global__ __launch_bounds__(kBlock) void k_sw_cut(BatchArgs a) {
+  const long long total = a.ctl->sw_total;
+  if (total <= 0) return;
+  b_scan(a, BSCAN_CUT, total,
+      [&](long long i0, long long* x) {
+#pragma unroll
+        for (int k = 0; k < kScanItems; k++)
+          x[k] = i0 + k < total ? (long long)a.sdeg[i0 + k] - 2ll * a.scnt[i0 + k] : 0;
+      },
+      [&](long long i, long long s, long long x) { a.scut[i] = s + x; }, [](long long) {});
+}
+
+// Boundary counts: edges to an earlier rank, in 1024-edge tiles.  One random
+// state word per edge bounds it: 67 G edges/s on dense slots.  The compact
+// tables' first probes of a thread's edges are in flight together (one after
+// another: 79 us a sweep of 13 queries on R-MAT 2^20, now 62).
 template <class St>
 __global__ __launch_bounds__(kBlock) void k_sw_count(BatchArgs a) {
   BatchCtl* c = a.ctl;
@@ -1016,8 +1131,7 @@ __global__ __launch_bounds__(kBlock) void k_sw_count(BatchArgs a) {
   __shared__ int64_t s_row[kEdgeTile + 1];
   __shared__ int32_t s_cnt[kEdgeTile + 1];
   __shared__ int32_t s_own[kEdgeTile + 1];
-  __shared__ const VRec* s_tab[kEdgeTile + 1];
-  __shared__ int32_t s_tcap[kEdgeTile + 1];
+  __shared__ TabView s_view[kEdgeTile + 1];
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const long long e0 = (long long)tile * kEdgeTile;
     const long long e1 = e0 + kEdgeTile < E ? e0 + kEdgeTile : E;
@@ -1036,29 +1150,36 @@ __global__ __launch_bounds__(kBlock) void k_sw_count(BatchArgs a) {
       s_row[j] = a.off[e.id];
       s_own[j] = (int32_t)(k - sg.elem_off + 1);
       const Slot& S = a.slots[sg.slot];
-      s_tab[j] = S.tab;
-      s_tcap[j] = S.tcap;
+      s_view[j] = TabView{S.tab, S.tcap};
       s_cnt[j] = 0;
     }
     __syncthreads();
-    int32_t rw[kEdgesPerThread];
+    // each step for all of the thread's edges before the next one
+    int32_t w[kEdgesPerThread], rw[kEdgesPerThread];
     int own[kEdgesPerThread];
+    uint32_t h[kEdgesPerThread];
+    int2 kr[kEdgesPerThread];
 #pragma unroll
     for (int kk = 0; kk < kEdgesPerThread; kk++) {
       const int rel = kk * kBlock + (int)threadIdx.x;
       own[kk] = -1;
-      rw[kk] = 0;
+      w[kk] = 0;
       if (e0 + rel < e1) {
         int lo = 0, hi = cnt - 1;
         while (lo < hi) {
           int mid = (lo + hi + 1) >> 1;
           if (s_start[mid] <= rel) lo = mid; else hi = mid - 1;
         }
-        const int32_t w = a.nbr[s_row[lo] + (rel - s_start[lo])];
-        rw[kk] = St::rank_at(s_tab[lo], s_tcap[lo], w);
+        w[kk] = a.nbr[s_row[lo] + (rel - s_start[lo])];
         own[kk] = lo;
       }
     }
+#pragma unroll
+    for (int kk = 0; kk < kEdgesPerThread; kk++)
+      if (own[kk] >= 0) kr[kk] = St::look_start(s_view[own[kk]], w[kk], &h[kk]);
+#pragma unroll
+    for (int kk = 0; kk < kEdgesPerThread; kk++)
+      rw[kk] = own[kk] >= 0 ? St::look_rank(s_view[own[kk]], w[kk], h[kk], kr[kk]) : 0;
 #pragma unroll
     for (int kk = 0; kk < kEdgesPerThread; kk++)
       if (own[kk] >= 0 && rw[kk] > 0 && rw[kk] < s_own[own[kk]]) atomicAdd(&s_cnt[own[kk]], 1);
@@ -1077,8 +1198,12 @@ __device__ __forceinline__ bool b_cand_better(long long oc, long long od, long l
   return !ratio_lt(xc, xd, oc, od) && ok < xk;
 }
 
-// One workgroup per segment: exact argmin of cut/min(vol, 2m - vol).
-__global__ __launch_bounds__(kBlock) void k_sw_argmin(BatchArgs a) {
+// One workgroup per segment: exact argmin of cut/min(vol, 2m - vol).  A
+// thread's candidates are a chain of loads and 128-bit comparisons, so the
+// workgroup is as large as it can be: 4,700 elements in 86 us with 256
+// threads and a tree of barriers (256 segments), 31 with 1024 and waves.
+constexpr int kArgBlk = 1024;
+__global__ __launch_bounds__(kArgBlk) void k_sw_argmin(BatchArgs a) {
   BatchCtl* c = a.ctl;
   const int s = blockIdx.x;
   if (s >= c->sw_nseg) return;
@@ -1087,36 +1212,37 @@ __global__ __launch_bounds__(kBlock) void k_sw_argmin(BatchArgs a) {
   const long long bv = off > 0 ? a.svol[off - 1] : 0;
   const long long bc = off > 0 ? a.scut[off - 1] : 0;
   const long long vt = a.vol_total;
-  __shared__ long long s_c[kBlock], s_d[kBlock], s_k[kBlock];
+  __shared__ long long s_c[kArgBlk / 64], s_d[kArgBlk / 64], s_k[kArgBlk / 64];
   long long mc = -1, md = 1, mk = 0;
-  for (int i = threadIdx.x; i < sg.n_elem; i += kBlock) {
+  for (int i = threadIdx.x; i < sg.n_elem; i += kArgBlk) {
     const long long cut = a.scut[off + i] - bc;
     const long long vol = a.svol[off + i] - bv;
     const long long den = vol < vt - vol ? vol : vt - vol;
     if (den > 0 && b_cand_better(cut, den, i + 1, mc, md, mk)) { mc = cut; md = den; mk = i + 1; }
   }
-  s_c[threadIdx.x] = mc; s_d[threadIdx.x] = md; s_k[threadIdx.x] = mk;
-  __syncthreads();
-  for (int o = kBlock / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-      const int u = threadIdx.x + o;
-      if (b_cand_better(s_c[u], s_d[u], s_k[u], s_c[threadIdx.x], s_d[threadIdx.x],
-                        s_k[threadIdx.x])) {
-        s_c[threadIdx.x] = s_c[u];
-        s_d[threadIdx.x] = s_d[u];
-        s_k[threadIdx.x] = s_k[u];
-      }
+  auto wave_best = [&]() {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const long long oc = __shfl_xor(mc, o), od = __shfl_xor(md, o), ok = __shfl_xor(mk, o);
+      if (b_cand_better(oc, od, ok, mc, md, mk)) { mc = oc; md = od; mk = ok; }
     }
-    __syncthreads();
+  };
+  wave_best();
+  if (PLC_LANE == 0) { s_c[PLC_WID] = mc; s_d[PLC_WID] = md; s_k[PLC_WID] = mk; }
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const int u = threadIdx.x & (kArgBlk / 64 - 1);
+    mc = s_c[u]; md = s_d[u]; mk = s_k[u];
+    wave_best();
   }
   if (threadIdx.x == 0) {
     Slot& S = a.slots[sg.slot];
-    const long long k = s_k[0];
+    const long long k = mk;
     S.kstar = k > 0 ? k : 0;
-    S.best_cut = k > 0 ? s_c[0] : 0;
-    S.best_den = k > 0 ? s_d[0] : 0;
+    S.best_cut = k > 0 ? mc : 0;
+    S.best_den = k > 0 ? md : 0;
     S.best_vol = k > 0 ? a.svol[off + k - 1] - bv : 0;
-    S.phi = k > 0 ? (double)s_c[0] / (double)s_d[0] : 0.0;
+    S.phi = k > 0 ? (double)mc / (double)md : 0.0;
     S.t_done = (long long)wall_clock64();
   }
 }
@@ -1321,7 +1447,7 @@ hipError_t launch_batch_round_end(hipStream_t s, const BatchArgs& a) {
 }
 
 template <class St>
-static hipError_t sweep_kernels(hipStream_t s, const BatchArgs& a, int nseg, int64_t max_elems,
+static hipError_t sweep_kernels(hipStream_t s, const BatchArgs& a, const SweepShape& sh,
                                 int grid) {
   hipLaunchKernelGGL(k_sw_keys<St>, dim3(grid), dim3(kBlock), 0, s, a);
   SortArgs sa;
@@ -1331,16 +1457,23 @@ static hipError_t sweep_kernels(hipStream_t s, const BatchArgs& a, int nseg, int
   sa.flip = &a.ctl->sort_flip;
   sa.active = nullptr;
   sa.active_value = 0;
-  sa.rank = nullptr;
-  hipError_t e = launch_sort(s, sa, max_elems, grid);
+  sa.rank = reinterpret_cast<unsigned long long*>(a.svol);  // (written after the sort)
+  hipError_t e;
+  if (sh.max_elem <= kSegMaxCount) {
+    const SegSort g{reinterpret_cast<const char*>(static_cast<const SortSeg*>(a.segs)),
+                    (int)sizeof(SweepSeg), sh.nseg, sh.tiles, sh.items};
+    e = launch_seg_sort(s, sa, g);
+  } else {
+    sa.rank = nullptr;
+    e = launch_sort(s, sa, sh.elems, grid);
+  }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sw_rank<St>, dim3(grid), dim3(kBlock), 0, s, a);
-  hipLaunchKernelGGL(k_sw_scan<false>, dim3(grid), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_sw_vol<St>, dim3(grid), dim3(kBlock), 0, s, a);
   // the count, the gathers and the reset walk many short, latency-bound
   // steps: a larger grid keeps more of them in flight
   hipLaunchKernelGGL(k_sw_count<St>, dim3(4 * grid), dim3(kBlock), 0, s, a);
-  hipLaunchKernelGGL(k_sw_scan<true>, dim3(grid), dim3(kBlock), 0, s, a);
-  hipLaunchKernelGGL(k_sw_argmin, dim3(nseg), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_sw_cut, dim3(grid), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_sw_argmin, dim3(sh.nseg), dim3(kArgBlk), 0, s, a);
   if (St::kCompact) {
     hipLaunchKernelGGL(k_sw_gather, dim3(4 * grid), dim3(kBlock), 0, s, a);
   } else {
@@ -1350,11 +1483,11 @@ static hipError_t sweep_kernels(hipStream_t s, const BatchArgs& a, int nseg, int
   return hipGetLastError();
 }
 
-hipError_t launch_batch_sweep(hipStream_t s, const BatchArgs& a, int nseg, int64_t max_elems,
-                              int grid, bool compact) {
-  if (nseg <= 0) return hipSuccess;
-  return compact ? sweep_kernels<CompactState>(s, a, nseg, max_elems, grid)
-                 : sweep_kernels<DenseState>(s, a, nseg, max_elems, grid);
+hipError_t launch_batch_sweep(hipStream_t s, const BatchArgs& a, const SweepShape& sh, int grid,
+                              bool compact) {
+  if (sh.nseg <= 0) return hipSuccess;
+  return compact ? sweep_kernels<CompactState>(s, a, sh, grid)
+                 : sweep_kernels<DenseState>(s, a, sh, grid);
 }
 
 hipError_t launch_table_clear(hipStream_t s, const ClearJob* jobs, int count, long long total,

@@ -70,10 +70,9 @@ struct __align__(64) Slot {
 };
 
 // One query's part of a sweep batch (written by the host before the sweep).
-struct __align__(16) SweepSeg {
+// The SortSeg part: first element, support size, sort tiles and items before.
+struct __align__(16) SweepSeg : SortSeg {
   int32_t slot;
-  int32_t n_elem;           // support size
-  long long elem_off;       // first element of the segment
   long long touch_off;      // first finish entry of the segment (flattened): touched-list
                             // positions (dense) or table records (compact)
   int32_t n_touch;          // touched-list length (dense) or table capacity (compact)
@@ -185,8 +184,14 @@ hipError_t launch_batch_plan_self(hipStream_t s, const BatchArgs& a, int grid_se
 hipError_t launch_batch_scatter(hipStream_t s, const BatchArgs& a, int grid_scatter,
                                 bool compact, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 hipError_t launch_batch_round_end(hipStream_t s, const BatchArgs& a);
-hipError_t launch_batch_sweep(hipStream_t s, const BatchArgs& a, int nseg, int64_t max_elems,
-                              int grid, bool compact);
+// What the host knows of a sweep: its segments, their elements together and
+// of the largest, and the sort's tiles and items (sort.h).
+struct SweepShape {
+  int nseg = 0, tiles = 0, items = 0;
+  long long elems = 0, max_elem = 0;
+};
+hipError_t launch_batch_sweep(hipStream_t s, const BatchArgs& a, const SweepShape& sh, int grid,
+                              bool compact);
 // compact layout: clear table blocks (records and p), move grown tables,
 // set the slots' hold flags (holds[i] = slot | flag << 16)
 hipError_t launch_table_clear(hipStream_t s, const ClearJob* jobs, int count, long long total,

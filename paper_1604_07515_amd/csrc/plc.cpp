@@ -2047,6 +2047,7 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
     }
   }
   // 3. sweep the queries whose frontier emptied in an earlier step
+  plc::SweepShape shp;
   int nseg = 0;
   long long total = 0, touch_total = 0, vol_bound = 0;
   E.sweeping.clear();
@@ -2070,11 +2071,15 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
     sg.slot = q;
     sg.n_elem = (int32_t)N;
     sg.elem_off = total;
+    sg.tile0 = shp.tiles;
+    sg.item0 = shp.items;
+    shp.tiles += plc::sort_seg_tiles((int)N);
+    shp.items += N <= plc::kSegMaxCount ? plc::sort_seg_items((int)N) : 0;
+    shp.max_elem = std::max(shp.max_elem, N);
     // finish entries: the touched list (dense) or every table record (compact)
     const long long F = E.compact ? (long long)E.qcap[q] : T;
     sg.touch_off = touch_total;
     sg.n_touch = (int32_t)F;
-    sg.pad = 0;
     if (res.block) {
       char* b = static_cast<char*>(res.block);
       res.ids = reinterpret_cast<int32_t*>(b);
@@ -2096,6 +2101,8 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
     nseg++;
   }
   if (nseg > 0) {
+    shp.nseg = nseg;
+    shp.elems = total;
     E.hdr_h->nseg = nseg;
     E.hdr_h->total = (int32_t)total;
     E.hdr_h->touch_total = touch_total;
@@ -2107,8 +2114,7 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
       HIPCHK(ctx, ev_pair(ctx->ev_sweep));
       HIPCHK(ctx, hipEventRecord(ctx->ev_sweep.a, s));
     }
-    HIPCHK(ctx, plc::launch_batch_sweep(s, a, nseg, total, shape(g->batch_sweep, ctx->grid_sweep),
-                                        E.compact));
+    HIPCHK(ctx, plc::launch_batch_sweep(s, a, shp, gw, E.compact));
     if (ctx->timing) HIPCHK(ctx, hipEventRecord(ctx->ev_sweep.b, s));
   }
   // 4. read back and wait

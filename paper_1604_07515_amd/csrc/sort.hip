@@ -22,7 +22,9 @@
 // thousand vertices is on several CUs, and replace the merge passes with one
 // launch: each element's place is its position in its own tile plus its
 // count in every other tile, found by binary searches in tiles held in LDS,
-// and the last of those additions places it.
+// and the last of those additions places it.  Many segments of at most so
+// many elements each (launch_seg_sort) are sorted the same way, every segment
+// within its own range of the buffer.
 //
 // The block-sort launch can carry a side job (SortArgs::side_ids) for its
 // workgroups that hold no tile: with supports of a few tiles most of the
@@ -263,21 +265,65 @@ struct __align__(16) RankElem {
 __device__ __forceinline__ RankElem rank_elem(const SortElem e) {
   return RankElem{__longlong_as_double((long long)~e.key), e.id, e.seg};
 }
-// SEG: several segments (the plain path has one).
-template <bool SEG>
+// No segment in it: the elements compared are of one segment.
 __device__ __forceinline__ bool rank_lt(const RankElem a, const RankElem b) {
-  const bool r = (a.ratio > b.ratio) | ((a.ratio == b.ratio) & (a.id < b.id));
-  return SEG ? (a.seg < b.seg) | ((a.seg == b.seg) & r) : r;
+  return (a.ratio > b.ratio) | ((a.ratio == b.ratio) & (a.id < b.id));
 }
 
-// Tile sort: pairs, then runs of L merge into runs of 2 L by rank: an
+// Sorts src[0 .. len) into dst (which may be src) and writes every element's
+// place to rank: pairs, then runs of L merge into runs of 2 L by rank: an
 // element's place is its position plus its count in the sibling run, a
 // branch-free binary search in LDS (a merge-path round of the block sort
-// takes as many LDS round trips, and then one per output).  Runs past the
-// count are left unmerged.  On R-MAT 2^22 queries (30,000 elements, the side
+// takes as many LDS round trips, and then one per output).
+__device__ void tile_sort(const SortElem* src, SortElem* dst, unsigned long long* rank, int len,
+                          RankElem (*sh)[kTileR]) {
+  const int t = threadIdx.x;
+  static_assert(kTileR == 2 * kTSBlk, "two elements per thread");
+  {
+    const int i = 2 * t;
+    RankElem a{-1.0, i, INT32_MAX}, b{-1.0, i + 1, INT32_MAX};
+    if (i < len) a = rank_elem(src[i]);
+    if (i + 1 < len) b = rank_elem(src[i + 1]);
+    const bool sw = rank_lt(b, a);
+    sh[0][sw ? i + 1 : i] = a;
+    sh[0][sw ? i : i + 1] = b;
+  }
+  __syncthreads();
+  int cur = 0;
+  for (int L = 2; L < len; L <<= 1, cur ^= 1) {
+    const RankElem* in = sh[cur];
+    RankElem* out = sh[cur ^ 1];
+    const RankElem x0 = in[t], x1 = in[t + kTSBlk];
+    const RankElem* s0 = in + ((t & ~(L - 1)) ^ L);
+    const RankElem* s1 = in + (((t + kTSBlk) & ~(L - 1)) ^ L);
+    int c0 = 0, c1 = 0;
+    for (int h = L >> 1; h > 0; h >>= 1) {
+      const RankElem y0 = s0[c0 + h - 1], y1 = s1[c1 + h - 1];
+      c0 += rank_lt(y0, x0) ? h : 0;
+      c1 += rank_lt(y1, x1) ? h : 0;
+    }
+    c0 += rank_lt(s0[c0], x0) ? 1 : 0;
+    c1 += rank_lt(s1[c1], x1) ? 1 : 0;
+    out[(t & ~(2 * L - 1)) + (t & (L - 1)) + c0] = x0;
+    out[((t + kTSBlk) & ~(2 * L - 1)) + (t & (L - 1)) + c1] = x1;
+    __syncthreads();
+  }
+  static_assert((kTSBlk & (kTSBlk - 1)) == 0, "t and t + kTSBlk agree below a run's length");
+#pragma unroll
+  for (int k = 0; k < 2; k++) {
+    const int i = k * kTSBlk + t;
+    if (i < len) {
+      const RankElem e = sh[cur][i];
+      dst[i] = SortElem{~(unsigned long long)__double_as_longlong(e.ratio), e.id, e.seg};
+      rank[i] = (unsigned long long)i;
+    }
+  }
+  __syncthreads();
+}
+
+// Tiles of one segment.  On R-MAT 2^22 queries (30,000 elements, the side
 // job beside it) 13.7 us where the block sort of 4096-element tiles took 32,
 // which it took for 100 elements too (now 3.9).
-template <bool SEG>
 __global__ __launch_bounds__(kTSBlk) void k_tile_sort(SortArgs s) {
   const int N = *s.count;
   if (!sort_enabled(s)) return;
@@ -285,54 +331,47 @@ __global__ __launch_bounds__(kTSBlk) void k_tile_sort(SortArgs s) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *s.flip = N > kTileR;
   __shared__ RankElem sh[2][kTileR];
   const int ntiles = (N + kTileR - 1) / kTileR;
-  const int t = threadIdx.x;
-  static_assert(kTileR == 2 * kTSBlk, "two elements per thread");
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int base = tile * kTileR;
-    const int len = N - base < kTileR ? N - base : kTileR;
-    {
-      const int i = 2 * t;
-      RankElem a{-1.0, i, INT32_MAX}, b{-1.0, i + 1, INT32_MAX};
-      if (i < len) a = rank_elem(buf[base + i]);
-      if (i + 1 < len) b = rank_elem(buf[base + i + 1]);
-      const bool sw = rank_lt<SEG>(b, a);
-      sh[0][sw ? i + 1 : i] = a;
-      sh[0][sw ? i : i + 1] = b;
-    }
-    __syncthreads();
-    int cur = 0;
-    for (int L = 2; L < len; L <<= 1, cur ^= 1) {
-      const RankElem* src = sh[cur];
-      RankElem* dst = sh[cur ^ 1];
-      const RankElem x0 = src[t], x1 = src[t + kTSBlk];
-      const RankElem* s0 = src + ((t & ~(L - 1)) ^ L);
-      const RankElem* s1 = src + (((t + kTSBlk) & ~(L - 1)) ^ L);
-      int c0 = 0, c1 = 0;
-      for (int h = L >> 1; h > 0; h >>= 1) {
-        const RankElem y0 = s0[c0 + h - 1], y1 = s1[c1 + h - 1];
-        c0 += rank_lt<SEG>(y0, x0) ? h : 0;
-        c1 += rank_lt<SEG>(y1, x1) ? h : 0;
-      }
-      c0 += rank_lt<SEG>(s0[c0], x0) ? 1 : 0;
-      c1 += rank_lt<SEG>(s1[c1], x1) ? 1 : 0;
-      dst[(t & ~(2 * L - 1)) + (t & (L - 1)) + c0] = x0;
-      dst[((t + kTSBlk) & ~(2 * L - 1)) + (t & (L - 1)) + c1] = x1;
-      __syncthreads();
-    }
-    static_assert((kTSBlk & (kTSBlk - 1)) == 0, "t and t + kTSBlk agree below a run's length");
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-      const int i = k * kTSBlk + t;
-      if (i < len) {
-        const RankElem e = sh[cur][i];
-        buf[base + i] =
-            SortElem{~(unsigned long long)__double_as_longlong(e.ratio), e.id, e.seg};
-        s.rank[base + i] = (unsigned long long)i;
-      }
-    }
-    __syncthreads();
+    tile_sort(buf + base, buf + base, s.rank + base, N - base < kTileR ? N - base : kTileR, sh);
   }
   if (s.side_ids != nullptr) side_job<kTSBlk>(s, ntiles);
+}
+
+// How many elements of the len in sh (sorted tiles of kTileR) come before x,
+// tile `own` left out: one search per tile, in flight together.
+__device__ __forceinline__ int rank_in(const RankElem* sh, int len, int own, const RankElem x) {
+  int n[kRankTiles], c[kRankTiles];
+#pragma unroll
+  for (int k = 0; k < kRankTiles; k++) {
+    const int r = len - k * kTileR;
+    n[k] = k == own ? 0 : r < kTileR ? r : kTileR;  // (<= 0: nothing to count)
+    c[k] = 0;
+  }
+  for (int h = kTileR; h > 0; h >>= 1) {
+#pragma unroll
+    for (int k = 0; k < kRankTiles; k++) {
+      const int at = c[k] + h - 1;
+      const RankElem y = sh[k * kTileR + (at < n[k] ? at : 0)];
+      c[k] += (at < n[k]) & rank_lt(y, x) ? h : 0;
+    }
+  }
+  int lo = 0;
+#pragma unroll
+  for (int k = 0; k < kRankTiles; k++) lo += c[k];
+  return lo;
+}
+
+// Adds group's count lo to element q's rank and places it at dst once the
+// counts of all groups are in (q0: its position in its own tile).
+__device__ __forceinline__ void rank_add(SortElem* dst, unsigned long long* rank, int groups,
+                                         int q0, int lo, const SortElem e) {
+  if (groups == 1) {
+    dst[q0 + lo] = e;
+    return;
+  }
+  const unsigned long long old = atomicAdd(rank, (1ull << 32) | (unsigned long long)lo);
+  if ((int)(old >> 32) == groups - 1) dst[(long long)(old & 0xffffffffull) + lo] = e;
 }
 
 // Places every element of the sorted tiles at its rank in the whole order.
@@ -343,14 +382,12 @@ __global__ __launch_bounds__(kTSBlk) void k_tile_sort(SortArgs s) {
 // element's rank word (set by the tile sort to its position in its own tile),
 // whose upper half counts the groups; the addition that completes them
 // writes the element out.
-template <bool SEG>
 __global__ __launch_bounds__(kRankBlk) void k_rank_merge(SortArgs s, int groups_max, int per) {
   const int N = *s.count;
   if (!sort_enabled(s)) return;
   if (N <= kTileR) return;
   const int groups = (N + kRankSpan - 1) / kRankSpan;
   const SortElem* src = s.buf[0];
-  SortElem* dst = s.buf[1];
   __shared__ RankElem sh[kRankSpan];
   const int g = blockIdx.x % per;
   for (int j = blockIdx.x / per; j < groups; j += groups_max) {
@@ -361,51 +398,110 @@ __global__ __launch_bounds__(kRankBlk) void k_rank_merge(SortArgs s, int groups_
     __syncthreads();
     for (int q = g * kRankBlk + threadIdx.x; q < N; q += per * kRankBlk) {
       const SortElem e = src[q];
-      const RankElem x = rank_elem(e);
-      const int own = q / kTileR - j * kRankTiles;
-      int n[kRankTiles], c[kRankTiles];
-#pragma unroll
-      for (int k = 0; k < kRankTiles; k++) {
-        const int r = len - k * kTileR;
-        n[k] = k == own ? 0 : r < kTileR ? r : kTileR;  // (<= 0: nothing to count)
-        c[k] = 0;
-      }
-      for (int h = kTileR; h > 0; h >>= 1) {
-#pragma unroll
-        for (int k = 0; k < kRankTiles; k++) {
-          const int at = c[k] + h - 1;
-          const RankElem y = sh[k * kTileR + (at < n[k] ? at : 0)];
-          c[k] += (at < n[k]) & rank_lt<SEG>(y, x) ? h : 0;
-        }
-      }
-      int lo = 0;
-#pragma unroll
-      for (int k = 0; k < kRankTiles; k++) lo += c[k];
-      if (groups == 1) {
-        dst[(q & (kTileR - 1)) + lo] = e;
-      } else {
-        const unsigned long long old =
-            atomicAdd(&s.rank[q], (1ull << 32) | (unsigned long long)lo);
-        if ((int)(old >> 32) == groups - 1) dst[(long long)(old & 0xffffffffull) + lo] = e;
-      }
+      const int lo = rank_in(sh, len, q / kTileR - j * kRankTiles, rank_elem(e));
+      rank_add(s.buf[1], s.rank + q, groups, q & (kTileR - 1), lo, e);
     }
   }
 }
 
-template <bool SEG>
 static void rank_sort(hipStream_t st, const SortArgs& s, int64_t max_count) {
   // a side job takes the workgroups without a tile: two per CU keep the
   // gather from outlasting the sort
   const int tiles = (int)((max_count + kTileR - 1) / kTileR);
   const int grid = s.side_ids != nullptr ? kSideGrid : tiles;
-  hipLaunchKernelGGL(k_tile_sort<SEG>, dim3(grid), dim3(kTSBlk), 0, st, s);
+  hipLaunchKernelGGL(k_tile_sort, dim3(grid), dim3(kTSBlk), 0, st, s);
   if (tiles <= 1) return;
   // one element per thread while that keeps to kRankGrid workgroups
   const int groups = (int)((max_count + kRankSpan - 1) / kRankSpan);
   const int want = (int)((max_count + kRankBlk - 1) / kRankBlk);
   const int most = kRankGrid / groups;
   const int per = want < most ? want : most;
-  hipLaunchKernelGGL(k_rank_merge<SEG>, dim3(groups * per), dim3(kRankBlk), 0, st, s, groups, per);
+  hipLaunchKernelGGL(k_rank_merge, dim3(groups * per), dim3(kRankBlk), 0, st, s, groups, per);
+}
+
+// ------------------------------------------------------ many small segments
+
+// The segment of tile (or merge item) x: the last one that starts at or
+// before it.  first[] holds every segment's first tile (item); a segment
+// without any shares its number with the next one and is passed over.
+__device__ __forceinline__ int seg_at(const int32_t* first, int nseg, int x) {
+  int lo = 0, hi = nseg - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (first[mid] <= x) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+__device__ __forceinline__ const SortSeg& seg_rec(const SegSort& g, int j) {
+  return *reinterpret_cast<const SortSeg*>(g.seg + (size_t)j * g.stride);
+}
+
+// A sweep's segments are sorted each by itself: their ranges in the buffer are
+// known, so the passes that a sort of the whole buffer needs for the segments'
+// number are not made.  Sweep of 256 queries of R-MAT 2^22 (1.2 M elements):
+// 142 us with the merge where block sort and merge passes took 310.
+__global__ __launch_bounds__(kTSBlk) void k_seg_tile_sort(SortArgs s, SegSort g) {
+  __shared__ RankElem sh[2][kTileR];
+  __shared__ int32_t first[kMaxSortSegs];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *s.flip = 1;
+  for (int j = threadIdx.x; j < g.nseg; j += kTSBlk) first[j] = seg_rec(g, j).tile0;
+  __syncthreads();
+  for (int tile = blockIdx.x; tile < g.tiles; tile += gridDim.x) {
+    const int j = seg_at(first, g.nseg, tile);
+    const SortSeg sg = seg_rec(g, j);
+    const int at = (tile - sg.tile0) * kTileR;
+    const long long base = sg.elem_off + at;
+    const int len = sg.n_elem - at < kTileR ? sg.n_elem - at : kTileR;
+    // a segment of one tile is done, and goes where the others will be
+    tile_sort(s.buf[0] + base, s.buf[sg.n_elem <= kTileR] + base, s.rank + base, len, sh);
+  }
+}
+
+// Item (tile i, group j) of a segment: the elements of its tile i against its
+// tile group j, as in k_rank_merge.
+__global__ __launch_bounds__(kRankBlk) void k_seg_merge(SortArgs s, SegSort g) {
+  __shared__ RankElem sh[kRankSpan];
+  __shared__ int32_t first[kMaxSortSegs];
+  for (int j = threadIdx.x; j < g.nseg; j += kRankBlk) first[j] = seg_rec(g, j).item0;
+  for (int item = blockIdx.x; item < g.items; item += gridDim.x) {
+    __syncthreads();
+    const SortSeg sg = seg_rec(g, seg_at(first, g.nseg, item));
+    const int n = sg.n_elem, r = item - sg.item0;
+    const int tiles = (n + kTileR - 1) / kTileR;
+    const int groups = (tiles + kRankTiles - 1) / kRankTiles;
+    const int i = r / groups, j = r % groups;
+    const SortElem* src = s.buf[0] + sg.elem_off;
+    const int base = j * kRankSpan;
+    const int len = n - base < kRankSpan ? n - base : kRankSpan;
+    for (int x = threadIdx.x; x < len; x += kRankBlk) sh[x] = rank_elem(src[base + x]);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kTileR / kRankBlk; k++) {
+      const int q0 = k * kRankBlk + threadIdx.x, q = i * kTileR + q0;
+      if (q >= n) continue;
+      const SortElem e = src[q];
+      const int lo = rank_in(sh, len, i - j * kRankTiles, rank_elem(e));
+      rank_add(s.buf[1] + sg.elem_off, s.rank + sg.elem_off + q, groups, q0, lo, e);
+    }
+  }
+}
+
+int sort_seg_tiles(int n) { return (n + kTileR - 1) / kTileR; }
+int sort_seg_items(int n) {
+  const int tiles = sort_seg_tiles(n);
+  return tiles > 1 ? tiles * ((tiles + kRankTiles - 1) / kRankTiles) : 0;
+}
+
+hipError_t launch_seg_sort(hipStream_t st, const SortArgs& s, const SegSort& g) {
+  // twice what is resident at once (32 KB and 68 KB of LDS), in strides past it
+  const int cap = 2048;
+  hipLaunchKernelGGL(k_seg_tile_sort, dim3(g.tiles < cap ? g.tiles : cap), dim3(kTSBlk), 0, st,
+                     s, g);
+  if (g.items > 0)
+    hipLaunchKernelGGL(k_seg_merge, dim3(g.items < cap ? g.items : cap), dim3(kRankBlk), 0, st,
+                       s, g);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------ merge passes
@@ -519,7 +615,7 @@ __global__ __launch_bounds__(kSortBlk) void k_merge_pass(SortArgs s, int L, int 
 
 hipError_t launch_sort(hipStream_t st, const SortArgs& s, int64_t max_count, int grid) {
   if (s.rank != nullptr && max_count <= kRankMaxCount) {
-    if (s.segments) rank_sort<true>(st, s, max_count); else rank_sort<false>(st, s, max_count);
+    rank_sort(st, s, max_count);
     return hipGetLastError();
   }
   const int bs_grid = s.side_ids != nullptr && grid < kSideGrid ? kSideGrid : grid;
