@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from dataclasses import dataclass
 
 import numpy as np
@@ -78,12 +79,27 @@ class plc_result_info(C.Structure):
                 ("table_cap", C.c_int64), ("pull_rounds", C.c_int32), ("reserved", C.c_int32)]
 
     def as_dict(self) -> dict:
-        return {k: getattr(self, k) for k in self.names()}
+        return dict(zip(_INFO_NAMES, _INFO_STRUCT.unpack_from(self)))
 
     @classmethod
     def names(cls) -> list:
         """Field names of the info dict (the reserved word left out)."""
-        return [k for k, _ in cls._fields_ if k != "reserved"]
+        return list(_INFO_NAMES)
+
+
+# The record as one struct format: a dict per result in 1 us, where a getattr
+# per field takes 6.
+_INFO_STRUCT = struct.Struct("@" + "".join(
+    {C.c_int32: "i", C.c_uint32: "I", C.c_int64: "q", C.c_double: "d"}[t]
+    for _, t in plc_result_info._fields_))
+_INFO_NAMES = [k for k, _ in plc_result_info._fields_ if k != "reserved"]
+assert _INFO_STRUCT.size == C.sizeof(plc_result_info)
+assert plc_result_info._fields_[-1][0] == "reserved"  # (zip ends before it)
+_QUERY_DTYPE = np.dtype(plc_query)
+
+
+def _info_dicts(infos) -> list:
+    return [dict(zip(_INFO_NAMES, t)) for t in _INFO_STRUCT.iter_unpack(infos)]
 
 
 PLC_TUNE_PLAIN = 1
@@ -306,12 +322,10 @@ class Context:
         eps = np.broadcast_to(np.asarray(eps, np.float64), (k,))
         rule = np.broadcast_to(np.asarray(rule, np.int64), (k,))
         qa = (plc_query * k)()
-        for i in range(k):
-            qa[i].seed = int(seeds[i])
-            qa[i].rule = int(rule[i])
-            qa[i].alpha = float(alpha[i])
-            qa[i].eps = float(eps[i])
-            qa[i].flags = int(flags)
+        if k:
+            q = np.frombuffer(qa, _QUERY_DTYPE)
+            q["seed"], q["rule"], q["alpha"], q["eps"] = seeds, rule, alpha, eps
+            q["flags"] = int(flags) & 0xffffffff
         return qa
 
     def run(self, g: Graph, seeds, alpha, eps, rule=PLC_RULE_OPT, check: bool = True,
@@ -324,7 +338,7 @@ class Context:
         rc = self.lib.plc_run(self.handle, g.handle, qa, k, ids, infos)
         if check and rc not in (PLC_OK,):
             raise PlcError(rc, "plc_run")
-        return list(ids), [x.as_dict() for x in infos]
+        return list(ids), _info_dicts(infos)
 
     def run_set(self, g: Graph, seeds, alpha, eps, rule=PLC_RULE_OPT, check: bool = True):
         """Plain path from a seed set (unit mass split equally over the
@@ -432,7 +446,7 @@ class Context:
         rc = self.lib.plc_run_batched(self.handle, g.handle, qa, k, ids, infos)
         if check and rc != PLC_OK:
             raise PlcError(rc, "plc_run_batched")
-        return list(ids), [x.as_dict() for x in infos]
+        return list(ids), _info_dicts(infos)
 
     def autotune(self, g: Graph, seeds, alpha, eps, which: int, rule=PLC_RULE_OPT) -> dict:
         """Pick launch shapes for graph g from a sample of queries (results discarded)."""

@@ -329,6 +329,22 @@ __global__ void k_b_admit(BatchArgs a, const Admit* adm, int count) {
 
 // ---------------------------------------------------------------- round
 
+// Bookkeeping of a slot's round after its scatter, and the frontier swap.
+__device__ __forceinline__ void b_round_end(Slot& S) {
+  if (S.fbase < 0 || S.status != SL_PUSH) return;
+  S.pushes += S.nf;
+  S.edges += S.round_edges;
+  S.rounds += 1;
+  S.cnt[S.par] = 0;
+  S.edge_next[S.par] = 0;
+  S.par ^= 1;
+  S.fbase = -1;
+  if (S.cnt[S.par] == 0) S.status = SL_PUSHED;
+}
+
+// CLOSES: ends the previous round first, where several rounds run without a
+// read-back between them (one launch of a few us less for each).
+template <bool CLOSES>
 __global__ __launch_bounds__(kMaxSlots) void k_b_plan(BatchArgs a) {
   __shared__ long long sh[kMaxSlots / 64 + 1];
   const int q = threadIdx.x;
@@ -336,6 +352,7 @@ __global__ __launch_bounds__(kMaxSlots) void k_b_plan(BatchArgs a) {
   long long nf = 0, e = 0;
   if (q < a.B) {
     Slot& S = a.slots[q];
+    if (CLOSES) b_round_end(S);
     S.fbase = -1;
     S.nf = 0;
     S.round_edges = 0;
@@ -819,18 +836,7 @@ __global__ __launch_bounds__(kBlock) void k_b_scatter(BatchArgs a) {
 }
 
 __global__ __launch_bounds__(kMaxSlots) void k_b_round_end(BatchArgs a) {
-  const int q = threadIdx.x;
-  if (q >= a.B) return;
-  Slot& S = a.slots[q];
-  if (S.fbase < 0 || S.status != SL_PUSH) return;
-  S.pushes += S.nf;
-  S.edges += S.round_edges;
-  S.rounds += 1;
-  S.cnt[S.par] = 0;
-  S.edge_next[S.par] = 0;
-  S.par ^= 1;
-  S.fbase = -1;
-  if (S.cnt[S.par] == 0) S.status = SL_PUSHED;
+  if ((int)threadIdx.x < a.B) b_round_end(a.slots[threadIdx.x]);
 }
 
 // ---------------------------------------------------------------- compact tables
@@ -962,8 +968,8 @@ __global__ void k_slot_hold(BatchArgs a, const int32_t* holds, int count) {
 template <class St>
 __global__ __launch_bounds__(kBlock) void k_sw_keys(BatchArgs a) {
   BatchCtl* c = a.ctl;
-  const int nseg = c->sw_nseg;
-  const long long total = c->sw_total;
+  const int nseg = a.hdr->nseg;
+  const long long total = a.hdr->total;
   __shared__ long long s_off[kMaxSlots];
   for (int j = threadIdx.x; j < nseg; j += kBlock) s_off[j] = a.segs[j].elem_off;
   if (blockIdx.x == 0 && threadIdx.x == 0) c->sort_flip = 0;
@@ -1042,7 +1048,7 @@ __device__ __forceinline__ void b_scan(const BatchArgs& a, int site_id, long lon
 template <class St>
 __global__ __launch_bounds__(kBlock) void k_sw_vol(BatchArgs a) {
   BatchCtl* c = a.ctl;
-  const long long total = c->sw_total;
+  const long long total = a.hdr->total;
   if (total <= 0) return;
   const SortElem* el = a.sbuf[c->sort_flip & 1];
   b_scan(a, BSCAN_VOL, total,
@@ -1104,7 +1110,7 @@ __global__ __launch_bounds__(kBlock) void k_sw_vol(BatchArgs a) {
 
 // Inclusive prefix of the boundary changes d - 2 * count.
 __global__ __launch_bounds__(kBlock) void k_sw_cut(BatchArgs a) {
-  const long long total = a.ctl->sw_total;
+  const long long total = a.hdr->total;
   if (total <= 0) return;
   b_scan(a, BSCAN_CUT, total,
       [&](long long i0, long long* x) {
@@ -1122,7 +1128,7 @@ __global__ __launch_bounds__(kBlock) void k_sw_cut(BatchArgs a) {
 template <class St>
 __global__ __launch_bounds__(kBlock) void k_sw_count(BatchArgs a) {
   BatchCtl* c = a.ctl;
-  const long long total = c->sw_total;
+  const long long total = a.hdr->total;
   if (total <= 0) return;
   const int ntiles = (int64_t)c->sw_ntiles > a.tile_cap ? (int)a.tile_cap : c->sw_ntiles;
   const long long E = c->sw_etotal;
@@ -1204,9 +1210,8 @@ __device__ __forceinline__ bool b_cand_better(long long oc, long long od, long l
 // threads and a tree of barriers (256 segments), 31 with 1024 and waves.
 constexpr int kArgBlk = 1024;
 __global__ __launch_bounds__(kArgBlk) void k_sw_argmin(BatchArgs a) {
-  BatchCtl* c = a.ctl;
   const int s = blockIdx.x;
-  if (s >= c->sw_nseg) return;
+  if (s >= a.hdr->nseg) return;
   const SweepSeg sg = a.segs[s];
   const long long off = sg.elem_off;
   const long long bv = off > 0 ? a.svol[off - 1] : 0;
@@ -1251,8 +1256,8 @@ __global__ __launch_bounds__(kArgBlk) void k_sw_argmin(BatchArgs a) {
 // touched list, and reset r (p and rank are reset by k_sw_reset).
 __global__ __launch_bounds__(kBlock) void k_sw_finish(BatchArgs a) {
   BatchCtl* c = a.ctl;
-  const int nseg = c->sw_nseg;
-  const long long total = c->sw_touch_total;
+  const int nseg = a.hdr->nseg;
+  const long long total = a.hdr->touch_total;
   // per segment: start in the flattened touched space, its slot's touched
   // list and records, and where its r nonzeros go
   __shared__ long long s_toff[kMaxSlots];
@@ -1330,9 +1335,9 @@ __global__ __launch_bounds__(kBlock) void k_sw_finish(BatchArgs a) {
 // (PLC_QF_NO_RESIDUAL) it only counts.
 __global__ __launch_bounds__(kBlock) void k_sw_gather(BatchArgs a) {
   BatchCtl* c = a.ctl;
-  const int nseg = c->sw_nseg;
+  const int nseg = a.hdr->nseg;
   constexpr int kPer = kScanBlock / 64;  // records per lane
-  const long long nchunk = c->sw_touch_total / kScanBlock;
+  const long long nchunk = a.hdr->touch_total / kScanBlock;
   __shared__ long long s_toff[kMaxSlots];
   for (int j = threadIdx.x; j < nseg; j += kBlock) s_toff[j] = a.segs[j].touch_off;
   __syncthreads();
@@ -1375,7 +1380,7 @@ __global__ __launch_bounds__(kBlock) void k_sw_gather(BatchArgs a) {
 // (after the boundary counts and the argmin no longer need them).
 __global__ __launch_bounds__(kBlock) void k_sw_reset(BatchArgs a) {
   BatchCtl* c = a.ctl;
-  const long long total = c->sw_total;
+  const long long total = a.hdr->total;
   const SortElem* el = a.sbuf[c->sort_flip & 1];
   for (long long k = (long long)blockIdx.x * kBlock + threadIdx.x; k < total;
        k += (long long)gridDim.x * kBlock) {
@@ -1414,8 +1419,12 @@ hipError_t launch_batch_admit(hipStream_t s, const BatchArgs& a, const Admit* ad
   return hipGetLastError();
 }
 
-hipError_t launch_batch_plan_self(hipStream_t s, const BatchArgs& a, int grid_self, bool compact) {
-  hipLaunchKernelGGL(k_b_plan, dim3(1), dim3(kMaxSlots), 0, s, a);
+hipError_t launch_batch_plan_self(hipStream_t s, const BatchArgs& a, int grid_self, bool compact,
+                                  bool closes) {
+  if (closes)
+    hipLaunchKernelGGL(k_b_plan<true>, dim3(1), dim3(kMaxSlots), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_b_plan<false>, dim3(1), dim3(kMaxSlots), 0, s, a);
   if (compact)
     hipLaunchKernelGGL(k_b_self<CompactState>, dim3(grid_self), dim3(kBlock), 0, s, a);
   else
@@ -1453,7 +1462,7 @@ static hipError_t sweep_kernels(hipStream_t s, const BatchArgs& a, const SweepSh
   SortArgs sa;
   sa.buf[0] = a.sbuf[0];
   sa.buf[1] = a.sbuf[1];
-  sa.count = &a.ctl->sw_total;
+  sa.count = &a.hdr->total;
   sa.flip = &a.ctl->sort_flip;
   sa.active = nullptr;
   sa.active_value = 0;

@@ -83,6 +83,13 @@ struct __align__(16) SweepSeg : SortSeg {
   double* out_rval;
 };
 
+// A sweep as a whole (written by the host before it).
+struct __align__(16) SweepHdr {
+  int32_t nseg;             // segments
+  int32_t total;            // elements
+  long long touch_total;    // finish entries
+};
+
 enum : int32_t { BSCAN_FRONTIER = 0, BSCAN_VOL = 1, BSCAN_CUT = 2, BNUM_SCANS = 3 };
 
 struct __align__(64) BatchCtl {
@@ -91,9 +98,6 @@ struct __align__(64) BatchCtl {
   long long e_total;        // edges this round (or sweep volume)
   int32_t fault;
   int32_t sort_flip;
-  int32_t sw_nseg;          // sweep: segments
-  int32_t sw_total;         // sweep: elements
-  long long sw_touch_total; // sweep: finish entries
   long long sw_etotal;      // sweep: volume of all swept supports
   int32_t sw_ntiles;        // sweep: edge tiles
   int32_t pad0;
@@ -123,8 +127,9 @@ struct BatchArgs {
   int64_t tile_cap;
   unsigned long long* desc[BNUM_SCANS];
   int32_t desc_cap;
-  // sweep buffers
-  SweepSeg* segs;           // [B]
+  // sweep plan (of this sweep only) and buffers
+  const SweepHdr* hdr;
+  const SweepSeg* segs;     // [hdr->nseg]
   SortElem* sbuf[2];        // [s_cap]
   int32_t* sdeg;            // [s_cap]
   int64_t* svol;            // [s_cap]
@@ -178,7 +183,9 @@ hipError_t launch_batch_init(hipStream_t s, const BatchArgs& a);      // dense l
 hipError_t launch_gdh_init(hipStream_t s, const BatchArgs& a, int2* gdh);  // compact layout
 hipError_t launch_batch_admit(hipStream_t s, const BatchArgs& a, const Admit* adm, int count,
                               bool compact);
-hipError_t launch_batch_plan_self(hipStream_t s, const BatchArgs& a, int grid_self, bool compact);
+// closes: the previous round's end first (it has no k_b_round_end of its own)
+hipError_t launch_batch_plan_self(hipStream_t s, const BatchArgs& a, int grid_self, bool compact,
+                                  bool closes = false);
 // With t0 set: launched with start and stop events on its own dispatch
 // timestamps (hipExtLaunchKernelGGL); not for graph capture.
 hipError_t launch_batch_scatter(hipStream_t s, const BatchArgs& a, int grid_scatter,

@@ -27,6 +27,7 @@
 #include <map>
 #include <new>
 #include <set>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -83,23 +84,19 @@ struct KTime {
 
 enum { HS_FREE = 0, HS_RUN = 1, HS_PUSHED = 2, HS_SWEEP = 3 };
 
-struct SweepHdr {
-  int32_t nseg;
-  int32_t total;
-  long long touch_total;
-};
-
 // Host side of a graph's batch engine.
 struct BatchEngine {
   int B = 0;
   plc::BatchArgs args{};
   std::vector<void*> blocks;
-  plc::Slot* slots_h = nullptr;      // pinned mirror of the slot array
-  plc::SweepSeg* segs_h = nullptr;   // pinned sweep plan
-  plc::Admit* adm_h = nullptr;       // pinned admission list
-  plc::Admit* adm_d = nullptr;       // device admission list
-  plc::BatchCtl* ctl_h = nullptr;    // pinned mirror of the control block
-  SweepHdr* hdr_h = nullptr;         // pinned sweep header
+  // control block and slot array: one block, one read-back a step
+  plc::BatchCtl* ctl_h = nullptr;    // pinned mirror of the block
+  plc::Slot* slots_h = nullptr;      // its slot array
+  // what the host tells the device in a step, packed into one upload
+  char* up_h = nullptr;              // pinned
+  char* up_d = nullptr;
+  std::vector<plc::Admit> adm;
+  std::vector<plc::SweepSeg> segs;
   std::vector<int> state;            // HS_*
   std::vector<uint64_t> qid;
   std::vector<int> qbucket;          // compact: hint bucket of the slot's query
@@ -108,6 +105,7 @@ struct BatchEngine {
   std::deque<std::pair<uint64_t, plc_query>> queue;
   size_t bytes = 0;
   Captured round_g;                  // one round: plan, self, scatter, round end
+  Captured chain_g;                  // kBatchChain rounds
   bool compact = false;              // PLC_STATE_COMPACT
   // dense layout: the slots' lists, slices of q*n (frontiers: (2q+k)*n)
   int32_t* d_fbuf = nullptr;
@@ -120,12 +118,9 @@ struct BatchEngine {
   std::vector<int64_t> qbound;       // touched bound of the slot's query
   std::vector<int> hold;             // hold flag last sent to the device
   std::vector<char> fresh;           // admitted this step: slots_h not read back yet
-  plc::Grow* grow_h = nullptr;       // pinned grow records
-  plc::Grow* grow_d = nullptr;
-  int32_t* holds_h = nullptr;        // pinned hold updates
-  int32_t* holds_d = nullptr;
-  plc::ClearJob* clear_h = nullptr;  // pinned table clears of one step (2B)
-  plc::ClearJob* clear_d = nullptr;
+  std::vector<plc::Grow> grow;
+  std::vector<int32_t> holds;
+  std::vector<plc::ClearJob> clear;  // table clears of one step (2B at most)
   // compact layout: running mean of the final touched count of finished
   // queries, per quarter decade of the work-bound scale 1/(alpha' eps); a
   // new query's first table is sized for it (fewer growth steps)
@@ -338,8 +333,9 @@ static void graph_release_blocks(plc_ctx* ctx, plc_graph* g) {
 // kDenseArcs arcs and kDenseRows rows, and rows times the longest row stays
 // within kDenseSpan (no lane sums more than kDenseSpan / 256 products of a
 // row); a longer row is cut into pieces of kDenseArcs arcs.
+// No blocks (and no dense rounds) when the host has no memory for them.
 static void dense_blocks(const std::vector<int64_t>& off, std::vector<plc::DenseBlk>* out,
-                         int32_t* nlong) {
+                         int32_t* nlong) try {
   const int64_t n = (int64_t)off.size() - 1;
   *nlong = 0;
   for (int64_t v = 0; v < n;) {
@@ -370,6 +366,9 @@ static void dense_blocks(const std::vector<int64_t>& off, std::vector<plc::Dense
                                    (long long)off[v]});
     v = w;
   }
+} catch (const std::bad_alloc&) {
+  out->clear();
+  *nlong = 0;
 }
 
 extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
@@ -397,6 +396,26 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
     if (d < 0 || d >= INT32_MAX) return PLC_E_INVALID;
     deg[v] = (int32_t)d;
     maxdeg = std::max(maxdeg, d);
+  }
+  // The dense round's blocks of rows (see dense_blocks) are laid out beside
+  // the other host passes over the graph.
+  const bool bins_on = ctx->opt.bin_min_edges >= 0 &&
+                       n <= plc::kBinMaxVertices;
+  std::vector<plc::DenseBlk> dblk;
+  int32_t nlong = 0;
+  std::thread dense_th;
+  struct Join {
+    std::thread& t;
+    void operator()() { if (t.joinable()) t.join(); }
+    ~Join() { (*this)(); }
+  } dense_join{dense_th};
+  if (bins_on) {
+    auto lay_out = [&]() { dense_blocks(off, &dblk, &nlong); };
+    try {
+      dense_th = std::thread(lay_out);
+    } catch (const std::system_error&) {
+      lay_out();
+    }
   }
   // Neighbour ids index per-vertex arrays on the device: always range-checked.
   {
@@ -475,8 +494,6 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
   std::vector<int32_t> bin_of_blk, bin_lo;
   std::vector<long long> bin_vol;
   const int64_t nblk = (n + plc::kBinGran - 1) / plc::kBinGran;
-  const bool bins_on = ctx->opt.bin_min_edges >= 0 &&
-                       n <= plc::kBinMaxVertices;
   static_assert(plc::kBinMaxVertices / plc::kBinWidth <= plc::kMaxBins * 3 / 4,
                 "the width bound alone leaves room for the volume bins");
   if (bins_on) {
@@ -522,10 +539,8 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
   // Dense rounds (same graphs and option): the two coefficient arrays
   // (cleared by the graph init kernel) and the blocks of rows.  Without room
   // for the blocks the graph does without the form.
-  std::vector<plc::DenseBlk> dblk;
-  int32_t nlong = 0;
+  dense_join();
   if (bins_on) {
-    dense_blocks(off, &dblk, &nlong);
     double* cd = static_cast<double*>(take(16 * N));
     void* blk = nullptr;
     const size_t acc_at = (sizeof(plc::DenseBlk) * dblk.size() + 255) & ~(size_t)255;
@@ -1515,19 +1530,23 @@ static void batch_free(plc_ctx* ctx, plc_graph* g) {
   for (int q = 0; q < E->B; q++)
     if (E->state[q] != HS_FREE) ctx->inflight.erase(E->qid[q]);
   for (auto& pq : E->queue) ctx->inflight.erase(pq.first);
-  if (E->slots_h) (void)hipHostFree(E->slots_h);
-  if (E->segs_h) (void)hipHostFree(E->segs_h);
-  if (E->adm_h) (void)hipHostFree(E->adm_h);
   if (E->ctl_h) (void)hipHostFree(E->ctl_h);
-  if (E->hdr_h) (void)hipHostFree(E->hdr_h);
-  if (E->grow_h) (void)hipHostFree(E->grow_h);
-  if (E->holds_h) (void)hipHostFree(E->holds_h);
-  if (E->clear_h) (void)hipHostFree(E->clear_h);
+  if (E->up_h) (void)hipHostFree(E->up_h);
   for (void* b : E->qblock)
     if (b) ctx->arena.release(b);
   captured_free(E->round_g);
+  captured_free(E->chain_g);
   delete E;
   g->batch = nullptr;
+}
+
+// Slots behind the control block in their common block, and the upload of a
+// step: every list at its longest, each at a multiple of 64 bytes.
+constexpr size_t kSlotsAt = (sizeof(plc::BatchCtl) + 255) & ~(size_t)255;
+static size_t batch_up_bytes(int B) {
+  return 6 * 64 + sizeof(plc::SweepHdr) +
+         (sizeof(plc::SweepSeg) + sizeof(plc::Admit) + sizeof(plc::Grow) +
+          2 * sizeof(plc::ClearJob) + 4) * (size_t)B;
 }
 
 // Round-buffer and sweep-buffer capacities (entries, edges, sort elements).
@@ -1552,8 +1571,7 @@ static size_t batch_fixed_bytes(const plc_graph* g, int B) {
   size_t b = 0;
   b += 28 * (size_t)nf_cap + 4 * (size_t)tile_cap + 3 * 16 * (size_t)desc_cap;
   b += (2 * sizeof(plc::SortElem) + 4 + 8 + 4 + 8) * (size_t)s_cap;
-  b += (sizeof(plc::Slot) + sizeof(plc::SweepSeg) + sizeof(plc::Admit) + sizeof(plc::Grow) +
-        2 * sizeof(plc::ClearJob) + 12) * (size_t)B;
+  b += (sizeof(plc::Slot) + 8) * (size_t)B + batch_up_bytes(B);
   b += 8 * (size_t)g->n + 64 * 1024;  // compact: graph-wide {d, hot code}
   return b;
 }
@@ -1630,7 +1648,10 @@ static plc_status batch_create(plc_ctx* ctx, plc_graph* g, int B) {
   a.hotcode = g->args.hotcode;
   a.B = B;
   E->compact = ctx->opt.batch_state == PLC_STATE_COMPACT;
-  a.slots = static_cast<plc::Slot*>(take(sizeof(plc::Slot) * B));
+  const size_t back_bytes = kSlotsAt + sizeof(plc::Slot) * (size_t)B;
+  char* const back = static_cast<char*>(take(back_bytes));
+  a.ctl = reinterpret_cast<plc::BatchCtl*>(back);
+  a.slots = reinterpret_cast<plc::Slot*>(back + kSlotsAt);
   if (E->compact) {
     a.vr = nullptr;
     a.p = nullptr;
@@ -1643,10 +1664,7 @@ static plc_status batch_create(plc_ctx* ctx, plc_graph* g, int B) {
     E->d_touched = static_cast<int32_t*>(take(4 * n * B));
     a.gdh = nullptr;
   }
-  E->grow_d = static_cast<plc::Grow*>(take(sizeof(plc::Grow) * B));
-  E->holds_d = static_cast<int32_t*>(take(4 * (size_t)B));
-  E->clear_d = static_cast<plc::ClearJob*>(take(sizeof(plc::ClearJob) * 2 * (size_t)B));
-  a.ctl = static_cast<plc::BatchCtl*>(take(sizeof(plc::BatchCtl)));
+  E->up_d = static_cast<char*>(take(batch_up_bytes(B)));
   a.fprefix = static_cast<int32_t*>(take(4 * ((size_t)B + 1)));
   a.eslot = static_cast<int32_t*>(take(4 * (size_t)nf_cap));
   a.coef = static_cast<double*>(take(8 * (size_t)nf_cap));
@@ -1659,7 +1677,6 @@ static plc_status batch_create(plc_ctx* ctx, plc_graph* g, int B) {
   a.desc_cap = (int32_t)desc_cap;
   for (int k = 0; k < plc::BNUM_SCANS; k++)
     a.desc[k] = static_cast<unsigned long long*>(take(2 * 8 * (size_t)desc_cap));
-  a.segs = static_cast<plc::SweepSeg*>(take(sizeof(plc::SweepSeg) * B));
   a.sbuf[0] = static_cast<plc::SortElem*>(take(sizeof(plc::SortElem) * (size_t)s_cap));
   a.sbuf[1] = static_cast<plc::SortElem*>(take(sizeof(plc::SortElem) * (size_t)s_cap));
   a.sdeg = static_cast<int32_t*>(take(4 * (size_t)s_cap));
@@ -1667,7 +1684,6 @@ static plc_status batch_create(plc_ctx* ctx, plc_graph* g, int B) {
   a.scnt = static_cast<int32_t*>(take(4 * (size_t)s_cap));
   a.scut = static_cast<int64_t*>(take(8 * (size_t)s_cap));
   a.s_cap = s_cap;
-  E->adm_d = static_cast<plc::Admit*>(take(sizeof(plc::Admit) * B));
   if (nomem) {
     batch_free(ctx, g);
     return PLC_E_NOMEM;
@@ -1682,29 +1698,22 @@ static plc_status batch_create(plc_ctx* ctx, plc_graph* g, int B) {
   E->qbound.assign(B, 0);
   E->hold.assign(B, 0);
   E->fresh.assign(B, 0);
-  if (hipHostMalloc(reinterpret_cast<void**>(&E->slots_h), sizeof(plc::Slot) * B,
-                    hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&E->segs_h), sizeof(plc::SweepSeg) * B,
-                    hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&E->adm_h), sizeof(plc::Admit) * B,
-                    hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&E->ctl_h), sizeof(plc::BatchCtl),
-                    hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&E->hdr_h), sizeof(SweepHdr),
-                    hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&E->grow_h), sizeof(plc::Grow) * B,
-                    hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&E->holds_h), 4 * (size_t)B,
-                    hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&E->clear_h), sizeof(plc::ClearJob) * 2 * (size_t)B,
+  E->adm.resize(B);
+  E->segs.resize(B);
+  E->grow.resize(B);
+  E->holds.resize(B);
+  E->clear.resize(2 * (size_t)B);
+  if (hipHostMalloc(reinterpret_cast<void**>(&E->ctl_h), back_bytes, hipHostMallocDefault) !=
+          hipSuccess ||
+      hipHostMalloc(reinterpret_cast<void**>(&E->up_h), batch_up_bytes(B),
                     hipHostMallocDefault) != hipSuccess) {
     batch_free(ctx, g);
     ctx->broken = true;
     return PLC_E_HIP;
   }
+  E->slots_h = reinterpret_cast<plc::Slot*>(reinterpret_cast<char*>(E->ctl_h) + kSlotsAt);
   hipStream_t s = ctx->stream;
-  HIPCHK(ctx, hipMemsetAsync(a.slots, 0, sizeof(plc::Slot) * B, s));
-  HIPCHK(ctx, hipMemsetAsync(a.ctl, 0, sizeof(plc::BatchCtl), s));
+  HIPCHK(ctx, hipMemsetAsync(back, 0, back_bytes, s));
   for (int k = 0; k < plc::BNUM_SCANS; k++)
     HIPCHK(ctx, hipMemsetAsync(a.desc[k], 0, 2 * 8 * (size_t)desc_cap, s));
   if (E->compact)
@@ -1768,29 +1777,33 @@ extern "C" plc_status plc_submit(plc_ctx* ctx, plc_graph* g, const plc_query* q,
   return first;
 }
 
-// Graph of one batched round: plan, self, scatter, round end.
-static Captured* batch_round_graph(plc_ctx* ctx, plc_graph* g) {
+constexpr int kBatchChain = 4;  // rounds per read-back, dense throughput mode
+
+// Graph of 1 or kBatchChain batched rounds: plan, self and scatter of each
+// (the plan ends the round before), and the last one's end.
+static Captured* batch_round_graph(plc_ctx* ctx, plc_graph* g, int rounds) {
   const int gs = shape(g->batch_self, ctx->grid_self);
   const int gc = shape(g->batch_scatter, ctx->grid_scatter);
-  Captured& c = g->batch->round_g;
-  if (c.matches(gs, gc, 0, 1)) return &c;
+  Captured& c = rounds > 1 ? g->batch->chain_g : g->batch->round_g;
+  if (c.matches(gs, gc, 0, rounds)) return &c;
   captured_free(c);
   c.gs = gs;
   c.gc = gc;
   c.gw = 0;
-  c.rounds = 1;
+  c.rounds = rounds;
   const plc::BatchArgs& a = g->batch->args;
   const bool compact = g->batch->compact;
   const bool ok = capture(ctx, c, [&](hipStream_t cs) -> hipError_t {
     hipError_t r;
-    if ((r = plc::launch_batch_plan_self(cs, a, gs, compact)) != hipSuccess) return r;
-    if ((r = plc::launch_batch_scatter(cs, a, gc, compact)) != hipSuccess) return r;
+    for (int i = 0; i < rounds; i++) {
+      if ((r = plc::launch_batch_plan_self(cs, a, gs, compact, i > 0)) != hipSuccess) return r;
+      if ((r = plc::launch_batch_scatter(cs, a, gc, compact)) != hipSuccess) return r;
+    }
     return plc::launch_batch_round_end(cs, a);
   });
   return ok ? &c : nullptr;
 }
 
-constexpr int kBatchChain = 4;  // rounds per read-back, dense throughput mode
 
 // One global step.  defer_sweep: while other queries are still pushing and
 // none waits for a slot, leave finished queries unswept so that they are
@@ -1798,7 +1811,7 @@ constexpr int kBatchChain = 4;  // rounds per read-back, dense throughput mode
 static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uint64_t* done_ids,
                              int32_t done_cap, int32_t* n_done, bool defer_sweep) {
   BatchEngine& E = *g->batch;
-  plc::BatchArgs& a = E.args;
+  plc::BatchArgs a = E.args;  // (with this step's sweep plan)
   hipStream_t s = ctx->stream;
   // 1. admission into free slots, in submission order (compact layout: while
   // the arena holds the query's first table and the result headroom)
@@ -1809,7 +1822,7 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
     if (E.state[q] != HS_FREE) continue;
     const uint64_t id = E.queue.front().first;
     const plc_query qq = E.queue.front().second;
-    plc::Admit& ad = E.adm_h[nadm];
+    plc::Admit& ad = E.adm[nadm];
     if (E.compact) {
       int64_t expect = 1;
       const int64_t bound = touched_bound(g, qq);
@@ -1841,7 +1854,7 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
       ad.touched = lists + 3 * L;
       ad.tcap = (int32_t)cap;
       ad.list_cap = (int32_t)L;
-      plc::ClearJob& J = E.clear_h[njobs++];
+      plc::ClearJob& J = E.clear[njobs++];
       J.tab = ad.tab;
       J.tp = ad.tp;
       J.cap = cap;
@@ -1880,11 +1893,10 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
   // 1b. compact layout: grow every table that this round could fill past
   // half (new keys this round <= the frontier's edge count); a query whose
   // table cannot grow now sits the round out
-  int nfail = 0, ngrow = 0;
+  int nfail = 0, ngrow = 0, nhold = 0;
   long long total_old = 0, total_list = 0;
   std::vector<void*> old_blocks;
   if (E.compact) {
-    int nhold = 0;
     for (int q = 0; q < E.B; q++) {
       if (E.state[q] != HS_RUN || E.fresh[q]) continue;
       const plc::Slot& S = E.slots_h[q];
@@ -1893,7 +1905,7 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
       const int64_t worst = std::min<int64_t>(E.qbound[q], occ + S.edge_next[S.par]);
       if (!table_needs_growth(E.qcap[q], occ, worst)) {
         if (E.hold[q]) {
-          E.holds_h[nhold++] = q;
+          E.holds[nhold++] = q;
           E.hold[q] = 0;
         }
         continue;
@@ -1904,14 +1916,14 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
                       ? ctx->arena.alloc(bytes) : nullptr;
       if (!blk) {
         if (!E.hold[q]) {
-          E.holds_h[nhold++] = q | (1 << 16);
+          E.holds[nhold++] = q | (1 << 16);
           E.hold[q] = 1;
         }
         continue;
       }
       char* b = static_cast<char*>(blk);
       const int64_t L = table_list_cap(cap);
-      plc::Grow& G = E.grow_h[ngrow++];
+      plc::Grow& G = E.grow[ngrow++];
       G.slot = q;
       G.old_cap = (int32_t)E.qcap[q];
       G.new_cap = (int32_t)cap;
@@ -1930,7 +1942,7 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
       G.fb1 = lists + L;
       G.support = lists + 2 * L;
       G.touched = lists + 3 * L;
-      plc::ClearJob& J = E.clear_h[njobs++];
+      plc::ClearJob& J = E.clear[njobs++];
       J.tab = G.tab;
       J.tp = G.tp;
       J.cap = cap;
@@ -1942,11 +1954,6 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
       E.qcap[q] = cap;
       E.qgrows[q]++;
       E.hold[q] = 0;  // k_c_move_lists clears the device flag
-    }
-    if (nhold > 0) {
-      HIPCHK(ctx, hipMemcpyAsync(E.holds_d, E.holds_h, 4 * (size_t)nhold, hipMemcpyHostToDevice,
-                                 s));
-      HIPCHK(ctx, plc::launch_slot_hold(s, a, E.holds_d, nhold));
     }
     // Every running query held and none left to sweep or admitted: nothing
     // would ever free memory, so the held query that needs the most fails.
@@ -1997,56 +2004,9 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
       E.qid[worst] = 0;
     }
   }
-  // 1c. clear new tables, admit, move grown tables (in this order)
-  const int gw = shape(g->batch_sweep, ctx->grid_sweep);
-  if (njobs > 0) {
-    HIPCHK(ctx, hipMemcpyAsync(E.clear_d, E.clear_h, sizeof(plc::ClearJob) * njobs,
-                               hipMemcpyHostToDevice, s));
-    HIPCHK(ctx, plc::launch_table_clear(s, E.clear_d, njobs, clear_total, gw));
-  }
-  if (nadm > 0) {
-    HIPCHK(ctx, hipMemcpyAsync(E.adm_d, E.adm_h, sizeof(plc::Admit) * nadm,
-                               hipMemcpyHostToDevice, s));
-    HIPCHK(ctx, plc::launch_batch_admit(s, a, E.adm_d, nadm, E.compact));
-  }
-  if (ngrow > 0) {
-    HIPCHK(ctx, hipMemcpyAsync(E.grow_d, E.grow_h, sizeof(plc::Grow) * ngrow,
-                               hipMemcpyHostToDevice, s));
-    HIPCHK(ctx, plc::launch_table_grow(s, a, E.grow_d, ngrow, total_old, total_list, gw));
-    // stream order: later users of these blocks run after the rehash
-    for (void* b : old_blocks) ctx->arena.release(b);
-  }
-  // 2. one round for every running query
-  bool any_run = false;
-  for (int q = 0; q < E.B; q++) any_run |= E.state[q] == HS_RUN;
-  const EventPair* scatter_ev = nullptr;
-  if (any_run) {
-    // while timing is on, the round is launched directly (graphs carry no
-    // events) and the scatter carries events on its own dispatch timestamps
-    Captured* rg = ctx->use_graphs && !ctx->timing ? batch_round_graph(ctx, g) : nullptr;
-    if (rg) {
-      // Dense slots with nothing waiting for admission (throughput mode) need
-      // no host action between rounds (k_b_plan retires a slot whose
-      // frontier emptied), so several rounds share one read-back.
-      const int chain = defer_sweep && E.queue.empty() && !E.compact ? kBatchChain : 1;
-      for (int i = 0; i < chain; i++) HIPCHK(ctx, hipGraphLaunch(rg->exec, s));
-    } else {
-      HIPCHK(ctx, plc::launch_batch_plan_self(s, a, shape(g->batch_self, ctx->grid_self),
-                                              E.compact));
-      hipEvent_t t0 = nullptr, t1 = nullptr;
-      if (ctx->timing) {
-        if (ctx->ev_scatter.empty()) ctx->ev_scatter.emplace_back();
-        HIPCHK(ctx, ev_pair(ctx->ev_scatter[0]));
-        scatter_ev = &ctx->ev_scatter[0];
-        t0 = scatter_ev->a;
-        t1 = scatter_ev->b;
-      }
-      HIPCHK(ctx, plc::launch_batch_scatter(s, a, shape(g->batch_scatter, ctx->grid_scatter),
-                                            E.compact, t0, t1));
-      HIPCHK(ctx, plc::launch_batch_round_end(s, a));
-    }
-  }
-  // 3. sweep the queries whose frontier emptied in an earlier step
+  // stream order: later users of these blocks run after the rehash
+  for (void* b : old_blocks) ctx->arena.release(b);
+  // 1c. plan the sweep of the queries whose frontier emptied in an earlier step
   plc::SweepShape shp;
   int nseg = 0;
   long long total = 0, touch_total = 0, vol_bound = 0;
@@ -2067,7 +2027,7 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
     size_t off_rid = off_p + ((8 * (size_t)N + 255) & ~(size_t)255);
     size_t off_rval = off_rid + ((4 * Tr + 255) & ~(size_t)255);
     res.block = ctx->arena.alloc(off_rval + 8 * Tr);
-    plc::SweepSeg& sg = E.segs_h[nseg];
+    plc::SweepSeg& sg = E.segs[nseg];
     sg.slot = q;
     sg.n_elem = (int32_t)N;
     sg.elem_off = total;
@@ -2100,16 +2060,69 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
     vol_bound += S.edges;
     nseg++;
   }
+  // 1d. one upload of all of these lists; then the hold flags, cleared new
+  // tables, admissions and grown tables, in this order
+  const int gw = shape(g->batch_sweep, ctx->grid_sweep);
+  size_t up = 0;
+  auto put = [&](const void* src, size_t bytes) {
+    char* at = E.up_d + up;
+    std::memcpy(E.up_h + up, src, bytes);
+    up = (up + bytes + 63) & ~(size_t)63;
+    return at;
+  };
+  const auto* holds_d = reinterpret_cast<int32_t*>(put(E.holds.data(), 4 * (size_t)nhold));
+  const auto* clear_d = reinterpret_cast<plc::ClearJob*>(
+      put(E.clear.data(), sizeof(plc::ClearJob) * (size_t)njobs));
+  const auto* adm_d =
+      reinterpret_cast<plc::Admit*>(put(E.adm.data(), sizeof(plc::Admit) * (size_t)nadm));
+  const auto* grow_d =
+      reinterpret_cast<plc::Grow*>(put(E.grow.data(), sizeof(plc::Grow) * (size_t)ngrow));
   if (nseg > 0) {
     shp.nseg = nseg;
     shp.elems = total;
-    E.hdr_h->nseg = nseg;
-    E.hdr_h->total = (int32_t)total;
-    E.hdr_h->touch_total = touch_total;
-    HIPCHK(ctx, hipMemcpyAsync(a.segs, E.segs_h, sizeof(plc::SweepSeg) * nseg,
-                               hipMemcpyHostToDevice, s));
-    HIPCHK(ctx, hipMemcpyAsync(reinterpret_cast<char*>(a.ctl) + offsetof(plc::BatchCtl, sw_nseg),
-                               E.hdr_h, sizeof(SweepHdr), hipMemcpyHostToDevice, s));
+    const plc::SweepHdr hdr{nseg, (int32_t)total, touch_total};
+    a.hdr = reinterpret_cast<plc::SweepHdr*>(put(&hdr, sizeof(hdr)));
+    a.segs = reinterpret_cast<plc::SweepSeg*>(
+        put(E.segs.data(), sizeof(plc::SweepSeg) * (size_t)nseg));
+  }
+  if (up > 0) HIPCHK(ctx, hipMemcpyAsync(E.up_d, E.up_h, up, hipMemcpyHostToDevice, s));
+  if (nhold > 0) HIPCHK(ctx, plc::launch_slot_hold(s, a, holds_d, nhold));
+  if (njobs > 0) HIPCHK(ctx, plc::launch_table_clear(s, clear_d, njobs, clear_total, gw));
+  if (nadm > 0) HIPCHK(ctx, plc::launch_batch_admit(s, a, adm_d, nadm, E.compact));
+  if (ngrow > 0)
+    HIPCHK(ctx, plc::launch_table_grow(s, a, grow_d, ngrow, total_old, total_list, gw));
+  // 2. one round for every running query
+  bool any_run = false;
+  for (int q = 0; q < E.B; q++) any_run |= E.state[q] == HS_RUN;
+  const EventPair* scatter_ev = nullptr;
+  if (any_run) {
+    // while timing is on, the round is launched directly (graphs carry no
+    // events) and the scatter carries events on its own dispatch timestamps
+    // Dense slots with nothing waiting for admission (throughput mode) need
+    // no host action between rounds (k_b_plan retires a slot whose
+    // frontier emptied), so several rounds share one read-back.
+    const int chain = defer_sweep && E.queue.empty() && !E.compact ? kBatchChain : 1;
+    Captured* rg = ctx->use_graphs && !ctx->timing ? batch_round_graph(ctx, g, chain) : nullptr;
+    if (rg) {
+      HIPCHK(ctx, hipGraphLaunch(rg->exec, s));
+    } else {
+      HIPCHK(ctx, plc::launch_batch_plan_self(s, a, shape(g->batch_self, ctx->grid_self),
+                                              E.compact));
+      hipEvent_t t0 = nullptr, t1 = nullptr;
+      if (ctx->timing) {
+        if (ctx->ev_scatter.empty()) ctx->ev_scatter.emplace_back();
+        HIPCHK(ctx, ev_pair(ctx->ev_scatter[0]));
+        scatter_ev = &ctx->ev_scatter[0];
+        t0 = scatter_ev->a;
+        t1 = scatter_ev->b;
+      }
+      HIPCHK(ctx, plc::launch_batch_scatter(s, a, shape(g->batch_scatter, ctx->grid_scatter),
+                                            E.compact, t0, t1));
+      HIPCHK(ctx, plc::launch_batch_round_end(s, a));
+    }
+  }
+  // 3. the sweep
+  if (nseg > 0) {
     if (ctx->timing) {
       HIPCHK(ctx, ev_pair(ctx->ev_sweep));
       HIPCHK(ctx, hipEventRecord(ctx->ev_sweep.a, s));
@@ -2118,8 +2131,8 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
     if (ctx->timing) HIPCHK(ctx, hipEventRecord(ctx->ev_sweep.b, s));
   }
   // 4. read back and wait
-  HIPCHK(ctx, hipMemcpyAsync(E.slots_h, a.slots, sizeof(plc::Slot) * E.B, hipMemcpyDeviceToHost, s));
-  HIPCHK(ctx, hipMemcpyAsync(E.ctl_h, a.ctl, sizeof(plc::BatchCtl), hipMemcpyDeviceToHost, s));
+  HIPCHK(ctx, hipMemcpyAsync(E.ctl_h, a.ctl, kSlotsAt + sizeof(plc::Slot) * (size_t)E.B,
+                             hipMemcpyDeviceToHost, s));
   HIPCHK(ctx, hipStreamSynchronize(s));
   if (E.ctl_h->fault) {
     ctx->broken = true;
@@ -2144,7 +2157,7 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
   }
   // 5. retire swept queries; note the ones whose frontier emptied
   for (int i = 0; i < nseg; i++) {
-    const int q = E.segs_h[i].slot;
+    const int q = E.segs[i].slot;
     const plc::Slot& S = E.slots_h[q];
     Result& res = E.sweeping[i];
     plc_result_info& info = res.info;
