@@ -1170,9 +1170,14 @@ struct BinSortLds {
   int hist[kMaxBins + kBlock];
   int sh[kBlock / 64 + 1];
 };
+struct NbLds {
+  int32_t fn[kBlock], tv[kBlock];
+  int nfn, ntv, base[2];
+};
 union ScatterShared {
   ScatterLds at;
   BinSortLds bs;
+  NbLds nb;
 };
 
 __device__ __forceinline__ bool bin_round(const PlainArgs& a, long long E) {
@@ -1309,6 +1314,7 @@ __device__ void bin_sort_chunks(const PlainArgs& a, int nf, BinSortLds& L) {
 // coefficients into an LDS array over the bin's vertices.  Then every touched
 // destination gets one update (plain when the item owns the whole bin, atomic
 // otherwise), on which its threshold crossing and first touch are decided.
+template <int MODE>
 __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
   Ctl* c = a.ctl;
   if (c->status != ST_PUSH) return;
@@ -1337,6 +1343,11 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
   const double eps = c->eps;
   int32_t* Fn = (t & 1) ? a.fbuf0 : a.fbuf1;
   int32_t* cntn = &c->cnt[(t + 1) & 1];
+  // where first touches go
+  constexpr bool NB = MODE == kModeNB;
+  const int list = (t + 1) % 3;
+  int32_t* const tv_list = NB ? a.hk_tl[list] : a.touched;
+  int32_t* const tv_cnt = NB ? &c->hk_tlc[list] : &c->touched_cnt;
   for (int j = threadIdx.x; j < kBinWidth; j += kBlock) acc[j] = 0.0;
   // items per bin: the bin's expected share of the round's edges (E vol_b /
   // 2m) over kBinQ, at least enough that an item spans <= kBinItemChunks
@@ -1470,14 +1481,20 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
       if (jv[m] < 0) continue;
       const int32_t w = vlo + jv[m];
       double old, thr;
-      if (own) {
+      if (own && !NB) {
         const VRec rec = a.vr[w];
         old = rec.r;
         a.vr[w].r = old + xv[m];
         thr = eps * (double)rec.deg;
       } else {
+        double* const dst = NB ? hk_res(a, t + 1, w) : &a.vr[w].r;
         thr = eps * (double)a.vr[w].deg;
-        old = unsafeAtomicAdd(&a.vr[w].r, xv[m]);
+        if (own) {
+          old = *dst;
+          *dst = old + xv[m];
+        } else {
+          old = unsafeAtomicAdd(dst, xv[m]);
+        }
       }
       if (old < thr && old + xv[m] >= thr) { fm |= 1u << m; nfl++; }
       if (__double_as_longlong(old) == 0) { tm |= 1u << m; ntl++; }
@@ -1489,7 +1506,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
     const int NF = both & 0xffff, NT = both >> 16;
     if (threadIdx.x == 0) {
       s_fb = NF > 0 ? atomicAdd(cntn, NF) : 0;
-      s_tb = NT > 0 ? atomicAdd(&c->touched_cnt, NT) : 0;
+      s_tb = NT > 0 ? atomicAdd(tv_cnt, NT) : 0;
       s_nl = 0;
     }
     __syncthreads();
@@ -1503,7 +1520,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
         pf++;
       }
       if (tm >> m & 1u) {
-        if (pt < a.n) a.touched[pt] = w; else c->fault = 1;
+        if (pt < a.n) tv_list[pt] = w; else c->fault = 1;
         pt++;
       }
     }
@@ -1513,12 +1530,43 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
     if (threadIdx.x == 0) {
       c->pushes += nf;
       c->edges += E;
-      c->bin_rounds += 1;
-      c->bin_edges += E;
+      if (!NB) {
+        c->bin_rounds += 1;
+        c->bin_edges += E;
+      }
       c->cnt[t & 1] = 0;
       c->round = t + 1;
       if (slot >= 0) a.work_log[2 * slot + 1] = 1;
     }
+  }
+}
+
+// Nibble steps are binned as PR-Nibble rounds are: 20 steps of up to 6 M edges
+// (R-MAT 2^22, eps 1e-8) took 189 us each with one atomic per edge, now 37 in
+// pass A, the halves included, and 70 in pass B.
+// The kept halves of a binned Nibble step, added before pass B (a launch of
+// its own) adds the contributions: an entry's vertex gets h = rho / 2.
+__device__ void nb_halves(const PlainArgs& a, int t, int nf, double eps, NbLds& L) {
+  Ctl* c = a.ctl;
+  const int32_t* Fc = (t & 1) ? a.fbuf1 : a.fbuf0;
+  int32_t* Fn = (t & 1) ? a.fbuf0 : a.fbuf1;
+  const int list = (t + 1) % 3;
+  if (threadIdx.x == 0) {
+    L.nfn = 0;
+    L.ntv = 0;
+  }
+  __syncthreads();
+  for (int b0 = blockIdx.x * kBlock; b0 < nf; b0 += gridDim.x * kBlock) {
+    const int i = b0 + (int)threadIdx.x;
+    if (i < nf) {
+      const int32_t v = Fc[i];
+      const double h = a.sp[i];
+      const double thr = eps * (double)a.vr[v].deg;
+      const double o = unsafeAtomicAdd(hk_res(a, t + 1, v), h);
+      decide(true, o, h, thr, v, L.fn, &L.nfn, L.tv, &L.ntv);
+    }
+    block_flush2(&c->cnt[(t + 1) & 1], Fn, L.fn, &L.nfn, &c->hk_tlc[list], a.hk_tl[list], L.tv,
+                 &L.ntv, a.n, L.base, &c->fault);
   }
 }
 
@@ -1560,10 +1608,13 @@ __device__ __forceinline__ void scatter_body(const PlainArgs& a, int slot, Scatt
   // which launch pairs of a first chunk carry rounds that could bin (the
   // host queues k_bin_apply behind those pairs only); without k_bin_apply
   // behind it such a round takes the atomic form
-  if (MODE == kModePR && bin_round(a, q.etotal)) {
+  // (Nibble: which steps could bin)
+  if (!HK && bin_round(a, q.etotal)) {
+    if (MODE == kModeNB) pair = t < 31 ? t : 31;
     if (pair >= 0 && blockIdx.x == 0 && threadIdx.x == 0) c->bin_pairs |= 1u << pair;
     if (apply) {
       bin_sort_chunks(a, nf, sm.bs);  // pass A; k_bin_apply adds and closes the round
+      if (MODE == kModeNB) nb_halves(a, t, nf, q.eps, sm.nb);
       return;
     }
   }
@@ -1704,9 +1755,9 @@ __global__ __launch_bounds__(kBlock) void k_hk_scatter(PlainArgs a) {
   __shared__ ScatterShared sm;
   scatter_body<kModeHK>(a, -1, sm);
 }
-__global__ __launch_bounds__(kBlock) void k_nb_scatter(PlainArgs a) {
+__global__ __launch_bounds__(kBlock) void k_nb_scatter(PlainArgs a, int apply) {
   __shared__ ScatterShared sm;
-  scatter_body<kModeNB>(a, -1, sm);
+  scatter_body<kModeNB>(a, -1, sm, -1, apply != 0);
 }
 
 // HK-PR initialisation (Fig. alg:hkpr: r = {(x, 1)}, Frontier = {x},
@@ -2315,9 +2366,12 @@ hipError_t launch_nb_init(hipStream_t s, const PlainArgs& a, int32_t x, double e
   return hipGetLastError();
 }
 
-hipError_t launch_nb_step(hipStream_t s, const PlainArgs& a, int grid_self, int grid_scatter) {
+hipError_t launch_nb_step(hipStream_t s, const PlainArgs& a, int grid_self, int grid_scatter,
+                          int grid_bin) {
   hipLaunchKernelGGL(k_nb_self, dim3(grid_self), dim3(kBlock), 0, s, a);
-  hipLaunchKernelGGL(k_nb_scatter, dim3(grid_scatter), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_nb_scatter, dim3(grid_scatter), dim3(kBlock), 0, s, a, (int)(grid_bin > 0));
+  if (grid_bin > 0)
+    hipLaunchKernelGGL(k_bin_apply<kModeNB>, dim3(grid_bin), dim3(kBlock), 0, s, a, -1);
   return hipGetLastError();
 }
 
@@ -2390,11 +2444,11 @@ hipError_t launch_scatter(hipStream_t s, const PlainArgs& a, int grid, hipEvent_
     hipExtLaunchKernelGGL(k_scatter, dim3(grid), dim3(kBlock), 0, s, t0, apply ? nullptr : t1, 0,
                           a, slot, pair, ap);
     if (apply)
-      hipExtLaunchKernelGGL(k_bin_apply, dim3(grid_bin), dim3(kBlock), 0, s, nullptr, t1, 0, a,
+      hipExtLaunchKernelGGL(k_bin_apply<kModePR>, dim3(grid_bin), dim3(kBlock), 0, s, nullptr, t1, 0, a,
                             slot);
   } else {
     hipLaunchKernelGGL(k_scatter, dim3(grid), dim3(kBlock), 0, s, a, slot, pair, ap);
-    if (apply) hipLaunchKernelGGL(k_bin_apply, dim3(grid_bin), dim3(kBlock), 0, s, a, slot);
+    if (apply) hipLaunchKernelGGL(k_bin_apply<kModePR>, dim3(grid_bin), dim3(kBlock), 0, s, a, slot);
   }
   return hipGetLastError();
 }

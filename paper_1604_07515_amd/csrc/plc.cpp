@@ -153,6 +153,7 @@ struct plc_graph {
   // queue k_bin_apply as the mask says and report rounds that could bin (a
   // mask that comes back finds its graph still recorded)
   std::map<uint64_t, Captured> first_g;
+  int nb_bin = 0;  // Nibble: first step of the last query that could bin
   int hk_pairs = 0, hk_dense = -1;  // HK-PR: pairs and dense launches the last query used
   std::map<int64_t, Captured> sweep_g;  // plain path: the sweep, by sort bound (power of 2)
 };
@@ -1344,7 +1345,15 @@ extern "C" plc_status plc_run_nibble(plc_ctx* ctx, plc_graph* g, int32_t seed, d
   // PR-Nibble sample the shape was tuned on: at least CU/2 workgroups)
   const int gs = std::max(shape(g->plain_self, ctx->grid_self), ctx->num_cu / 2);
   const int gc = shape(g->plain_scatter, ctx->grid_scatter);
-  for (int32_t j = 0; j < T; j++) HIPCHK(ctx, plc::launch_nb_step(s, a, gs, gc));
+  // Steps that may be binned carry a pass B launch (a few us where a step is
+  // not): none while the graph, or the frontier's volume, which p >= eps d
+  // keeps below 1 / eps, has fewer edges than a binned round; from the first
+  // step on that could bin in the graph's last query otherwise (all of them
+  // until a query has told).
+  const bool bins = plc::bins_possible(a) && g->arcs >= a.bin_emin &&
+                    1.0 / eps >= (double)a.bin_emin;
+  for (int32_t j = 0; j < T; j++)
+    HIPCHK(ctx, plc::launch_nb_step(s, a, gs, gc, bins && j >= g->nb_bin ? ctx->grid_bin : 0));
   Ctl& h = *ctx->ctl_host;
   HIPCHK(ctx, hipMemcpyAsync(&h, a.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
   HIPCHK(ctx, hipStreamSynchronize(s));
@@ -1352,6 +1361,7 @@ extern "C" plc_status plc_run_nibble(plc_ctx* ctx, plc_graph* g, int32_t seed, d
     ctx->broken = true;
     return PLC_E_HIP;
   }
+  if (bins) g->nb_bin = h.bin_pairs != 0 ? __builtin_ctz(h.bin_pairs) : INT32_MAX;
   // the returned vector: the last step's, unless that step's frontier was
   // empty, then the one before it
   const int32_t J = h.round;

@@ -290,7 +290,9 @@ hipError_t launch_hk_clear(hipStream_t s, const PlainArgs& a, int grid);
 // an empty frontier or T exit at once), and the end (vector R of J steps
 // into p and the support list, both vector arrays cleared)
 hipError_t launch_nb_init(hipStream_t s, const PlainArgs& a, int32_t x, double eps, int32_t T);
-hipError_t launch_nb_step(hipStream_t s, const PlainArgs& a, int grid_self, int grid_scatter);
+// grid_bin > 0: a step of many edges may be binned (k_bin_apply follows)
+hipError_t launch_nb_step(hipStream_t s, const PlainArgs& a, int grid_self, int grid_scatter,
+                          int grid_bin);
 hipError_t launch_nb_finish(hipStream_t s, const PlainArgs& a, int32_t R, int32_t J, int grid);
 // With t0 set, the kernel is launched with start and stop events that take
 // its own dispatch timestamps (hipExtLaunchKernelGGL); not for graph capture.
