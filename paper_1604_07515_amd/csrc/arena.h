@@ -40,6 +40,25 @@ class Arena {
     return nullptr;
   }
 
+  // alloc, but only from the first free block: whatever smaller size was
+  // asked for instead would have been given the same address.
+  void* alloc_front(size_t bytes) {
+    if (free_.empty() || free_.begin()->second < bytes) return nullptr;
+    return alloc(bytes);
+  }
+
+  // Gives back what lies past the first `bytes` of a block.
+  void trim(void* p, size_t bytes) {
+    if (bytes == 0) bytes = kAlign;
+    bytes = (bytes + kAlign - 1) & ~(kAlign - 1);
+    const size_t off = static_cast<size_t>(static_cast<char*>(p) - base_);
+    auto u = used_.find(off);
+    if (u == used_.end() || u->second <= bytes) return;
+    used_[off + bytes] = u->second - bytes;
+    u->second = bytes;
+    release(base_ + off + bytes);
+  }
+
   // Returns false for pointers this arena did not hand out.
   bool release(void* p) {
     if (!p) return true;

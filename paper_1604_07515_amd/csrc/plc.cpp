@@ -183,6 +183,7 @@ struct plc_ctx {
   // before its first dense round, and its dense launches that did work
   std::deque<int> round_hist, dense_hist;
   std::deque<int> support_hist;  // plain path: support sizes of the last queries
+  std::deque<int> rnnz_hist;     // and nonzeros of r, where kept
   // plain path: Ctl::bin_pairs of the last queries whose first chunk reported
   // them (the pairs of a first chunk whose rounds could bin)
   std::deque<uint32_t> pair_hist;
@@ -847,10 +848,16 @@ static hipError_t queue_rounds(plc_ctx* ctx, const plc_graph* g, Chunk ch, bool 
   return hipSuccess;
 }
 
+// A result block taken before the result's sizes are known (null: none).
+struct Ahead {
+  void* block = nullptr;
+};
 static plc_status sweep_and_record(plc_ctx* ctx, plc_graph* g, uint64_t* id_out,
                                    plc_result_info* info_out);
 static plc_status record_result(plc_ctx* ctx, plc_graph* g, uint64_t* id_out,
-                                plc_result_info* info_out);
+                                plc_result_info* info_out, Ahead ahead);
+static bool keeps_r(const plc_ctx* ctx);
+static hipError_t copy_ahead(plc_ctx* ctx, const plc_graph* g, int64_t N, int64_t R, Ahead* out);
 static hipError_t queue_sweep(plc_ctx* ctx, plc_graph* g, int64_t bound);
 
 // One plain query: from q.seed, or, with set non-null, from the nset
@@ -958,6 +965,7 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
     while (spec_bound < mx) spec_bound <<= 1;
   }
   bool swept = false;
+  Ahead done;
   bool reports = pre.pairs > 0;  // the first chunk reports Ctl::bin_pairs
   Ctl& h = *ctx->ctl_host;
   for (bool first = true;; first = false) {
@@ -976,6 +984,16 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
         HIPCHK(ctx, queue_rounds(ctx, g, chunk, use_beta, first));
     }
     if (spec_bound) HIPCHK(ctx, queue_sweep(ctx, g, spec_bound));
+    // the last query's result is copied ahead of the read-back, into a block
+    // for the largest recent sizes (the copies of the others wait behind the
+    // next query's first chunk)
+    Ahead ahead;
+    if (spec_bound && !next) {
+      const int64_t top = keeps_r(ctx) && !ctx->rnnz_hist.empty()
+                              ? *std::max_element(ctx->rnnz_hist.begin(), ctx->rnnz_hist.end()) : 0;
+      HIPCHK(ctx, copy_ahead(ctx, g, std::min(spec_bound, g->n),
+                             std::min(top + top / 2, g->n), &ahead));
+    }
     const EventPair* ev_s = ctx->ev_self.data();
     const EventPair* ev_c = ctx->ev_scatter.data();
     HIPCHK(ctx, hipMemcpyAsync(&h, a.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
@@ -1039,7 +1057,12 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
     }
     queued.pairs += chunk.pairs;
     queued.dense += chunk.dense;
-    if (h.status == plc::ST_SWEPT) { swept = true; break; }  // pushed and swept
+    if (h.status == plc::ST_SWEPT) {  // pushed and swept
+      done = ahead;
+      swept = true;
+      break;
+    }
+    if (ahead.block) ctx->arena.release(ahead.block);  // (its copy, if queued, has run: nothing)
     if (h.status == plc::ST_LIMIT) break;  // watchdog: sweep the partial p
     if (h.status != plc::ST_PUSH || h.fault) {  // unexpected state: device-side fault
       ctx->broken = true;
@@ -1054,12 +1077,29 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
   if (ctx->dense_hist.size() > 16) ctx->dense_hist.pop_front();
   ctx->support_hist.push_back(swept ? h.N : h.support_cnt);
   if (ctx->support_hist.size() > 16) ctx->support_hist.pop_front();
+  if (swept && keeps_r(ctx)) {
+    ctx->rnnz_hist.push_back(h.rnnz);
+    if (ctx->rnnz_hist.size() > 16) ctx->rnnz_hist.pop_front();
+  }
   if (reports) {
     ctx->pair_hist.push_back(h.bin_pairs);
     if (ctx->pair_hist.size() > 16) ctx->pair_hist.pop_front();
   }
-  if (swept) return record_result(ctx, g, id_out, info_out);
+  if (swept) return record_result(ctx, g, id_out, info_out, done);
   return sweep_and_record(ctx, g, id_out, info_out);
+}
+
+static bool keeps_r(const plc_ctx* ctx) { return !(ctx->cur_flags & PLC_QF_NO_RESIDUAL); }
+
+// Queue the copy of a result of at most N and R elements ahead of the
+// read-back that tells its sizes.  No block (and no copy) unless it comes from
+// the arena's first free block, where the result's own would lie as well.
+static hipError_t copy_ahead(plc_ctx* ctx, const plc_graph* g, int64_t N, int64_t R, Ahead* out) {
+  const size_t bytes = plc::result_layout((size_t)N, (size_t)R).bytes;
+  out->block = ctx->arena.alloc_front(bytes);
+  if (!out->block) return hipSuccess;
+  return plc::launch_copy_ahead(ctx->stream, g->args, out->block, bytes, keeps_r(ctx),
+                                shape(g->plain_sweep, ctx->grid_sweep));
 }
 
 // Queue the plain sweep for supports of at most `bound` vertices (a power
@@ -1090,9 +1130,13 @@ static plc_status sweep_and_record(plc_ctx* ctx, plc_graph* g, uint64_t* id_out,
   int64_t bound = 1024;
   while (bound < h.support_cnt) bound <<= 1;
   HIPCHK(ctx, queue_sweep(ctx, g, bound));
+  Ahead ahead;
+  if (!ctx->timing)
+    HIPCHK(ctx, copy_ahead(ctx, g, std::min<int64_t>(h.support_cnt, g->n),
+                           keeps_r(ctx) ? std::min<int64_t>(h.touched_cnt, g->n) : 0, &ahead));
   HIPCHK(ctx, hipMemcpyAsync(&h, a.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
   HIPCHK(ctx, hipStreamSynchronize(s));
-  return record_result(ctx, g, id_out, info_out);
+  return record_result(ctx, g, id_out, info_out, ahead);
 }
 
 // After a plain sweep (the control block read back into ctx->ctl_host):
@@ -1100,7 +1144,7 @@ static plc_status sweep_and_record(plc_ctx* ctx, plc_graph* g, uint64_t* id_out,
 // of r), queue the copy of the results into it and record the result.
 // Without room for the block the query reports PLC_E_NOMEM.
 static plc_status record_result(plc_ctx* ctx, plc_graph* g, uint64_t* id_out,
-                                plc_result_info* info_out) {
+                                plc_result_info* info_out, Ahead ahead) {
   hipStream_t s = ctx->stream;
   const PlainArgs& a = g->args;
   Ctl& h = *ctx->ctl_host;
@@ -1111,19 +1155,25 @@ static plc_status record_result(plc_ctx* ctx, plc_graph* g, uint64_t* id_out,
   }
   const size_t N = (size_t)h.N;
   const size_t R = (ctx->cur_flags & PLC_QF_NO_RESIDUAL) ? 0 : (size_t)h.rnnz;
-  const size_t off_p = (4 * N + 255) & ~(size_t)255;
-  const size_t off_rid = off_p + ((8 * N + 255) & ~(size_t)255);
-  const size_t off_rval = off_rid + ((4 * R + 255) & ~(size_t)255);
+  const plc::ResultLayout l = plc::result_layout(N, R);
   Result res;
-  res.block = ctx->arena.alloc(off_rval + 8 * R);
+  const bool copied = ahead.block && h.copied;
+  if (copied) {
+    ctx->arena.trim(ahead.block, l.bytes);
+    res.block = ahead.block;
+  } else {
+    if (ahead.block) ctx->arena.release(ahead.block);
+    res.block = ctx->arena.alloc(l.bytes);
+  }
   if (res.block) {
     char* b = static_cast<char*>(res.block);
     res.ids = reinterpret_cast<int32_t*>(b);
-    res.p = reinterpret_cast<double*>(b + off_p);
-    res.rid = reinterpret_cast<int32_t*>(b + off_rid);
-    res.rval = reinterpret_cast<double*>(b + off_rval);
-    HIPCHK(ctx, plc::launch_copy_result(s, a, res.ids, res.p, res.rid, res.rval, (int)N, (int)R,
-                                        shape(g->plain_sweep, ctx->grid_sweep)));
+    res.p = reinterpret_cast<double*>(b + l.p);
+    res.rid = reinterpret_cast<int32_t*>(b + l.rid);
+    res.rval = reinterpret_cast<double*>(b + l.rval);
+    if (!copied)
+      HIPCHK(ctx, plc::launch_copy_result(s, a, res.ids, res.p, res.rid, res.rval, (int)N, (int)R,
+                                          shape(g->plain_sweep, ctx->grid_sweep)));
     if (ctx->cur_flags & PLC_QF_NO_RESIDUAL) {
       res.rid = nullptr;
       res.rval = nullptr;

@@ -93,7 +93,8 @@ struct __align__(64) Ctl {
   // round bookkeeping: `steps` counts self launches that did work;
   // loop_rounds / loop_pushes / loop_edges count the small rounds a self
   // launch ran on its own
-  int32_t steps, pad2;
+  int32_t steps;
+  int32_t copied;  // k_copy_ahead copied the result
   int32_t loop_rounds;
   int32_t init_held;  // a queued guarded initialisation found the previous query unfinished
   long long loop_pushes, loop_edges;
@@ -328,6 +329,24 @@ hipError_t launch_scatter(hipStream_t s, const PlainArgs& a, int grid, hipEvent_
 // (r over the touched list, p and the rank over the support list).
 // launch_copy_result copies N and R of them into a result block.
 hipError_t launch_sweep(hipStream_t s, const PlainArgs& a, int grid, int64_t max_count);
+// Offsets of a plain result's parts in its block (ids at 0): support N,
+// nonzeros of r R; and its size.
+struct ResultLayout {
+  size_t p, rid, rval, bytes;
+};
+__host__ __device__ inline ResultLayout result_layout(size_t N, size_t R) {
+  ResultLayout l;
+  l.p = (4 * N + 255) & ~(size_t)255;
+  l.rid = l.p + ((8 * N + 255) & ~(size_t)255);
+  l.rval = l.rid + ((4 * R + 255) & ~(size_t)255);
+  l.bytes = l.rval + 8 * R;
+  return l;
+}
+// The copy of a result whose size the host does not know yet: made (and
+// Ctl::copied set) when the sweep has ended and the result fits into cap
+// bytes at block, else nothing but Ctl::copied = 0.
+hipError_t launch_copy_ahead(hipStream_t s, const PlainArgs& a, void* block, size_t cap,
+                             bool residual, int grid);
 hipError_t launch_copy_result(hipStream_t s, const PlainArgs& a, int32_t* ids, double* p,
                               int32_t* rid, double* rval, int N, int R, int grid);
 
