@@ -573,7 +573,7 @@ def plain_arena_bytes(n: int, arcs: int) -> int:
     scans = 3 * 16 * (n // 1024 + 2) + 24 * (n // 1024 + 2)
     # binned scatter (graphs up to 6,291,456 vertices): pairs (8 B per edge of the
     # largest binned round, at most 2^23), the per-chunk run table (2049
-    # ints per 2048-edge chunk) and the pull records (16 B per vertex)
+    # ints per 2048-edge chunk) and the dense rounds' coefficients (16 B per vertex)
     binned = n <= 1536 * 4096
     chunks = (min(max(arcs, 1), 1 << 23) + 2047) // 2048 if binned else 0
     bins = n // 16 + 12 * 2048 + chunks * (8 * 2048 + 4 * 2049) + 7 * 256

@@ -13,11 +13,13 @@
 //                 frontier.  Entries of a tile are slot-sorted, so appends are
 //                 counted per slot in LDS and reserved with one global atomic
 //                 per slot and tile.
-//   k_b_round_end (one workgroup) per-slot bookkeeping and frontier swap.
-// Queries whose frontier emptied are swept together: their supports form
-// the segments of one merge sort (segment = query), then the rank map,
-// volume scan, boundary deltas and boundary scan run over the concatenation
-// and one workgroup per segment takes the exact argmin.
+//   k_b_round_end (one workgroup) per-slot bookkeeping and frontier swap; done
+//                 by the next round's plan where no read-back is between.
+// Queries whose frontier emptied are swept together: their supports, laid end
+// to end, are sorted each by itself (one merge sort by segment, ratio and id
+// where one is too large for that), then the rank map with the volume scan,
+// the boundary deltas and the boundary scan run over the concatenation and one
+// workgroup per segment takes the exact argmin.
 //
 // The kernels that touch per-query state are templates over the state layout
 // (DenseState or CompactState, see batch_device.h).

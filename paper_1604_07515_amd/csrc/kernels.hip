@@ -24,8 +24,8 @@
 //             form whatever the round's size).
 // Rounds that cover a good part of the arcs are dense: one launch of k_dense
 // each, queued in a row once a query has got there.
-// A frontier of at most one scan block is handled by k_self alone: its last
-// workgroup to arrive runs such rounds back to back (self step, scan, edge
+// A frontier of at most one scan block is handled by k_self alone: its
+// workgroup 0 runs such rounds back to back (self step, scan, edge
 // scatter, round close) until the frontier grows, empties or a round has
 // too many edges for one workgroup; k_scatter then pushes only rounds whose
 // entries were built in memory.
@@ -34,7 +34,7 @@
 // sweep, guarded the same way) can be queued ahead of the host's
 // termination check.
 //
-// The sweep: k_sweep_keys, the sort (sort.hip; its block-sort launch also
+// The sweep: k_sweep_keys, the sort (sort.hip; its first launch also
 // gathers the nonzeros of r over the touched list and resets r, on the
 // workgroups that hold no tile), k_vol_scan, k_cut_count and k_cut_scan (which
 // also resets p and the ranks, and takes the best prefix).
@@ -747,7 +747,7 @@ struct DenseLds {
 // every arc once, the other forms a launch more (about kDenseBase arcs'
 // worth) and about kDenseRatio times as much per edge.
 __device__ __forceinline__ bool dense_pays(const PlainArgs& a, long long E) {
-  if (a.cd[0] == nullptr || a.bin_emin >= kBinOff) return false;
+  if (a.cd[0] == nullptr) return false;
   if (a.dense_free) return a.vol_total <= kDenseBase + kDenseRatio * E;
   return E >= a.bin_emin && E >= a.dense_emin;
 }

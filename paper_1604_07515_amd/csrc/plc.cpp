@@ -11,8 +11,9 @@
 // next query's guarded initialisation and first chunk are queued behind the
 // running query's first read-back (they stand aside on the device while the
 // running query is unfinished), so the GPU works while the host reads back.  Results are copied
-// device-to-device into an exact-size arena block, and the dense per-vertex
-// state is reset through the touched list.  The batch engine (plc_batch_reserve and after)
+// device-to-device into an exact-size arena block (a lone query's ahead of the
+// read-back that tells the size), and the dense per-vertex state is reset
+// through the touched list.  The batch engine (plc_batch_reserve and after)
 // runs many queries per launch.
 #include <hip/hip_runtime.h>
 

@@ -38,8 +38,7 @@ enum : int32_t { SCAN_FRONTIER = 0, SCAN_VOL = 1, SCAN_CUT = 2, NUM_SCANS = 3 };
 
 // Last-workgroup counters.
 enum : int32_t {
-  DONE_SCATTER = 0, DONE_KEYS = 1, DONE_SORT = 2, DONE_FINISH = 3, DONE_SELF = 4, DONE_BIN = 5,
-  DONE_DENSE = 6, NUM_DONE = 8
+  DONE_SCATTER = 0, DONE_KEYS = 1, DONE_FINISH = 2, DONE_BIN = 3, DONE_DENSE = 4, NUM_DONE = 8
 };
 
 // Device control block of one plain-path query.  Written by kernels only,
@@ -254,13 +253,12 @@ constexpr long long kDenseBase = 1 << 20;
 constexpr int kDenseRatio = 4;
 static_assert(kBinChunk <= 65536 && kMaxBins <= 32768, "pass A packs (bin, rank) in 32 bits");
 
-// Whether a round of this graph can be binned or dense (both need bins and
-// a reachable threshold); otherwise k_bin_apply never has work and the
-// scatter closes every round itself.
+// Whether a round of this graph can be binned (it needs bins and a reachable
+// threshold; otherwise k_bin_apply never has work and the scatter closes every
+// round itself) or dense (also where the autotuner, whose sample rarely gets
+// that wide, turned binning off: an HK-PR query would take ten times as long).
 inline bool bins_possible(const PlainArgs& a) { return a.nbins > 0 && a.bin_emin < kBinOff; }
-inline bool dense_possible(const PlainArgs& a) {
-  return a.cd[0] != nullptr && a.bin_emin < kBinOff;
-}
+inline bool dense_possible(const PlainArgs& a) { return a.cd[0] != nullptr; }
 
 // Host-side launchers (return hipError_t of the launch).
 hipError_t launch_graph_init(hipStream_t s, const PlainArgs& a);

@@ -1,4 +1,4 @@
-// sort.h -- interface of the device merge sort used by the sweep cut.
+// sort.h -- interface of the device sort used by the sweep cut.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -23,7 +23,7 @@ struct SortArgs {
   // at every count.  That path compares keys and ids only: the elements are
   // of one segment.
   unsigned long long* rank;
-  // Optional side job of the block-sort launch, taken first by its
+  // Optional side job of the sort's first launch, taken first by its
   // workgroups that hold no tile: for each id in side_ids[0 .. *side_count)
   // (at most side_out_cap of them), the double at side_val[id * side_stride]
   // is read and set to +0.0, and every nonzero one is appended as (id,

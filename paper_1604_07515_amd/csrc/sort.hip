@@ -26,7 +26,7 @@
 // many elements each (launch_seg_sort) are sorted the same way, every segment
 // within its own range of the buffer.
 //
-// The block-sort launch can carry a side job (SortArgs::side_ids) for its
+// The first launch can carry a side job (SortArgs::side_ids) for its
 // workgroups that hold no tile: with supports of a few tiles most of the
 // launch's workgroups would otherwise only exit.
 #include <hip/hip_runtime.h>
@@ -94,7 +94,7 @@ __device__ __forceinline__ void cswap(SortElem& a, SortElem& b, bool up) {
 constexpr int kSideItems = 4;                    // side-job entries per thread and step
 constexpr int kSideGrid = 512;                   // block-sort workgroups when a side job rides along
 
-// The block-sort launch's side job (SortArgs::side_ids), in steps of
+// The first launch's side job (SortArgs::side_ids), in steps of
 // NT * kSideItems ids per workgroup of NT threads: the workgroups are renumbered so that those
 // holding no tile take the first steps; the ones that sorted a tile join
 // only when there are more steps than workgroups without one.  Each step
