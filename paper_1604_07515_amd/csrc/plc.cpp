@@ -341,6 +341,7 @@ static void dense_blocks(const std::vector<int64_t>& off, std::vector<plc::Dense
                          int32_t* nlong) try {
   const int64_t n = (int64_t)off.size() - 1;
   *nlong = 0;
+  out->reserve((size_t)(n / plc::kDenseRows + 2 * (off[n] / plc::kDenseArcs) + 16));
   for (int64_t v = 0; v < n;) {
     int64_t d = off[v + 1] - off[v];
     if (d > plc::kDenseArcs) {
@@ -355,15 +356,18 @@ static void dense_blocks(const std::vector<int64_t>& off, std::vector<plc::Dense
       v++;
       continue;
     }
-    int64_t w = v, arcs = 0, top = 0;
-    while (w < n && w - v < plc::kDenseRows) {
+    // rows up to `end`, which the row limit and the longest row so far set
+    const int64_t last = off[v] + plc::kDenseArcs;
+    int64_t w = v, top = 0, end = std::min<int64_t>(n, v + plc::kDenseRows);
+    for (; w < end && off[w + 1] <= last; w++) {
       d = off[w + 1] - off[w];
-      const int64_t m = std::max(top, d);
-      if (arcs + d > plc::kDenseArcs || (w > v && (w - v + 1) * m > plc::kDenseSpan)) break;
-      arcs += d;
-      top = m;
-      w++;
+      if (d <= top) continue;
+      const int64_t lim = v + plc::kDenseSpan / d;
+      if (w >= lim) break;
+      top = d;
+      end = std::min(end, lim);
     }
+    const int64_t arcs = off[w] - off[v];
     if (arcs > 0)  // (isolated vertices take part in no round)
       out->push_back(plc::DenseBlk{(int32_t)v, (int32_t)(w - v), -1, (int32_t)arcs,
                                    (long long)off[v]});
@@ -400,8 +404,9 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
     deg[v] = (int32_t)d;
     maxdeg = std::max(maxdeg, d);
   }
-  // The dense round's blocks of rows (see dense_blocks) are laid out beside
-  // the other host passes over the graph.
+  // The dense round's blocks of rows (see dense_blocks): 3 ns a row, laid out
+  // beside the range check where that is more than a thread costs (2 ms: its
+  // stack and heap come and go in a process that the GPU maps).
   const bool bins_on = ctx->opt.bin_min_edges >= 0 &&
                        n <= plc::kBinMaxVertices;
   std::vector<plc::DenseBlk> dblk;
@@ -413,12 +418,13 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
     ~Join() { (*this)(); }
   } dense_join{dense_th};
   if (bins_on) {
-    auto lay_out = [&]() { dense_blocks(off, &dblk, &nlong); };
+    bool beside = n >= (int64_t)1 << 21;
     try {
-      dense_th = std::thread(lay_out);
+      if (beside) dense_th = std::thread([&]() { dense_blocks(off, &dblk, &nlong); });
     } catch (const std::system_error&) {
-      lay_out();
+      beside = false;
     }
+    if (!beside) dense_blocks(off, &dblk, &nlong);
   }
   // Neighbour ids index per-vertex arrays on the device: always range-checked.
   {
@@ -1633,7 +1639,7 @@ static size_t batch_fixed_bytes(const plc_graph* g, int B) {
   b += 28 * (size_t)nf_cap + 4 * (size_t)tile_cap + 3 * 16 * (size_t)desc_cap;
   b += (2 * sizeof(plc::SortElem) + 4 + 8 + 4 + 8) * (size_t)s_cap;
   b += (sizeof(plc::Slot) + 8) * (size_t)B + batch_up_bytes(B);
-  b += 8 * (size_t)g->n + 64 * 1024;  // compact: graph-wide {d, hot code}
+  b += 8 * (size_t)g->n + 44 * 1024;  // compact: graph-wide {d, hot code}; alignment
   return b;
 }
 
