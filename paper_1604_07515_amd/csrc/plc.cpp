@@ -896,19 +896,24 @@ static Chunk first_chunk(const plc_ctx* ctx, const plc_graph* g, bool beta = fal
     ch.pairs = upper_quartile(ctx->round_hist);
     ch.dense = dense ? upper_quartile(ctx->dense_hist) : 0;
   }
-  ch.pairs = std::max(2, std::min(plc::kMaxChunk / 2, ch.pairs));
   ch.dense = std::min(plc::kMaxChunk / 2, (ch.dense + kDenseStep - 1) / kDenseStep * kDenseStep);
+  ch.pairs = std::max(2, std::min(plc::kMaxChunk - ch.dense, ch.pairs));
   return ch;
 }
 
 // The next chunk of a query that needs more than its first, by its state.
-static Chunk next_chunk(const Ctl& h, Chunk queued) {
+// What recent queries needed beyond the pairs queued, if they did (a chunk is
+// limited, and each costs an idle sweep and a read-back: randLocal 10^7, 266
+// pairs, took four), else a third of those.
+static Chunk next_chunk(const plc_ctx* ctx, const Ctl& h, Chunk queued) {
   Chunk ch;
   if (h.dense == plc::DN_READY || h.dense == plc::DN_CONVERT) {
     ch.dense = std::max(2 * kDenseStep, std::min(64, queued.dense / 2));
     ch.dense = (ch.dense + kDenseStep - 1) / kDenseStep * kDenseStep;
   } else {
-    ch.pairs = std::max(2, std::min(64, queued.pairs / 3));
+    const int more = ctx->round_hist.empty() ? 0 : upper_quartile(ctx->round_hist) - queued.pairs;
+    ch.pairs = std::max(2, more > 0 ? std::min(plc::kMaxChunk / 2, more)
+                                    : std::min(64, queued.pairs / 3));
     ch.light = h.dense == plc::DN_LIGHT;
   }
   return ch;
@@ -1076,7 +1081,7 @@ static plc_status run_one(plc_ctx* ctx, plc_graph* g, const plc_query& q, uint64
       return PLC_E_HIP;
     }
     if (h.cnt[h.round & 1] == 0) break;     // next frontier empty: the push is done
-    chunk = next_chunk(h, queued);
+    chunk = next_chunk(ctx, h, queued);
   }
   ctx->round_hist.push_back(h.dsteps > 0 && !use_beta ? h.pairs0 : h.steps);
   if (ctx->round_hist.size() > 16) ctx->round_hist.pop_front();
