@@ -455,13 +455,21 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot, const Ct
   }
 }
 
+// Whether the addition of c that returned `old` is the first touch of a word
+// that was +0.0.  A c that underflowed to 0 (HK-PR and Nibble, whose eps may be
+// any positive number) leaves the word as it was and touches nothing: counted,
+// every such addition would be a first one, more of them than the lists hold.
+__device__ __forceinline__ bool first_touch(double old, double c) {
+  return __double_as_longlong(old) == 0 && c != 0.0;
+}
+
 // Threshold decision for one addition of c to r[w] that returned `old`
 // (lanes without an addition pass valid = false): crossing appends w to the
 // next frontier, first touch to the touched list (wave-ballot appends).
 __device__ __forceinline__ void decide(bool valid, double old, double c, double thr, int32_t w,
                                        int32_t* s_fn, int* s_nfn, int32_t* s_tv, int* s_ntv) {
   wave_append(valid && old < thr && old + c >= thr, w, s_fn, s_nfn);
-  wave_append(valid && __double_as_longlong(old) == 0, w, s_tv, s_ntv);
+  wave_append(valid && first_touch(old, c), w, s_tv, s_ntv);
 }
 
 template <typename T>
@@ -1717,7 +1725,7 @@ __device__ __forceinline__ void scatter_body(const PlainArgs& a, int slot, Scatt
       const double thr = (eps * (double)dw[k]) / den;
       if (w[k] < 0) continue;
       if (!hk_last && old[k] < thr && old[k] + cf[k] >= thr) cross |= 1u << k;
-      if (__double_as_longlong(old[k]) == 0) touch |= 1u << k;
+      if (first_touch(old[k], cf[k])) touch |= 1u << k;
     }
     if (!hk_last) wave_append_all<kEdgesPerThread>(cross, w, s_fn, &s_nfn);
     wave_append_all<kEdgesPerThread>(touch, w, s_tv, &s_ntv);
