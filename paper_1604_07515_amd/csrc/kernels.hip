@@ -843,6 +843,8 @@ __device__ __forceinline__ void dense_round(const PlainArgs& a, int slot, DenseL
           sup = pold == 0.0;
           if (HK) {
             x = hk_next_last ? r / (double)d : (hk_t * r) / ((double)(t + 2) * (double)d);
+            // (one that underflows is kept apart from those off the frontier)
+            if (x == 0.0) x = -0.0;
           } else {
             a.vr[w].r = opt ? -0.0 : keep * r;
             x = (cn * r) / (double)d;
@@ -1013,7 +1015,8 @@ __device__ __forceinline__ void dense_round(const PlainArgs& a, int slot, DenseL
   c->round = t + 1;
 }
 
-// Back to the list form: the frontier is listed from the coefficients, and
+// Back to the list form: the frontier is listed from the coefficients (a 0 on
+// it is -0.0, PR-Nibble has none: eps >= 1e-250 bounds its r from below), and
 // the other array is cleared.
 __device__ void dense_convert(const PlainArgs& a, DenseLds& L) {
   Ctl* c = a.ctl;
@@ -1027,7 +1030,7 @@ __device__ void dense_convert(const PlainArgs& a, DenseLds& L) {
     const int64_t i = i0 + threadIdx.x;
     bool in = false;
     if (i < a.n) {
-      in = cd[i] != 0.0;
+      in = __double_as_longlong(cd[i]) != 0;
       old[i] = 0.0;
     }
     wave_append(in, (int32_t)i, L.fn, &L.nfn);

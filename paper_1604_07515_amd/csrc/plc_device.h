@@ -114,7 +114,7 @@ struct __align__(64) Ctl {
 };
 
 // Ctl::dense.  LIST: frontier list (the other forms).  READY: the round's
-// self step is done and cd[t & 1] holds its coefficients, 0 off the frontier
+// self step is done and cd[t & 1] holds its coefficients, +0.0 off the frontier
 // (cnt[t & 1] is then only known to be positive).
 // CONVERT: the same, but the round goes back to the list form; LIGHT: the
 // list has been rebuilt, the entries not yet.
@@ -192,7 +192,7 @@ struct PlainArgs {
   int32_t* bin_T;              // [(nbins + 1) x bin_cmax]: start of bin b's run in chunk c
   int2* bin_pairs;             // [bin_cmax x kBinChunk]: (neighbour, entry) by bin per chunk
   // Dense rounds: every row sums the coefficients of its neighbours from a
-  // dense array (0 off the frontier) and takes its own next self step in the
+  // dense array (+0.0 off the frontier) and takes its own next self step in the
   // same launch; cd[t & 1] is read and cd[(t + 1) & 1] written by round t.
   // dblk covers all rows; rows cut into pieces meet in dacc / dcnt (one per
   // such row, 0 between launches).  cd[0] = null turns it off.  dense_free:

@@ -1,6 +1,8 @@
 """HK-PR levels whose coefficients underflow to 0: the vertices still belong to
 the level's frontier, and their additions of 0 touch nothing (in the list form
-the touched list holds n vertices, and the level makes more additions).
+the touched list holds n vertices, and the level makes more additions), also
+when the level goes back from the dense to the list form (which lists the
+frontier from the coefficient array).
 
 With t = 1e-98 a level-k residual is about 1e-98^k / (k! d^k): level 3 is
 still a normal number, level 4 is 0.  eps is put between the level-3 ratios
@@ -51,7 +53,7 @@ def test_case(name):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("bin_min_edges", (-1, 0))
+@pytest.mark.parametrize("bin_min_edges", (-1, 1, 0))
 @pytest.mark.parametrize("name", ("rmat9", "rmat12"))
 def test_zero_coefficients(name, bin_min_edges):
     import paper_1604_07515_amd as plc
