@@ -410,7 +410,7 @@ struct BSelfLds {
   int32_t pref[kMaxSlots + 1];
   long long sh[kBlock / 64 + 1];
   long long excl;
-  int tk[2];
+  unsigned long long tk;
   int qlo, qhi;
   int csup[kScanBlock], cstay[kScanBlock];
   unsigned long long estay[kScanBlock];
@@ -431,14 +431,9 @@ __device__ void b_self(const BatchArgs& a, int NF, BSelfLds& L) {
   unsigned long long* const s_estay = L.estay;
   for (int j = threadIdx.x; j <= B; j += kBlock) s_pref[j] = a.fprefix[j];
   ScanSite* site = &c->scan[BSCAN_FRONTIER];
-  scan_clear_prev(site, a.desc[BSCAN_FRONTIER], a.desc_cap, fixed ? nblk : 0);
-  unsigned long long* desc = a.desc[BSCAN_FRONTIER] + (size_t)site->parity * a.desc_cap;
-  __syncthreads();
-
-  for (int pass = 0;; pass++) {
-    bool last;
-    const int b = fixed ? (pass == 0 ? (int)blockIdx.x : nblk) : scan_ticket(site, nblk, L.tk, &last);
-    if (b >= nblk) break;
+  unsigned long long* desc;
+  for (int b = scan_begin(site, a.desc[BSCAN_FRONTIER], a.desc_cap, nblk, fixed, &L.tk, &desc);
+       b < nblk; b = scan_next(site, nblk, fixed, &L.tk)) {
     const int g0 = b * kSpan + (int)threadIdx.x * IT;
     // the entries' slots (ascending), the block's first and last
     int qk[IT];
@@ -571,7 +566,6 @@ __device__ void b_self(const BatchArgs& a, int NF, BSelfLds& L) {
     }
     __syncthreads();
   }
-  if (fixed && threadIdx.x == 0) (void)scan_retire(site, nblk);
 }
 
 template <class St>
@@ -998,24 +992,21 @@ __global__ __launch_bounds__(kBlock) void k_sw_keys(BatchArgs a) {
 // (kScanItems consecutive ones per thread): body(i0, x) fills the thread's
 // values for the elements i0 .. i0 + kScanItems, then out(i, s, x) gets each
 // with the sum of all values before it, and at the end fin(sum of all).
-// Up to kScanFixed blocks go to the workgroups of the same numbers.
+// Up to kScanFixed blocks go to one workgroup each.
 template <class Load, class Out, class Fin>
 __device__ __forceinline__ void b_scan(const BatchArgs& a, int site_id, long long total,
                                        Load&& load, Out&& out, Fin&& fin) {
   BatchCtl* c = a.ctl;
   __shared__ long long sh[kBlock / 64 + 1];
   __shared__ long long s_excl;
-  __shared__ int s_tk[2];
+  __shared__ unsigned long long s_tk;
   const int nblk = (int)((total + kScanBlock - 1) / kScanBlock);
   const bool fixed = scan_fixed(nblk);
   if (fixed && (int)blockIdx.x >= nblk) return;
   ScanSite* site = &c->scan[site_id];
-  scan_clear_prev(site, a.desc[site_id], a.desc_cap, fixed ? nblk : 0);
-  unsigned long long* desc = a.desc[site_id] + (size_t)site->parity * a.desc_cap;
-  for (int pass = 0;; pass++) {
-    bool last;
-    const int b = fixed ? (pass == 0 ? (int)blockIdx.x : nblk) : scan_ticket(site, nblk, s_tk, &last);
-    if (b >= nblk) break;
+  unsigned long long* desc;
+  for (int b = scan_begin(site, a.desc[site_id], a.desc_cap, nblk, fixed, &s_tk, &desc); b < nblk;
+       b = scan_next(site, nblk, fixed, &s_tk)) {
     const long long i0 = (long long)b * kScanBlock + (long long)threadIdx.x * kScanItems;
     long long xk[kScanItems];
     long long xsum = 0;
@@ -1038,7 +1029,6 @@ __device__ __forceinline__ void b_scan(const BatchArgs& a, int site_id, long lon
     if (b == nblk - 1 && threadIdx.x == 0) fin(s_excl + agg);
     __syncthreads();
   }
-  if (fixed && threadIdx.x == 0) (void)scan_retire(site, nblk);
 }
 
 // Rank map, degrees, p and ids in sweep order, the inclusive volume prefix

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "scan_site.h"
+
 namespace plc {
 
 #define PLC_LANE (threadIdx.x & 63)
@@ -53,13 +55,6 @@ __device__ __forceinline__ long long block_excl_scan(long long x, long long* tot
 // the slots the previous launch used in the other buffer, so the next launch
 // starts from zeroed flags.
 
-struct ScanSite {
-  unsigned int ticket;   // next block ticket
-  unsigned int parity;   // descriptor buffer of the current launch
-  int prev_nblk;         // blocks used by the previous launch
-  int pad;
-};
-
 __device__ __forceinline__ unsigned long long desc_pack(unsigned flag, long long v) {
   return ((unsigned long long)flag << 62) | ((unsigned long long)v & ((1ull << 62) - 1));
 }
@@ -75,38 +70,62 @@ __device__ __forceinline__ void atomic_st64(unsigned long long* p, unsigned long
 
 constexpr long kSpinLimit = 1L << 24;
 
-// Clear the other buffer's slots used by the previous launch (the first
-// `members` workgroups share the work; 0: all of them).  Call once per
-// workgroup at kernel start.
-__device__ __forceinline__ void scan_clear_prev(const ScanSite* site, unsigned long long* desc2,
-                                                int cap, int members = 0) {
-  unsigned par = site->parity;
-  int prev = site->prev_nblk;
-  if (prev > cap) prev = cap;
-  unsigned long long* other = desc2 + (size_t)(par ^ 1u) * cap;
-  const int m = members > 0 ? members : (int)gridDim.x;
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < prev; j += m * blockDim.x)
-    other[j] = 0ull;
-}
-
-// Scans of few blocks: workgroup b takes block b and the workgroups past them
-// leave at once, so the dispenser's word, which every workgroup of the launch
-// adds to otherwise (~10 ns each, one after another), is touched only by the
-// nblk of them as they finish (scan_retire).  Up to kScanFixed blocks: one
-// per CU, so that all of them are resident together and none waits for one
-// that cannot start.
+// Scans of few blocks: the first nblk workgroups draw one ticket each and those
+// past them leave at once, so that the site's word, to which every workgroup of
+// the launch adds otherwise (~10 ns each, one after another), gets nblk
+// additions only.  The block a workgroup takes is its ticket and not its own
+// number: workgroups start in no order across XCDs, and where another stream's
+// launches hold part of the chip, one that waited for a lower number could
+// keep out of its place the very workgroup it waits for.  The holder of a lower
+// ticket has started.  kScanFixed: at most so many such additions, a block per
+// CU.
 constexpr int kScanFixed = 256;
 __device__ __forceinline__ bool scan_fixed(int nblk) {
   return nblk <= kScanFixed && nblk <= (int)gridDim.x;
 }
-// One thread per workgroup, after the workgroup's last use of the site.
-// Returns true in the last of them.
-__device__ __forceinline__ bool scan_retire(ScanSite* site, int nblk) {
-  if (atomicAdd(&site->ticket, 1u) != (unsigned)nblk - 1) return false;
-  site->ticket = 0;
-  site->parity ^= 1u;
-  site->prev_nblk = nblk;
-  return true;
+
+// A draw (one thread): the site's word before it.  The last draw of the launch
+// leaves the word of the next one.
+__device__ __forceinline__ unsigned long long scan_draw(ScanSite* site, int nblk, bool fixed) {
+  const unsigned long long w = atomicAdd(&site->word, 1ull);
+  if (scan_ticket_of(w) == scan_draws(nblk, (int)gridDim.x, fixed) - 1)
+    atomic_st64(&site->word, scan_after(w, nblk));
+  return w;
+}
+
+// The workgroup's first block (>= nblk: none) and the launch's descriptors.
+// With fixed only the first nblk workgroups call it, and one alone draws
+// nothing: it has no descriptors, and the site stays as it was.  sh: one LDS
+// word, which scan_next takes too.
+__device__ __forceinline__ int scan_begin(ScanSite* site, unsigned long long* desc2, int cap,
+                                          int nblk, bool fixed, unsigned long long* sh,
+                                          unsigned long long** desc) {
+  *desc = nullptr;
+  if (fixed && nblk == 1) {
+    __syncthreads();
+    return 0;
+  }
+  if (threadIdx.x == 0) *sh = scan_draw(site, nblk, fixed);
+  __syncthreads();
+  const unsigned long long w = *sh;
+  const unsigned par = scan_parity_of(w);
+  *desc = desc2 + (size_t)par * cap;
+  // the slots of the previous launch, shared out among the workgroups here
+  unsigned long long* const other = desc2 + (size_t)(par ^ 1u) * cap;
+  const int prev = scan_prev_of(w) < cap ? scan_prev_of(w) : cap;
+  const int m = fixed ? nblk : (int)gridDim.x;
+  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < prev; j += m * blockDim.x)
+    other[j] = 0ull;
+  return scan_ticket_of(w);
+}
+// The workgroup's next block (>= nblk: none).
+__device__ __forceinline__ int scan_next(ScanSite* site, int nblk, bool fixed,
+                                         unsigned long long* sh) {
+  if (fixed) return nblk;
+  __syncthreads();
+  if (threadIdx.x == 0) *sh = scan_draw(site, nblk, fixed);
+  __syncthreads();
+  return scan_ticket_of(*sh);
 }
 
 // Decoupled look-back for block b, by the 64 lanes of wave 0 together (call
@@ -115,13 +134,13 @@ __device__ __forceinline__ bool scan_retire(ScanSite* site, int nblk) {
 // back to the nearest inclusive prefix; lanes past block 0 count as an
 // inclusive prefix of 0.  A round that meets a predecessor without a
 // descriptor before any inclusive one waits and reads again.  Predecessors
-// claimed their tickets earlier, so they are running or done; the wait is
+// drew their tickets earlier, so they are running or done; the wait is
 // bounded and raises *fault if it ever runs out.  Returns the exclusive
-// prefix.
+// prefix.  desc: null where there is one block only.
 __device__ long long scan_lookback(unsigned long long* desc, int b, long long agg, int* fault) {
   const int lane = PLC_LANE;
   if (b == 0) {
-    if (lane == 0) atomic_st64(&desc[0], desc_pack(2, agg));
+    if (lane == 0 && desc) atomic_st64(&desc[0], desc_pack(2, agg));
     return 0;
   }
   if (lane == 0) atomic_st64(&desc[b], desc_pack(1, agg));
@@ -153,30 +172,6 @@ __device__ long long scan_lookback(unsigned long long* desc, int b, long long ag
   }
   if (lane == 0) atomic_st64(&desc[b], desc_pack(2, excl + agg));
   return excl;
-}
-
-// Ticket dispenser.  Returns the next block index (>= nblk when exhausted).
-// The workgroup drawing the last ticket (nblk + gridDim.x - 1) retires the
-// launch: it resets the dispenser, flips the descriptor buffer and records
-// nblk for the next launch's clearing pass.  *is_last tells the caller.
-__device__ __forceinline__ int scan_ticket(ScanSite* site, int nblk, int* sh, bool* is_last) {
-  if (threadIdx.x == 0) {
-    unsigned t = atomicAdd(&site->ticket, 1u);
-    int last = 0;
-    if (t == (unsigned)nblk + gridDim.x - 1) {
-      site->ticket = 0;
-      site->parity ^= 1u;
-      site->prev_nblk = nblk;
-      last = 1;
-    }
-    sh[0] = (int)t;
-    sh[1] = last;
-  }
-  __syncthreads();
-  int b = sh[0];
-  *is_last = sh[1] != 0;
-  __syncthreads();
-  return b;
 }
 
 // Last-workgroup detection: true in exactly one workgroup, after all others

@@ -316,20 +316,15 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot, const Ct
   }
   __shared__ long long sh[NT / 64 + 1];
   __shared__ long long s_excl;
-  __shared__ int s_tk[2];
+  __shared__ unsigned long long s_tk;
   __shared__ int32_t s_sup[kScanBlock];
   __shared__ int32_t s_stay[LEVELS ? 1 : kScanBlock];
   __shared__ int s_nsup, s_nstay, s_base;
   const int nblk = (nf + kScanBlock - 1) / kScanBlock;
-  // a frontier of one scan block is handled by workgroup 0 alone, with no
-  // ticket and no look-back (its exclusive prefix is 0; no descriptor is
-  // published and the scan site is left as it was)
-  const bool solo = nblk == 1 && !LIGHT;
   const bool fixed = !LIGHT && scan_fixed(nblk);
   if (fixed && (int)blockIdx.x >= nblk) return;
   ScanSite* site = &c->scan[SCAN_FRONTIER];
-  scan_clear_prev(site, a.desc[SCAN_FRONTIER], a.desc_cap, fixed ? nblk : 0);
-  unsigned long long* desc = a.desc[SCAN_FRONTIER] + (size_t)site->parity * a.desc_cap;
+  unsigned long long* desc;
   const int32_t* F = (t & 1) ? a.fbuf1 : a.fbuf0;
   int32_t* Fn = (t & 1) ? a.fbuf0 : a.fbuf1;
   int32_t* cntn = &c->cnt[(t + 1) & 1];
@@ -339,18 +334,8 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot, const Ct
   const double hk_t = HK ? c->hk_t : 0.0;
   double* const cd = LIGHT ? a.cd[t & 1] : nullptr;
   if (threadIdx.x == 0) { s_nsup = 0; s_nstay = 0; }
-  __syncthreads();
-
-  for (int pass = 0;; pass++) {
-    int b;
-    if (fixed) {
-      if (pass > 0) break;
-      b = blockIdx.x;
-    } else {
-      bool last;
-      b = scan_ticket(site, nblk, s_tk, &last);
-      if (b >= nblk) break;
-    }
+  for (int b = scan_begin(site, a.desc[SCAN_FRONTIER], a.desc_cap, nblk, fixed, &s_tk, &desc);
+       b < nblk; b = scan_next(site, nblk, fixed, &s_tk)) {
     // each thread takes kItems consecutive entries: one workgroup scan
     // of the per-thread sums, then a serial prefix inside the thread.  All
     // loads of the thread's entries go out together, before any store (entry
@@ -417,9 +402,7 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot, const Ct
     if (MODE != kModeNB && !LIGHT) wave_append_all<kItems>(sup, vk, s_sup, &s_nsup);
     long long agg;
     const long long ex = block_excl_scan<NT>(dsum, &agg, sh);
-    if (solo) {
-      if (threadIdx.x == 0) s_excl = 0;
-    } else if (threadIdx.x < 64) {
+    if (threadIdx.x < 64) {
       const long long ex0 = scan_lookback(desc, b, agg, &c->fault);
       if (threadIdx.x == 0) s_excl = ex0;
     }
@@ -446,7 +429,6 @@ __device__ __forceinline__ void self_body(const PlainArgs& a, int slot, const Ct
       block_flush(&c->support_cnt, a.support, a.n, s_sup, &s_nsup, &s_base, &c->fault);
     if (!opt) block_flush(cntn, Fn, a.n, s_stay, &s_nstay, &s_base, &c->fault);
   }
-  if (fixed && !solo && threadIdx.x == 0) (void)scan_retire(site, nblk);
   // (every workgroup has read the state it decided on by the time the last
   // one gets here)
   if (LIGHT && last_block(&c->done[DONE_DENSE], &s_base, false) && threadIdx.x == 0) {
@@ -2050,17 +2032,14 @@ __global__ __launch_bounds__(kBlock) void k_vol_scan(PlainArgs a) {
   double* const out_p = a.sp;
   __shared__ long long sh[kBlock / 64 + 1];
   __shared__ long long s_excl;
-  __shared__ int s_tk[2];
+  __shared__ unsigned long long s_tk;
   const int nblk = (N + kScanBlock - 1) / kScanBlock;
   const bool fixed = scan_fixed(nblk);
   if (fixed && (int)blockIdx.x >= nblk) return;
   ScanSite* site = &c->scan[SCAN_VOL];
-  scan_clear_prev(site, a.desc[SCAN_VOL], a.desc_cap, fixed ? nblk : 0);
-  unsigned long long* desc = a.desc[SCAN_VOL] + (size_t)site->parity * a.desc_cap;
-  for (int pass = 0;; pass++) {
-    bool last;
-    const int b = fixed ? (pass == 0 ? (int)blockIdx.x : nblk) : scan_ticket(site, nblk, s_tk, &last);
-    if (b >= nblk) break;
+  unsigned long long* desc;
+  for (int b = scan_begin(site, a.desc[SCAN_VOL], a.desc_cap, nblk, fixed, &s_tk, &desc); b < nblk;
+       b = scan_next(site, nblk, fixed, &s_tk)) {
     // kScanItems consecutive positions per thread (see k_self)
     const int i0 = b * kScanBlock + (int)threadIdx.x * kScanItems;
     int32_t dk[kScanItems];
@@ -2104,7 +2083,6 @@ __global__ __launch_bounds__(kBlock) void k_vol_scan(PlainArgs a) {
     }
     __syncthreads();
   }
-  if (fixed && threadIdx.x == 0) (void)scan_retire(site, nblk);
 }
 
 // For every support edge (v_k, w): count w with 1 <= rank[w] < k.  Then
@@ -2227,20 +2205,18 @@ __global__ __launch_bounds__(kBlock) void k_cut_scan(PlainArgs a) {
   const int N = c->N;
   __shared__ long long sh[kBlock / 64 + 1];
   __shared__ long long s_excl;
-  __shared__ int s_tk[2];
+  __shared__ unsigned long long s_tk;
   __shared__ int s_last;
   __shared__ long long s_bc[kBlock], s_bd[kBlock], s_bk[kBlock];
   const int nblk = (N + kScanBlock - 1) / kScanBlock;
   const bool fixed = scan_fixed(nblk);
   if (fixed && (int)blockIdx.x >= (nblk > 1 ? nblk : 1)) return;
   ScanSite* site = &c->scan[SCAN_CUT];
-  scan_clear_prev(site, a.desc[SCAN_CUT], a.desc_cap, fixed && nblk > 0 ? nblk : 0);
-  unsigned long long* desc = a.desc[SCAN_CUT] + (size_t)site->parity * a.desc_cap;
+  unsigned long long* desc = nullptr;
   const long long vt = c->vol_total;
-  for (int pass = 0; N > 0; pass++) {
-    bool last;
-    const int b = fixed ? (pass == 0 ? (int)blockIdx.x : nblk) : scan_ticket(site, nblk, s_tk, &last);
-    if (b >= nblk) break;
+  int b = nblk;
+  if (N > 0) b = scan_begin(site, a.desc[SCAN_CUT], a.desc_cap, nblk, fixed, &s_tk, &desc);
+  for (; b < nblk; b = scan_next(site, nblk, fixed, &s_tk)) {
     // kScanItems consecutive positions per thread (see k_self)
     const int i0 = b * kScanBlock + (int)threadIdx.x * kScanItems;
     long long dk[kScanItems];
@@ -2292,13 +2268,9 @@ __global__ __launch_bounds__(kBlock) void k_cut_scan(PlainArgs a) {
     }
     __syncthreads();
   }
-  if (fixed) {
-    if (threadIdx.x == 0) s_last = nblk < 1 || scan_retire(site, nblk);
-    __syncthreads();
-    if (!s_last) return;
-  } else if (!last_block(&c->done[DONE_FINISH], &s_last, false)) {
+  const int members = !fixed ? (int)gridDim.x : nblk > 1 ? nblk : 1;
+  if (members > 1 && !last_block_of(&c->done[DONE_FINISH], &s_last, false, (unsigned)members))
     return;
-  }
   if (N > 0) cut_final(a, c, N, s_bc, s_bd, s_bk);
   if (threadIdx.x == 0) {
     c->t_end = (long long)wall_clock64();
