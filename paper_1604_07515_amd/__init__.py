@@ -9,6 +9,7 @@ GPU is present, the calls raise: there is no CPU fallback.
 from __future__ import annotations
 
 import ctypes as C
+import math
 import os
 import struct
 from dataclasses import dataclass
@@ -565,6 +566,13 @@ def run_noalloc(off, nbr, seed: int, alpha: float, eps: float, rule: int = PLC_R
     return rc, info.as_dict(), ids, p
 
 
+def dense_table_bytes(n: int, arcs: int) -> int:
+    """Arena bytes of the dense rounds' blocks of rows, at most: 32 B a block (as many as
+    csrc/dense_blocks.h bounds), 12 B a row of more than 2048 arcs, 64 groups of 128 B."""
+    blocks = 3 * arcs // 2048 + n // 256 + arcs // 8192 + math.isqrt(arcs * n // 8192) + 6
+    return 32 * blocks + 12 * (arcs // 2048 + 1) + 64 * 128 + 2 * 256
+
+
 def plain_arena_bytes(n: int, arcs: int) -> int:
     """Arena bytes the plain path needs for one graph, plus 64 MiB for results."""
     per_vertex = 168          # offsets, state records, frontier, sweep and HK-PR buffers
@@ -577,6 +585,7 @@ def plain_arena_bytes(n: int, arcs: int) -> int:
     binned = n <= 1536 * 4096
     chunks = (min(max(arcs, 1), 1 << 23) + 2047) // 2048 if binned else 0
     bins = n // 16 + 12 * 2048 + chunks * (8 * 2048 + 4 * 2049) + 7 * 256
-    bins += 16 * n if binned else 0
+    bins += 16 * n + dense_table_bytes(n, arcs) if binned else 0
+    # fixed parts, and what the blocks' alignment to 256 B adds
     return int(per_vertex * (n + 1) + per_arc * arcs + tiles + scans + bins + (64 << 20)
-               + 8 * 1025 + 2048)
+               + 8 * 1025 + (32 << 10))

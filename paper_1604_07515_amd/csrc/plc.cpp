@@ -332,47 +332,11 @@ static void graph_release_blocks(plc_ctx* ctx, plc_graph* g) {
   g->blocks.clear();
 }
 
-// Blocks of the dense round: consecutive rows while they have at most
-// kDenseArcs arcs and kDenseRows rows, and rows times the longest row stays
-// within kDenseSpan (no lane sums more than kDenseSpan / 256 products of a
-// row); a longer row is cut into pieces of kDenseArcs arcs.
-// No blocks (and no dense rounds) when the host has no memory for them.
-static void dense_blocks(const std::vector<int64_t>& off, std::vector<plc::DenseBlk>* out,
+// The dense round's blocks of rows; none (and no dense rounds) when the host
+// has no memory for them.
+static void dense_layout(const std::vector<int64_t>& off, std::vector<plc::DenseBlk>* out,
                          int32_t* nlong) try {
-  const int64_t n = (int64_t)off.size() - 1;
-  *nlong = 0;
-  out->reserve((size_t)(n / plc::kDenseRows + 2 * (off[n] / plc::kDenseArcs) + 16));
-  for (int64_t v = 0; v < n;) {
-    int64_t d = off[v + 1] - off[v];
-    if (d > plc::kDenseArcs) {
-      const int32_t pieces = (int32_t)((d + plc::kDenseArcs - 1) / plc::kDenseArcs);
-      for (int32_t k = 0; k < pieces; k++) {
-        const int64_t e = (int64_t)k * plc::kDenseArcs;
-        out->push_back(plc::DenseBlk{(int32_t)v, pieces, *nlong,
-                                     (int32_t)std::min<int64_t>(plc::kDenseArcs, d - e),
-                                     (long long)(off[v] + e)});
-      }
-      (*nlong)++;
-      v++;
-      continue;
-    }
-    // rows up to `end`, which the row limit and the longest row so far set
-    const int64_t last = off[v] + plc::kDenseArcs;
-    int64_t w = v, top = 0, end = std::min<int64_t>(n, v + plc::kDenseRows);
-    for (; w < end && off[w + 1] <= last; w++) {
-      d = off[w + 1] - off[w];
-      if (d <= top) continue;
-      const int64_t lim = v + plc::kDenseSpan / d;
-      if (w >= lim) break;
-      top = d;
-      end = std::min(end, lim);
-    }
-    const int64_t arcs = off[w] - off[v];
-    if (arcs > 0)  // (isolated vertices take part in no round)
-      out->push_back(plc::DenseBlk{(int32_t)v, (int32_t)(w - v), -1, (int32_t)arcs,
-                                   (long long)off[v]});
-    v = w;
-  }
+  plc::dense_blocks(off, out, nlong);
 } catch (const std::bad_alloc&) {
   out->clear();
   *nlong = 0;
@@ -420,11 +384,11 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
   if (bins_on) {
     bool beside = n >= (int64_t)1 << 21;
     try {
-      if (beside) dense_th = std::thread([&]() { dense_blocks(off, &dblk, &nlong); });
+      if (beside) dense_th = std::thread([&]() { dense_layout(off, &dblk, &nlong); });
     } catch (const std::system_error&) {
       beside = false;
     }
-    if (!beside) dense_blocks(off, &dblk, &nlong);
+    if (!beside) dense_layout(off, &dblk, &nlong);
   }
   // Neighbour ids index per-vertex arrays on the device: always range-checked.
   {

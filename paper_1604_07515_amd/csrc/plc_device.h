@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dense_blocks.h"
 #include "device_util.h"
 #include "sort.h"
 
@@ -119,14 +120,6 @@ struct __align__(64) Ctl {
 // CONVERT: the same, but the round goes back to the list form; LIGHT: the
 // list has been rebuilt, the entries not yet.
 enum : int32_t { DN_LIST = 0, DN_READY = 1, DN_CONVERT = 2, DN_LIGHT = 3 };
-
-// One block of the dense round: nrows consecutive rows from row on (at most
-// kDenseRows, kDenseArcs arcs), or, with lid >= 0, one piece of the arcs of a
-// row longer than kDenseArcs (nrows pieces in all).
-struct __align__(32) DenseBlk {
-  int32_t row, nrows, lid, len;
-  long long first;  // first arc and number of arcs
-};
 
 // A dense round's book for kDenseGroup workgroups, a line of its own: edges
 // of the next frontier << 16 | workgroups done, and its vertices (by parity
@@ -243,10 +236,7 @@ constexpr long long kBinOff = 1ll << 62;  // a threshold no round reaches: binni
 // larger graphs use the atomic scatter only (their width-bound bins alone
 // would crowd out the volume-balanced ones)
 constexpr long long kBinMaxVertices = (long long)kMaxBins * 3 / 4 * kBinWidth;
-// Dense rounds: rows and arcs of one block, and the cost rule (dense_pays).
-constexpr int kDenseRows = 256;
-constexpr int kDenseArcs = 2048;
-constexpr int kDenseSpan = 16384;  // rows of a block x its longest row, at most
+// Dense rounds: the groups that count themselves, and the cost rule (dense_pays).
 constexpr int kDenseGroup = 32;    // workgroups that count themselves on one line
 constexpr int kDenseGroups = 64;
 constexpr long long kDenseBase = 1 << 20;
