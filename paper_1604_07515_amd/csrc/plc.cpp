@@ -518,10 +518,11 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
     void* blk = nullptr;
     const size_t acc_at = (sizeof(plc::DenseBlk) * dblk.size() + 255) & ~(size_t)255;
     const size_t grp_at = (acc_at + 12 * (size_t)(nlong + 1) + 255) & ~(size_t)255;
-    if (!nomem && !dblk.empty())
-      blk = ctx->arena.alloc(grp_at + sizeof(plc::DenseGrp) * plc::kDenseGroups);
+    const size_t blk_bytes = grp_at + sizeof(plc::DenseGrp) * plc::kDenseGroups;
+    if (!nomem && !dblk.empty()) blk = ctx->arena.alloc(blk_bytes);
     if (blk) {
       g->blocks.push_back(blk);
+      g->bytes += (blk_bytes + Arena::kAlign - 1) & ~(Arena::kAlign - 1);
       a.cd[0] = cd;
       a.cd[1] = cd + N;
       a.dense_free = ctx->opt.bin_min_edges == 0;
