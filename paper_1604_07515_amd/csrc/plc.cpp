@@ -28,7 +28,6 @@
 #include <map>
 #include <new>
 #include <set>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -332,14 +331,26 @@ static void graph_release_blocks(plc_ctx* ctx, plc_graph* g) {
   g->blocks.clear();
 }
 
-// The dense round's blocks of rows; none (and no dense rounds) when the host
-// has no memory for them.
-static void dense_layout(const std::vector<int64_t>& off, std::vector<plc::DenseBlk>* out,
-                         int32_t* nlong) try {
-  plc::dense_blocks(off, out, nlong);
+// The dense round's blocks of rows, and behind them, all 0, the sums of the rows
+// cut into pieces and the groups' books, as one block to upload.  Nothing (and
+// no dense rounds) when the host has no memory for it.
+struct DenseTable {
+  std::vector<plc::DenseBlk> data;
+  size_t count = 0, acc_at = 0, cnt_at = 0, grp_at = 0;  // blocks; bytes
+};
+static void dense_layout(const std::vector<int64_t>& off, const int32_t* deg,
+                         DenseTable* t) try {
+  int32_t nlong = 0;
+  plc::dense_blocks(off, deg, &t->data, &nlong);
+  t->count = t->data.size();
+  t->acc_at = sizeof(plc::DenseBlk) * t->count;
+  t->cnt_at = t->acc_at + 8 * (size_t)(nlong + 1);
+  t->grp_at = (t->cnt_at + 4 * (size_t)(nlong + 1) + 127) & ~(size_t)127;
+  const size_t end = t->grp_at + sizeof(plc::DenseGrp) * plc::kDenseGroups;
+  static_assert(sizeof(plc::DenseGrp) % sizeof(plc::DenseBlk) == 0, "whole records");
+  t->data.resize(end / sizeof(plc::DenseBlk));
 } catch (const std::bad_alloc&) {
-  out->clear();
-  *nlong = 0;
+  t->count = 0;
 }
 
 extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
@@ -368,28 +379,10 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
     deg[v] = (int32_t)d;
     maxdeg = std::max(maxdeg, d);
   }
-  // The dense round's blocks of rows (see dense_blocks): 3 ns a row, laid out
-  // beside the range check where that is more than a thread costs (2 ms: its
-  // stack and heap come and go in a process that the GPU maps).
   const bool bins_on = ctx->opt.bin_min_edges >= 0 &&
                        n <= plc::kBinMaxVertices;
-  std::vector<plc::DenseBlk> dblk;
-  int32_t nlong = 0;
-  std::thread dense_th;
-  struct Join {
-    std::thread& t;
-    void operator()() { if (t.joinable()) t.join(); }
-    ~Join() { (*this)(); }
-  } dense_join{dense_th};
-  if (bins_on) {
-    bool beside = n >= (int64_t)1 << 21;
-    try {
-      if (beside) dense_th = std::thread([&]() { dense_layout(off, &dblk, &nlong); });
-    } catch (const std::system_error&) {
-      beside = false;
-    }
-    if (!beside) dense_layout(off, &dblk, &nlong);
-  }
+  DenseTable dense;
+  if (bins_on) dense_layout(off, deg.data(), &dense);
   // Neighbour ids index per-vertex arrays on the device: always range-checked.
   {
     bool ok = true;
@@ -512,14 +505,11 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
   // Dense rounds (same graphs and option): the two coefficient arrays
   // (cleared by the graph init kernel) and the blocks of rows.  Without room
   // for the blocks the graph does without the form.
-  dense_join();
   if (bins_on) {
     double* cd = static_cast<double*>(take(16 * N));
     void* blk = nullptr;
-    const size_t acc_at = (sizeof(plc::DenseBlk) * dblk.size() + 255) & ~(size_t)255;
-    const size_t grp_at = (acc_at + 12 * (size_t)(nlong + 1) + 255) & ~(size_t)255;
-    const size_t blk_bytes = grp_at + sizeof(plc::DenseGrp) * plc::kDenseGroups;
-    if (!nomem && !dblk.empty()) blk = ctx->arena.alloc(blk_bytes);
+    const size_t blk_bytes = sizeof(plc::DenseBlk) * dense.data.size();
+    if (!nomem && dense.count > 0) blk = ctx->arena.alloc(blk_bytes);
     if (blk) {
       g->blocks.push_back(blk);
       g->bytes += (blk_bytes + Arena::kAlign - 1) & ~(Arena::kAlign - 1);
@@ -527,11 +517,12 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
       a.cd[1] = cd + N;
       a.dense_free = ctx->opt.bin_min_edges == 0;
       a.dense_emin = std::max<long long>(1, (num_arcs + 1) / 2);
-      a.ndblk = (int32_t)dblk.size();
-      a.dblk = static_cast<plc::DenseBlk*>(blk);
-      a.dacc = reinterpret_cast<double*>(static_cast<char*>(blk) + acc_at);
-      a.dcnt = reinterpret_cast<unsigned*>(a.dacc + nlong + 1);
-      a.dgrp = reinterpret_cast<plc::DenseGrp*>(static_cast<char*>(blk) + grp_at);
+      char* const at = static_cast<char*>(blk);
+      a.ndblk = (int32_t)dense.count;
+      a.dblk = reinterpret_cast<plc::DenseBlk*>(at);
+      a.dacc = reinterpret_cast<double*>(at + dense.acc_at);
+      a.dcnt = reinterpret_cast<unsigned*>(at + dense.cnt_at);
+      a.dgrp = reinterpret_cast<plc::DenseGrp*>(at + dense.grp_at);
     }
   }
   if (nomem) {
@@ -555,16 +546,21 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
   // Hot destinations: the kHot highest-degree vertices (degree >= 32, ties by
   // id).  Their hot index lives in the idle rank field of the state record.
   {
-    std::vector<int32_t> order(N);
-    for (size_t v = 0; v < N; v++) order[v] = (int32_t)v;
-    const size_t H = std::min<size_t>(N, (size_t)plc::kHot);
+    std::vector<int32_t> order(N + 1);
+    size_t top = 0;
+    for (size_t v = 0; v < N; v++) {  // (no branch: degrees are in no order)
+      order[top] = (int32_t)v;
+      top += g->deg[v] >= 32;
+    }
+    order.resize(top);
+    const size_t H = std::min<size_t>(top, (size_t)plc::kHot);
     auto by_deg = [&](int32_t x, int32_t y) {
       return g->deg[x] != g->deg[y] ? g->deg[x] > g->deg[y] : x < y;
     };
     std::partial_sort(order.begin(), order.begin() + H, order.end(), by_deg);
     g->hotcode_h.assign(N, 0);
     std::vector<int32_t> ids(plc::kHot, 0);
-    for (size_t j = 0; j < H && g->deg[order[j]] >= 32; j++) {
+    for (size_t j = 0; j < H; j++) {
       ids[j] = order[j];
       g->hotcode_h[order[j]] = -(int32_t)(j + 1);
     }
@@ -584,11 +580,9 @@ extern "C" plc_status plc_graph_load(plc_ctx* ctx, int64_t n, int64_t num_arcs,
        hipMemcpyAsync((void*)a.bin_vol, bin_vol.data(), 8 * bin_vol.size(),
                       hipMemcpyHostToDevice, s) != hipSuccess))
     return fail();
-  if (a.cd[0] &&
-      (hipMemcpyAsync((void*)a.dblk, dblk.data(), sizeof(plc::DenseBlk) * dblk.size(),
-                      hipMemcpyHostToDevice, s) != hipSuccess ||
-       hipMemsetAsync(a.dacc, 0, 12 * (size_t)(nlong + 1), s) != hipSuccess ||
-       hipMemsetAsync(a.dgrp, 0, sizeof(plc::DenseGrp) * plc::kDenseGroups, s) != hipSuccess))
+  if (a.cd[0] && hipMemcpyAsync((void*)a.dblk, dense.data.data(),
+                                sizeof(plc::DenseBlk) * dense.data.size(),
+                                hipMemcpyHostToDevice, s) != hipSuccess)
     return fail();
   if (hipMemsetAsync(a.ctl, 0, sizeof(Ctl), s) != hipSuccess) return fail();
   for (int k = 0; k < plc::NUM_SCANS; k++)

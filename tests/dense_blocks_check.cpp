@@ -1,5 +1,5 @@
 // dense_blocks and dense_blocks_most on the CPU: the blocks cover every arc
-// once within their limits, a lane of the dense round sums fewer than 128
+// once within their limits and are as long as those allow, a lane of the dense round sums fewer than 128
 // products of a row, and no graph has more blocks than dense_blocks_most, also
 // those whose blocks end as early as each limit allows.  Prints
 // "n arcs most" lines for test_dense_blocks.py, which builds and runs it.
@@ -23,7 +23,7 @@ static int check(const std::vector<int32_t>& deg) {
   for (int64_t v = 0; v < n; v++) off[v + 1] = off[v] + deg[v];
   std::vector<plc::DenseBlk> blk;
   int32_t nlong = -1;
-  plc::dense_blocks(off, &blk, &nlong);
+  plc::dense_blocks(off, deg.data(), &blk, &nlong);
   int64_t row = 0, lids = 0, at = 0;
   for (size_t i = 0; i < blk.size(); i++) {
     const plc::DenseBlk& b = blk[i];
@@ -44,6 +44,11 @@ static int check(const std::vector<int32_t>& deg) {
     int32_t top = 0;
     for (int r = 0; r < b.nrows; r++) top = std::max(top, deg[b.row + r]);
     CHECK((int64_t)top * b.nrows <= plc::kDenseSpan);
+    if (row + b.nrows < n) {  // it ends only where the next row would break a limit
+      const int32_t d = deg[row + b.nrows];
+      CHECK(b.nrows == plc::kDenseRows || b.len + d > plc::kDenseArcs ||
+            (int64_t)(b.nrows + 1) * std::max(top, d) > plc::kDenseSpan);
+    }
     int lanes = 1;  // of 256 threads per row, a power of two, at most a wave
     while (2 * lanes * b.nrows <= 256 && lanes < 64) lanes *= 2;
     CHECK((top + lanes - 1) / lanes < 2 * plc::kDenseSpan / 256);
