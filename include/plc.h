@@ -170,8 +170,9 @@ typedef struct {
    * the end of its sweep; batched path, from its admission into a slot to the
    * end of its sweep (so it includes rounds shared with other queries) */
   int64_t device_ns;
-  /* plain path only: rounds of at least plc_options.bin_min_edges edges whose
-   * edge scatter was binned or dense, and their edges */
+  /* plain path only: rounds (HK-PR levels, Nibble steps) of at least
+   * plc_options.bin_min_edges edges whose edge scatter was binned or dense, and
+   * their edges */
   int32_t bin_rounds;
   uint32_t flags;     /* the query's flags */
   int64_t bin_edges;

@@ -1523,10 +1523,8 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
     if (threadIdx.x == 0) {
       c->pushes += nf;
       c->edges += E;
-      if (!NB) {
-        c->bin_rounds += 1;
-        c->bin_edges += E;
-      }
+      c->bin_rounds += 1;
+      c->bin_edges += E;
       c->cnt[t & 1] = 0;
       c->round = t + 1;
       if (slot >= 0) a.work_log[2 * slot + 1] = 1;
