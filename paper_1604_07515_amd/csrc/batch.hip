@@ -403,18 +403,19 @@ __global__ __launch_bounds__(kMaxSlots) void k_b_plan(BatchArgs a) {
 // step of the chain slot -> vertex -> record -> p, which is what bounds it.
 // Rounds of up to kScanFixed workgroups of one entry per thread are spread
 // that way over four times the CUs.  32 rounds of 40,000 entries on average
-// (R-MAT 2^22, 256 slots) took 19.2 us each, one entry after another, 18.4 in
-// blocks of 1024 entries with their loads together, and now 12.8; compact
-// tables (R-MAT 2^20, 128 slots, 61,000 entries) 34.7, now 26.0.
+// (R-MAT 2^22, 256 slots) take 12.8 us each (18.4 in blocks of 1024 entries,
+// 19.2 so and one entry after another); compact tables (R-MAT 2^20, 128 slots,
+// 61,000 entries) 26.0 (34.7).
 struct BSelfLds {
   int32_t pref[kMaxSlots + 1];
   long long sh[kBlock / 64 + 1];
   long long excl;
   unsigned long long tk;
   int qlo, qhi;
-  int csup[kScanBlock], cstay[kScanBlock];
-  unsigned long long estay[kScanBlock];
-  int bsup[kScanBlock], bstay[kScanBlock];
+  // per slot of a block's range
+  int csup[kMaxSlots], cstay[kMaxSlots];
+  unsigned long long estay[kMaxSlots];
+  int bsup[kMaxSlots], bstay[kMaxSlots];
 };
 
 template <class St, int IT>
@@ -453,7 +454,8 @@ __device__ void b_self(const BatchArgs& a, int NF, BSelfLds& L) {
     }
     __syncthreads();
     const int qlo = L.qlo;
-    const int range = L.qhi - qlo + 1;  // <= kSpan: each entry is one slot
+    // slots between the first and the last (those without an entry too)
+    const int range = L.qhi - qlo + 1;  // <= B
     for (int j = threadIdx.x; j < range; j += kBlock) {
       s_csup[j] = 0;
       s_cstay[j] = 0;
@@ -1115,8 +1117,8 @@ __global__ __launch_bounds__(kBlock) void k_sw_cut(BatchArgs a) {
 
 // Boundary counts: edges to an earlier rank, in 1024-edge tiles.  One random
 // state word per edge bounds it: 67 G edges/s on dense slots.  The compact
-// tables' first probes of a thread's edges are in flight together (one after
-// another: 79 us a sweep of 13 queries on R-MAT 2^20, now 62).
+// tables' first probes of a thread's edges are in flight together: 62 us a
+// sweep of 13 queries on R-MAT 2^20, 79 one after another.
 template <class St>
 __global__ __launch_bounds__(kBlock) void k_sw_count(BatchArgs a) {
   BatchCtl* c = a.ctl;

@@ -75,8 +75,6 @@ struct __align__(16) SweepSeg : SortSeg {
   int32_t slot;
   long long touch_off;      // first finish entry of the segment (flattened): touched-list
                             // positions (dense) or table records (compact)
-  int32_t n_touch;          // touched-list length (dense) or table capacity (compact)
-  int32_t pad;
   int32_t* out_ids;         // support in sweep order (NULL: discard the vectors)
   double* out_p;            // p at those vertices
   int32_t* out_rid;         // nonzeros of r

@@ -712,7 +712,7 @@ __device__ void loop_rounds(const PlainArgs& a, int slot, int t, int nf) {
 //
 // A round whose frontier's edges are a good part of the graph's arcs needs
 // neither atomics nor pairs: every row w sums the coefficients of its
-// neighbours, read from the dense array cd[t & 1] (0 off the frontier).  The
+// neighbours, read from the dense array cd[t & 1] (+0.0 off the frontier).  The
 // row's sum is complete in one place, so the same lane takes w's next self
 // step at once (p, r, and w's coefficient for round t + 1 into
 // cd[(t + 1) & 1]): a round is one launch with no frontier list.
@@ -720,7 +720,8 @@ __device__ void loop_rounds(const PlainArgs& a, int slot, int t, int nf) {
 // A workgroup takes a block of rows with at most kDenseArcs arcs, so that its
 // products fit 16 KB of LDS and seven workgroups share a CU; rows are then
 // summed by 256 / rows lanes each, and a block's rows times its longest row
-// is bounded so that no lane sums more than 64 products.  Longer rows are cut
+// is bounded (kDenseSpan) so that a lane sums fewer than 128 products: 256 /
+// rows lanes would have 64 at most, and are a power of two.  Longer rows are cut
 // into pieces that add up in dacc; the last piece finishes the row.
 
 struct DenseLds {
@@ -1092,8 +1093,8 @@ __device__ __forceinline__ bool dense_wanted(const PlainArgs& a, const Ctl* c, i
 }
 
 // The self launch of PR-Nibble.  A frontier of at most one scan block goes
-// to loop_rounds, run by workgroup 0; the others leave.  (They used to be
-// counted out first, 256 additions to one word at ~10 ns each.)
+// to loop_rounds, run by workgroup 0; the others leave (counting them out would
+// be 256 additions to one word at ~10 ns each).
 __global__ __launch_bounds__(kSelfBlk) void k_self(PlainArgs a, int slot) {
   Ctl* c = a.ctl;
   const CtlHead h = ctl_head(c);
@@ -1532,11 +1533,10 @@ __global__ __launch_bounds__(kBlock) void k_bin_apply(PlainArgs a, int slot) {
   }
 }
 
-// Nibble steps are binned as PR-Nibble rounds are: 20 steps of up to 6 M edges
-// (R-MAT 2^22, eps 1e-8) took 189 us each with one atomic per edge, now 37 in
-// pass A, the halves included, and 70 in pass B.
 // The kept halves of a binned Nibble step, added before pass B (a launch of
-// its own) adds the contributions: an entry's vertex gets h = rho / 2.
+// its own) adds the contributions: an entry's vertex gets h = rho / 2.  20 steps
+// of up to 6 M edges (R-MAT 2^22, eps 1e-8) take 37 us each in pass A, the
+// halves included, and 70 in pass B; with one atomic per edge 189.
 __device__ void nb_halves(const PlainArgs& a, int t, int nf, double eps, NbLds& L) {
   Ctl* c = a.ctl;
   const int32_t* Fc = (t & 1) ? a.fbuf1 : a.fbuf0;
@@ -2457,9 +2457,9 @@ hipError_t launch_copy_result(hipStream_t s, const PlainArgs& a, int32_t* ids, d
   return hipGetLastError();
 }
 
-// Before the read-back that tells the sizes, so that a query ends with it: the
-// copy launched after it cost another launch and wait (R-MAT 2^12, one query:
-// 163 us, now 144; R-MAT 2^20 288, now 268).
+// Before the read-back that tells the sizes, so that a query ends with it: one
+// query on R-MAT 2^12 takes 144 us (163 with the copy launched after it, another
+// launch and wait), on R-MAT 2^20 268 (288).
 __global__ __launch_bounds__(kBlock) void k_copy_ahead(PlainArgs a, char* block,
                                                        unsigned long long cap, int residual) {
   Ctl* c = a.ctl;

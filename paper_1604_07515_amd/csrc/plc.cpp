@@ -2070,7 +2070,6 @@ static plc_status batch_step(plc_ctx* ctx, plc_graph* g, int32_t* in_flight, uin
     // finish entries: the touched list (dense) or every table record (compact)
     const long long F = E.compact ? (long long)E.qcap[q] : T;
     sg.touch_off = touch_total;
-    sg.n_touch = (int32_t)F;
     if (res.block) {
       char* b = static_cast<char*>(res.block);
       res.ids = reinterpret_cast<int32_t*>(b);
